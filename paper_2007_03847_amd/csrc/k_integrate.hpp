@@ -142,6 +142,65 @@ __device__ __forceinline__ void sincos_many(const R (&x)[N], R (&s)[N], R (&c)[N
   }
 }
 
+// sin d and 1 - cos d of a lane's N angle deviations d.  When every active
+// lane's angles are below half a radian (the usual case for deviations from the
+// operating point), both come straight from their Taylor polynomials in d^2
+// (sin through d^13 and 1 - cos through d^14 in FP64, d^7 and d^8 in FP32: the
+// first term left out is below half an ulp), 15 operations in FP64 against 23
+// for the half-angle form below, and without its doubled rounding; else from
+// one sin/cos of d/2 with the full reduction, 1 - cos d = 2 sin^2(d/2), which
+// has no cancellation either.  live[k] = false marks a machine without EMF: its
+// angle multiplies zero and does not decide the branch.
+__device__ __forceinline__ void rotation_poly(double d, double& sd, double& omc) {
+  const double r2 = d * d;
+  double ps = 1.0 / 6227020800.0;
+  ps = fma3(ps, r2, -1.0 / 39916800.0);
+  ps = fma3(ps, r2, 1.0 / 362880.0);
+  ps = fma3(ps, r2, -1.0 / 5040.0);
+  ps = fma3(ps, r2, 1.0 / 120.0);
+  ps = fma3(ps, r2, -1.0 / 6.0);
+  sd = fma(d * r2, ps, d);
+  double pc = 1.0 / 87178291200.0;
+  pc = fma3(pc, r2, -1.0 / 479001600.0);
+  pc = fma3(pc, r2, 1.0 / 3628800.0);
+  pc = fma3(pc, r2, -1.0 / 40320.0);
+  pc = fma3(pc, r2, 1.0 / 720.0);
+  pc = fma3(pc, r2, -1.0 / 24.0);
+  pc = fma(pc, r2, 0.5);
+  omc = r2 * pc;
+}
+__device__ __forceinline__ void rotation_poly(float d, float& sd, float& omc) {
+  const float r2 = d * d;
+  float ps = -1.0f / 5040.0f;
+  ps = fmaf(ps, r2, 1.0f / 120.0f);
+  ps = fmaf(ps, r2, -1.0f / 6.0f);
+  sd = fmaf(d * r2, ps, d);
+  float pc = -1.0f / 40320.0f;
+  pc = fmaf(pc, r2, 1.0f / 720.0f);
+  pc = fmaf(pc, r2, -1.0f / 24.0f);
+  pc = fmaf(pc, r2, 0.5f);
+  omc = r2 * pc;
+}
+template <typename R, int N>
+__device__ __forceinline__ void rotation_many(const R (&d)[N], const bool (&live)[N], R (&sd)[N],
+                                              R (&omc)[N]) {
+  bool small = true;
+#pragma unroll
+  for (int k = 0; k < N; ++k) small = small && (!live[k] || fabs(d[k]) < R(0.5));
+  if (sincos_all_small(small)) [[likely]] {
+#pragma unroll
+    for (int k = 0; k < N; ++k) rotation_poly(d[k], sd[k], omc[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      R sh, ch;
+      sincos_r_nb(live[k] ? d[k] * R(0.5) : R(0), sh, ch);
+      sd[k] = R(2) * sh * ch;
+      omc[k] = R(2) * sh * sh;
+    }
+  }
+}
+
 // The FP64 common-angle offset in two state slots: the exact bits of the
 // double (two 32-bit halves for an FP32 state array), so that a run split
 // into time chunks gives the same bits as a run in one chunk.
@@ -198,7 +257,9 @@ __device__ __forceinline__ void swing_rhs(const R* cfg, const R* sdeg, const R w
   // Re-derive the pointer at every stage: the compiler then streams the
   // machine data through scalar loads instead of keeping it live in (spilled)
   // registers across stages and steps.
-  asm volatile("" : "+s"(cfg));
+  // (One or two machines fit the scalar registers: there the reload would put a
+  // scalar load's latency on every stage of a latency-bound kernel.)
+  if constexpr (NG > 2) asm volatile("" : "+s"(cfg));
   const cptr<R> cf = (cptr<R>)cfg;
   // general processes first: their injections feed the machines
   R xin[GEN ? PM : 1];
@@ -208,17 +269,28 @@ __device__ __forceinline__ void swing_rhs(const R* cfg, const R* sdeg, const R w
     for (int p = 0; p < PM; ++p) kx[p] = sde_rhs<R>(sq + p * kSdeCols, yx[p], wv[p], xin[p]);
   }
   R dc[NG], ds[NG];
+  R sdv[NG], omcv[NG];
+  if constexpr (NG <= 2) {
+    bool live[NG];
 #pragma unroll
-  for (int k = 0; k < NG; ++k) {
+    for (int k = 0; k < NG; ++k) live[k] = cf[L.c0() + k] != R(0) || cf[L.s0() + k] != R(0);
+    rotation_many(yd, live, sdv, omcv);
+  } else {
     // the branch-free form: a lane's machines are interleaved by the compiler
     // around the scalar loads of their data
-    R sh, ch;
-    sincos_r_nb(yd[k] * R(0.5), sh, ch);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+      R sh, ch;
+      sincos_r_nb(yd[k] * R(0.5), sh, ch);
+      sdv[k] = R(2) * sh * ch;   // sin d
+      omcv[k] = R(2) * sh * sh;  // 1 - cos d
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
     const R c0 = cf[L.c0() + k], s0 = cf[L.s0() + k];
-    const R sd = R(2) * sh * ch;   // sin d
-    const R omc = R(2) * sh * sh;  // 1 - cos d
-    dc[k] = -(c0 * omc + s0 * sd);
-    ds[k] = c0 * sd - s0 * omc;
+    dc[k] = -(c0 * omcv[k] + s0 * sdv[k]);
+    ds[k] = c0 * sdv[k] - s0 * omcv[k];
   }
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
@@ -271,40 +343,36 @@ __device__ __forceinline__ double rrf_u_lane(const IntegArgs<R>& a, double coff,
   return u;
 }
 
-// Per-wave two-pass statistics of one output time through an LDS transpose:
-// lane v of the wave reduces variable v over the wave's valid trajectories.
-template <typename R, int NG, int PM>
-__device__ __forceinline__ void emit_step(const IntegArgs<R>& a, double (*tile)[65], int lane,
-                                          int cnt, int64_t s, int slot, double coff,
+// Output steps a wave collects before it reduces them: as many as give about
+// half the lanes a (step, variable) row each, one where a step has more
+// variables than that.  (One machine, 1000 samples, 1000 steps, FP64: 5.74 ms
+// with the rows reduced step by step by three lanes; 32 rows, not 64, keep the
+// tile at 17 KB, so that nine waves still fit a CU at large N.)
+template <int VM>
+constexpr int lane_steps() {
+  return VM >= 32 ? 1 : 32 / VM;
+}
+
+// The outputs of step s into row b of the wave's tile, and of a selected
+// sample into its trajectory.
+template <typename R, int NG, int PM, int VM>
+__device__ __forceinline__ void emit_step(const IntegArgs<R>& a, double (*tile)[VM][65], int b,
+                                          int lane, int64_t s, int slot, double coff,
                                           const R (&yd)[NG], const R (&yw)[NG],
                                           const R (&yx)[PM]) {
   const int n = a.n, P = a.P, V = a.V;
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
     if (i < n) {
-      tile[i][lane] = coff + (double)yd[i];
-      tile[n + i][lane] = (double)yw[i];
+      tile[b][i][lane] = coff + (double)yd[i];
+      tile[b][n + i][lane] = (double)yw[i];
     }
   }
 #pragma unroll
   for (int p = 0; p < PM; ++p)
-    if (p < P) tile[2 * n + p][lane] = (double)yx[p];
-  __syncthreads();
-  const int64_t S1 = a.S + 1;
-  for (int v = lane; v < V; v += 64) {
-    double sm = 0.0;
-    for (int j = 0; j < cnt; ++j) sm += tile[v][j];
-    const double mu = sm / (double)cnt;
-    double m2 = 0.0;
-    for (int j = 0; j < cnt; ++j) {
-      const double d = tile[v][j] - mu;
-      m2 += d * d;
-    }
-    double2* dst = reinterpret_cast<double2*>(a.partial);
-    dst[((int64_t)blockIdx.x * S1 + s) * V + v] = make_double2(mu, m2);
-  }
+    if (p < P) tile[b][2 * n + p][lane] = (double)yx[p];
   if (slot >= 0) {
-    double* o = a.traj + ((int64_t)slot * S1 + s) * V;
+    double* o = a.traj + ((int64_t)slot * (a.S + 1) + s) * V;
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       if (i < n) {
@@ -316,14 +384,54 @@ __device__ __forceinline__ void emit_step(const IntegArgs<R>& a, double (*tile)[
     for (int p = 0; p < PM; ++p)
       if (p < P) o[2 * n + p] = (double)yx[p];
   }
+}
+
+// Two-pass statistics of the nb collected steps from s_first on, a lane per
+// (step, variable) row of the wave's cnt valid trajectories, each sum in four
+// parts over entries j mod 4.
+template <typename R, int VM>
+__device__ __forceinline__ void reduce_steps(const IntegArgs<R>& a, double (*tile)[VM][65],
+                                             int lane, int cnt, int64_t s_first, int nb) {
+  const int V = a.V;
+  const int64_t S1 = a.S + 1;
+  __syncthreads();
+  for (int rv = lane; rv < nb * V; rv += 64) {
+    const int b = rv / V, v = rv % V;
+    const double* row = tile[b][v];
+    const double k = row[0];  // the mean as an offset from the first sample: exact for equal ones
+    double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
+    int j = 0;
+    for (; j + 3 < cnt; j += 4) {
+      q0 += row[j] - k;
+      q1 += row[j + 1] - k;
+      q2 += row[j + 2] - k;
+      q3 += row[j + 3] - k;
+    }
+    for (; j < cnt; ++j) q0 += row[j] - k;
+    const double mu = k + ((q0 + q1) + (q2 + q3)) / (double)cnt;
+    q0 = q1 = q2 = q3 = 0.0;
+    for (j = 0; j + 3 < cnt; j += 4) {
+      const double d0 = row[j] - mu, d1 = row[j + 1] - mu, d2 = row[j + 2] - mu, d3 = row[j + 3] - mu;
+      q0 = fma(d0, d0, q0);
+      q1 = fma(d1, d1, q1);
+      q2 = fma(d2, d2, q2);
+      q3 = fma(d3, d3, q3);
+    }
+    for (; j < cnt; ++j) {
+      const double d = row[j] - mu;
+      q0 = fma(d, d, q0);
+    }
+    double2* dst = reinterpret_cast<double2*>(a.partial);
+    dst[((int64_t)blockIdx.x * S1 + s_first + b) * V + v] = make_double2(mu, (q0 + q1) + (q2 + q3));
+  }
   __syncthreads();
 }
 
 template <typename R, int NG, int PM, bool GEN = false>
 __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
   constexpr PackLayout L{NG, PM};
-  constexpr int VM = 2 * NG + PM;
-  __shared__ double tile[VM][65];
+  constexpr int VM = 2 * NG + PM, D = lane_steps<VM>();
+  __shared__ double tile[D][VM][65];
   const int lane = threadIdx.x;
   const int64_t gidx = (int64_t)blockIdx.x * 64 + lane;
   const int64_t N = a.N;
@@ -339,6 +447,8 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
   R yd[NG], yw[NG], yx[PM];
   double coff = 0.0;  // common-angle offset of the trajectory (see IntegArgs::recenter)
   double racc = 0.0;  // the epilogue's RRF sum (see IntegArgs::rrf_w)
+  int nbuf = 0;       // steps in the tile, from s_first on
+  int64_t s_first = 0;
   if (a.s_begin == 0) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
@@ -347,7 +457,8 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
     }
 #pragma unroll
     for (int p = 0; p < PM; ++p) yx[p] = cf[L.xi0() + p];
-    emit_step<R, NG, PM>(a, tile, lane, cnt, 0, slot, coff, yd, yw, yx);
+    emit_step<R, NG, PM, VM>(a, tile, 0, lane, 0, slot, coff, yd, yw, yx);
+    nbuf = 1;
     if (a.rrf_w) {
       const double u = rrf_u_lane<R, NG, PM>(a, coff, yd, yw, yx);
       racc = 0.5 * u * u;
@@ -439,12 +550,18 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
 #pragma unroll
       for (int i = 0; i < NG; ++i) yd[i] -= ref;
     }
-    emit_step<R, NG, PM>(a, tile, lane, cnt, s + 1, slot, coff, yd, yw, yx);
+    if (nbuf == D) {
+      reduce_steps<R, VM>(a, tile, lane, cnt, s_first, nbuf);
+      nbuf = 0;
+    }
+    if (nbuf == 0) s_first = s + 1;
+    emit_step<R, NG, PM, VM>(a, tile, nbuf++, lane, s + 1, slot, coff, yd, yw, yx);
     if (a.rrf_w) {
       const double u = rrf_u_lane<R, NG, PM>(a, coff, yd, yw, yx);
       racc += (s + 1 == a.S ? 0.5 : 1.0) * u * u;
     }
   }
+  reduce_steps<R, VM>(a, tile, lane, cnt, s_first, nbuf);
   if (a.rrf_w && valid) {
     a.rrf_acc[gidx] = racc;
     if (a.s_end == a.S) a.rrf[gidx] = sqrt(racc / (double)a.S);

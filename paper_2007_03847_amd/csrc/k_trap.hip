@@ -93,8 +93,8 @@ __device__ __forceinline__ void rhs_and_jac(const double* cfg, double wb, const 
 template <int NG, int PM>
 __global__ void __launch_bounds__(64) k_trap_lane(IntegArgs<double> a) {
   constexpr PackLayout L{NG, PM};
-  constexpr int VM = 2 * NG + PM;
-  __shared__ double tile[VM][65];
+  constexpr int VM = 2 * NG + PM, D = lane_steps<VM>();
+  __shared__ double tile[D][VM][65];
   __shared__ double mat[NG * NG * 64];
   const int lane = threadIdx.x;
   const int64_t gidx = (int64_t)blockIdx.x * 64 + lane;
@@ -111,12 +111,15 @@ __global__ void __launch_bounds__(64) k_trap_lane(IntegArgs<double> a) {
 
   double yd[NG], yw[NG], yx[PM];
   double racc = 0.0;  // the epilogue's RRF sum (see IntegArgs::rrf_w)
+  int nbuf = 0;       // steps in the tile, from s_first on
+  int64_t s_first = 0;
   if (a.s_begin == 0) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) { yd[i] = 0.0; yw[i] = 0.0; }
 #pragma unroll
     for (int p = 0; p < PM; ++p) yx[p] = cf[L.xi0() + p];
-    emit_step<double, NG, PM>(a, tile, lane, cnt, 0, slot, 0.0, yd, yw, yx);
+    emit_step<double, NG, PM, VM>(a, tile, 0, lane, 0, slot, 0.0, yd, yw, yx);
+    nbuf = 1;
     if (a.rrf_w) {
       const double u = rrf_u_lane<double, NG, PM>(a, 0.0, yd, yw, yx);
       racc = 0.5 * u * u;
@@ -233,12 +236,18 @@ __global__ void __launch_bounds__(64) k_trap_lane(IntegArgs<double> a) {
     for (int i = 0; i < NG; ++i) { yd[i] = zd[i]; yw[i] = zw[i]; }
 #pragma unroll
     for (int p = 0; p < PM; ++p) yx[p] = zx[p];
-    emit_step<double, NG, PM>(a, tile, lane, cnt, s + 1, slot, 0.0, yd, yw, yx);
+    if (nbuf == D) {
+      reduce_steps<double, VM>(a, tile, lane, cnt, s_first, nbuf);
+      nbuf = 0;
+    }
+    if (nbuf == 0) s_first = s + 1;
+    emit_step<double, NG, PM, VM>(a, tile, nbuf++, lane, s + 1, slot, 0.0, yd, yw, yx);
     if (a.rrf_w) {
       const double u = rrf_u_lane<double, NG, PM>(a, 0.0, yd, yw, yx);
       racc += (s + 1 == a.S ? 0.5 : 1.0) * u * u;
     }
   }
+  reduce_steps<double, VM>(a, tile, lane, cnt, s_first, nbuf);
   if (a.rrf_w && valid) {
     a.rrf_acc[gidx] = racc;
     if (a.s_end == a.S) a.rrf[gidx] = sqrt(racc / (double)a.S);
