@@ -240,22 +240,31 @@ hipError_t launch_kron(const NetDev& net, double2* work, double2* Yred, int* sta
 // Operating point.  Pe_i = Re{E~_i conj(I_i)}, I = Y E~ + Yinf V_inf.  Given
 // delta0: Pm defaults to Pe(delta0) (equilibrium).  Without delta0 (infinite
 // bus): Newton on Pe(delta) = Pm from delta = 0, dense LU with partial
-// pivoting, serial in one thread (small n).
+// pivoting.
 // ---------------------------------------------------------------------------
+// Et and I of the machines at angles d: thread i takes machine i, its current
+// summed over k in index order.
 __device__ void op_currents(const SetupDev& s, const double* d, double2* Et, double2* I) {
   const int n = s.n;
-  for (int k = 0; k < n; ++k) Et[k] = make_double2(s.E[k] * cos(d[k]), s.E[k] * sin(d[k]));
-  for (int i = 0; i < n; ++i) {
+  for (int k = threadIdx.x; k < n; k += blockDim.x)
+    Et[k] = make_double2(s.E[k] * cos(d[k]), s.E[k] * sin(d[k]));
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
     double2 c = (s.inf_bus && s.Yinf) ? make_double2(s.Yinf[i].x * s.V_inf, s.Yinf[i].y * s.V_inf)
                                       : make_double2(0.0, 0.0);
+#pragma unroll 8
     for (int k = 0; k < n; ++k) c = cadd(c, cmul(s.Y[(int64_t)i * n + k], Et[k]));
     I[i] = c;
   }
+  __syncthreads();
 }
 
-__global__ void k_setup(SetupDev s) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int n = s.n, P = s.P;
+// One workgroup.  Bound by latency: a thread per machine walks its row of Y
+// (one thread for all machines took 47 us for 10 machines and 13.5 ms for
+// 200).  The dense solve of a Newton step stays with one thread: an
+// infinite-bus system that gives Pm has few machines.
+__global__ void __launch_bounds__(256) k_setup(SetupDev s) {
+  const int n = s.n, P = s.P, tid = threadIdx.x, bd = blockDim.x;
   CanonLayout L{n, P};
   double* cn = s.canon;
   double* d = cn + L.delta0();
@@ -263,15 +272,16 @@ __global__ void k_setup(SetupDev s) {
   double2* I = Et + n;
   double* J = (double*)(I + n);
   double* rhs = J + (int64_t)n * n;
+  __shared__ int s_state;  // 0: iterate, 1: converged, 2: singular
   int ok = 1;
-  if (s.delta0) {
-    for (int i = 0; i < n; ++i) d[i] = s.delta0[i];
-  } else {
-    for (int i = 0; i < n; ++i) d[i] = 0.0;
+  for (int i = tid; i < n; i += bd) d[i] = s.delta0 ? s.delta0[i] : 0.0;
+  if (tid == 0) s_state = 0;
+  __syncthreads();
+  if (!s.delta0) {
     ok = 0;
     for (int it = 0; it < 100; ++it) {
       op_currents(s, d, Et, I);
-      for (int i = 0; i < n; ++i) {
+      for (int i = tid; i < n; i += bd) {
         const double pe = Et[i].x * I[i].x + Et[i].y * I[i].y;
         rhs[i] = s.Pm[i] - pe;
         for (int k = 0; k < n; ++k) {
@@ -282,44 +292,52 @@ __global__ void k_setup(SetupDev s) {
           J[(int64_t)i * n + k] = v;
         }
       }
-      // solve J dx = rhs
-      int sing = 0;
-      for (int k = 0; k < n && !sing; ++k) {
-        int piv = k;
-        double best = fabs(J[(int64_t)k * n + k]);
-        for (int r = k + 1; r < n; ++r)
-          if (fabs(J[(int64_t)r * n + k]) > best) { best = fabs(J[(int64_t)r * n + k]); piv = r; }
-        if (best == 0.0) { sing = 1; break; }
-        if (piv != k) {
-          for (int c = 0; c < n; ++c) {
-            const double t = J[(int64_t)k * n + c];
-            J[(int64_t)k * n + c] = J[(int64_t)piv * n + c];
-            J[(int64_t)piv * n + c] = t;
+      __syncthreads();
+      if (tid == 0) {  // solve J dx = rhs
+        int sing = 0;
+        for (int k = 0; k < n && !sing; ++k) {
+          int piv = k;
+          double best = fabs(J[(int64_t)k * n + k]);
+          for (int r = k + 1; r < n; ++r)
+            if (fabs(J[(int64_t)r * n + k]) > best) { best = fabs(J[(int64_t)r * n + k]); piv = r; }
+          if (best == 0.0) { sing = 1; break; }
+          if (piv != k) {
+            for (int c = 0; c < n; ++c) {
+              const double t = J[(int64_t)k * n + c];
+              J[(int64_t)k * n + c] = J[(int64_t)piv * n + c];
+              J[(int64_t)piv * n + c] = t;
+            }
+            const double t = rhs[k]; rhs[k] = rhs[piv]; rhs[piv] = t;
           }
-          const double t = rhs[k]; rhs[k] = rhs[piv]; rhs[piv] = t;
+          for (int r = k + 1; r < n; ++r) {
+            const double f = J[(int64_t)r * n + k] / J[(int64_t)k * n + k];
+            for (int c = k; c < n; ++c) J[(int64_t)r * n + c] -= f * J[(int64_t)k * n + c];
+            rhs[r] -= f * rhs[k];
+          }
         }
-        for (int r = k + 1; r < n; ++r) {
-          const double f = J[(int64_t)r * n + k] / J[(int64_t)k * n + k];
-          for (int c = k; c < n; ++c) J[(int64_t)r * n + c] -= f * J[(int64_t)k * n + c];
-          rhs[r] -= f * rhs[k];
+        if (sing) {
+          s_state = 2;
+        } else {
+          double nrm = 0.0;
+          for (int k = n - 1; k >= 0; --k) {
+            double acc = rhs[k];
+            for (int j = k + 1; j < n; ++j) acc -= J[(int64_t)k * n + j] * rhs[j];
+            rhs[k] = acc / J[(int64_t)k * n + k];
+          }
+          for (int i = 0; i < n; ++i) {
+            d[i] += rhs[i];
+            nrm = fmax(nrm, fabs(rhs[i]));
+          }
+          if (nrm <= 1e-15) s_state = 1;
         }
       }
-      if (sing) break;
-      double nrm = 0.0;
-      for (int k = n - 1; k >= 0; --k) {
-        double acc = rhs[k];
-        for (int j = k + 1; j < n; ++j) acc -= J[(int64_t)k * n + j] * rhs[j];
-        rhs[k] = acc / J[(int64_t)k * n + k];
-      }
-      for (int i = 0; i < n; ++i) {
-        d[i] += rhs[i];
-        nrm = fmax(nrm, fabs(rhs[i]));
-      }
-      if (nrm <= 1e-15) { ok = 1; break; }
+      __syncthreads();
+      if (s_state != 0) break;  // uniform: read after the barrier, written before it
     }
+    ok = s_state == 1;
   }
   op_currents(s, d, Et, I);
-  for (int i = 0; i < n; ++i) {
+  for (int i = tid; i < n; i += bd) {
     const double pe = Et[i].x * I[i].x + Et[i].y * I[i].y;
     const double pm = s.Pm ? s.Pm[i] : pe;
     cn[L.c0() + i] = Et[i].x;
@@ -330,21 +348,21 @@ __global__ void k_setup(SetupDev s) {
     cn[L.dmp() + i] = s.D[i];
     cn[L.inv2h() + i] = 1.0 / (2.0 * s.H[i]);
     cn[L.pm() + i] = pm;
-    for (int k = 0; k < n; ++k) {
-      cn[L.yre() + (int64_t)i * n + k] = s.Y[(int64_t)i * n + k].x;
-      cn[L.yim() + (int64_t)i * n + k] = s.Y[(int64_t)i * n + k].y;
-    }
   }
-  for (int p = 0; p < P; ++p) {
+  for (int64_t q = tid; q < (int64_t)n * n; q += bd) {
+    cn[L.yre() + q] = s.Y[q].x;
+    cn[L.yim() + q] = s.Y[q].y;
+  }
+  for (int p = tid; p < P; p += bd) {
     cn[L.theta() + p] = s.theta[p];
     cn[L.sigma() + p] = s.sigma[p];
     cn[L.xi0() + p] = s.xi0 ? s.xi0[p] : 0.0;
   }
-  *s.status = ok ? 0 : -6;
+  if (tid == 0) *s.status = ok ? 0 : -6;
 }
 
 hipError_t launch_setup(const SetupDev& s, hipStream_t st) {
-  hipLaunchKernelGGL(k_setup, dim3(1), dim3(64), 0, st, s);
+  hipLaunchKernelGGL(k_setup, dim3(1), dim3(s.n <= 64 ? 64 : 256), 0, st, s);
   return hipGetLastError();
 }
 
