@@ -23,183 +23,362 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
   const double r = b.x / b.y, d = b.x * r + b.y;
   return make_double2((a.x * r + a.y) / d, (a.y * r - a.x) / d);
 }
-__device__ __forceinline__ double cabs2(double2 a) { return sqrt(a.x * a.x + a.y * a.y); }
 
 // ---------------------------------------------------------------------------
-// Kron reduction (eq. 2 eliminated): one workgroup of 256 threads.  The
-// augmented system [Y_BB | Y_BA] (n_bus rows, n_bus + n_gen columns) lives in
-// LDS when it fits (else in the global work buffer).  Thread b assembles row b
-// alone, scanning branches, loads and generators in index order, so the sums
-// are deterministic.  Gaussian elimination with partial pivoting (pivot: the
-// largest |a_rk|, lowest row on ties, found by wave shuffles), then back
-// substitution gives X = Y_BB^-1 Y_BA and Y_red = Y_AA - Y_AB X.
+// Kron reduction (eq. 2 eliminated) of a small network: one workgroup of 512
+// threads, bound by the latency of its n_bus elimination steps.  The augmented
+// system [Y_BB | Y_BA] (n_bus rows, W = n_bus + n_gen columns) lives in LDS when
+// it fits (n_bus W <= 4096).  Branches, loads and generators enter a row in
+// index order, so the sums are deterministic.  Gauss-Jordan elimination with
+// partial pivoting on rows that stay where they are: in step k every wave
+// finds the pivot (the largest max(|Re|, |Im|) of a_rk, to 18 bits, over the rows
+// not yet used, the lowest row on ties) by itself, and every element of the other rows and of the columns
+// beyond k is updated from the pivot row and column k, which the step leaves
+// alone, so one barrier per step suffices and no back substitution follows:
+// X = Y_BB^-1 Y_BA stands in the pivot rows and Y_red = Y_AA - Y_AB X.  39 buses
+// and 10 machines: 160 us with row exchanges, four barriers per step, a
+// complex division per element and a back substitution.
 // ---------------------------------------------------------------------------
 constexpr int kKronLdsComplex = 4096;  // 64 KB of double2
+constexpr int kKronStage = 256;        // branches staged in LDS at a time
 
-__device__ __forceinline__ void kron_pivot_reduce(double& v, int& idx) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const double v2 = __shfl_xor(v, off);
-    const int i2 = __shfl_xor(idx, off);
-    if (v2 > v || (v2 == v && i2 < idx)) {
-      v = v2;
-      idx = i2;
-    }
-  }
+// 1 / b = conj(b) / |b|^2, the reciprocal by the hardware's estimate and two Newton
+// steps (about 45 cycles on the chain of every elimination step, a division of
+// doubles takes 75 and Smith's algorithm two of them in a row).  |b|^2 stays far
+// inside the range of a double for admittances; a zero b gives NaN.
+__device__ __forceinline__ double2 cinv(double2 b) {
+  const double m = fma(b.x, b.x, b.y * b.y);
+  double r = __builtin_amdgcn_rcp(m);
+  r = fma(fma(-m, r, 1.0), r, r);
+  r = fma(fma(-m, r, 1.0), r, r);
+  return make_double2(b.x * r, -b.y * r);
 }
 
-__global__ void __launch_bounds__(256) k_kron(NetDev net, double2* __restrict__ gwork,
-                                              double2* __restrict__ Yred, int* status) {
+// The largest key over the wave's lanes: rows of 16 by DPP, then the four rows.
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  auto step = [&](unsigned o) { v = o > v ? o : v; };
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));   // lane ^ 1
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));   // lane ^ 2
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));  // half row mirrored
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));  // row mirrored
+  const unsigned r0 = __builtin_amdgcn_readlane((int)v, 0), r1 = __builtin_amdgcn_readlane((int)v, 16),
+                 r2 = __builtin_amdgcn_readlane((int)v, 32), r3 = __builtin_amdgcn_readlane((int)v, 48);
+  const unsigned a = r0 > r1 ? r0 : r1, b = r2 > r3 ? r2 : r3;
+  return a > b ? a : b;
+}
+
+__global__ void __launch_bounds__(512) k_kron(NetDev net, double2* __restrict__ Yred, int* status) {
   const int nb = net.n_bus, ng = net.n_gen, W = nb + ng;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  __shared__ double2 lds[kKronLdsComplex];
-  __shared__ double s_val[4];
-  __shared__ int s_idx[4];
-  __shared__ int s_bad;
-  double2* A = ((int64_t)nb * W <= kKronLdsComplex) ? lds : gwork;
-  if (tid == 0) s_bad = 0;
-  // assembly: thread b owns row b
-  for (int b = tid; b < nb; b += nt) {
-    double2* row = A + (int64_t)b * W;
-    for (int c = 0; c < W; ++c) row[c] = make_double2(0.0, 0.0);
-    for (int k = 0; k < net.n_branch; ++k) {
-      const int f = net.from[k], t = net.to[k];
-      if (f != b && t != b) continue;
-      const double2 y = cdiv(make_double2(1.0, 0.0), make_double2(net.r[k], net.x[k]));
-      const double2 sh = make_double2(0.0, net.b ? 0.5 * net.b[k] : 0.0);
-      row[b] = cadd(row[b], cadd(y, sh));
-      const int o = (f == b) ? t : f;
-      row[o] = csub(row[o], y);
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+  __shared__ double2 A[kKronLdsComplex];
+  __shared__ int s_from[kKronStage], s_to[kKronStage];
+  __shared__ double2 s_y[kKronStage];
+  __shared__ double s_sh[kKronStage];
+  for (int q = tid; q < nb * W; q += nt) A[q] = make_double2(0.0, 0.0);
+  // assembly: thread b owns row b; the branches' data is staged by all
+  for (int k0 = 0; k0 < net.n_branch; k0 += kKronStage) {
+    const int m = net.n_branch - k0 < kKronStage ? net.n_branch - k0 : kKronStage;
+    __syncthreads();
+    for (int k = tid; k < m; k += nt) {
+      s_from[k] = net.from[k0 + k];
+      s_to[k] = net.to[k0 + k];
+      s_y[k] = cdiv(make_double2(1.0, 0.0), make_double2(net.r[k0 + k], net.x[k0 + k]));
+      s_sh[k] = net.b ? 0.5 * net.b[k0 + k] : 0.0;
     }
+    __syncthreads();
+    for (int b = tid; b < nb; b += nt) {
+      double2* row = A + b * W;
+#pragma unroll 4
+      for (int k = 0; k < m; ++k) {
+        const int f = s_from[k], t = s_to[k];
+        if (f != b && t != b) continue;
+        row[b] = cadd(row[b], cadd(s_y[k], make_double2(0.0, s_sh[k])));
+        const int o = (f == b) ? t : f;
+        row[o] = csub(row[o], s_y[k]);
+      }
+    }
+  }
+  __syncthreads();
+  for (int g = tid; g < ng && g < kKronStage; g += nt) s_from[g] = net.gen_bus[g];
+  __syncthreads();
+  for (int b = tid; b < nb; b += nt) {
+    double2* row = A + b * W;
     row[b] = cadd(row[b], make_double2(net.lg ? net.lg[b] : 0.0, net.lb ? net.lb[b] : 0.0));
-    for (int g = 0; g < ng; ++g) {
-      if (net.gen_bus[g] != b) continue;
+    for (int g = 0; g < ng; ++g) {  // machines in index order
+      const int gb = g < kKronStage ? s_from[g] : net.gen_bus[g];
+      if (gb != b) continue;
       const double2 yg = make_double2(0.0, -1.0 / net.xdp[g]);  // 1/(j X'd)
       row[b] = cadd(row[b], yg);
       row[nb + g] = csub(row[nb + g], yg);  // Y_BA = -yg
     }
   }
   __syncthreads();
+  // n_bus (n_bus + n_gen) <= 4096 means at most 63 buses: a lane per row
+  bool used = lane >= nb;    // row `lane` has been a pivot row (each wave's own copy)
+  __shared__ int s_prow[64];  // pivot row and inverse pivot of column k
+  __shared__ double2 s_pinv[64];
   for (int k = 0; k < nb; ++k) {
-    double best = -1.0;
-    int bi = nb;
-    for (int r = k + tid; r < nb; r += nt) {
-      const double v = cabs2(A[(int64_t)r * W + k]);
-      if (v > best || (v == best && r < bi)) { best = v; bi = r; }
+    unsigned key = 0;
+    if (!used) {
+      const double2 v = A[lane * W + k];
+      const float m = (float)fmax(fabs(v.x), fabs(v.y));
+      if (m > 0.0f) key = (__float_as_uint(m) & ~63u) | (unsigned)(63 - lane);
     }
-    kron_pivot_reduce(best, bi);
-    if ((tid & 63) == 0) {
-      s_val[tid >> 6] = best;
-      s_idx[tid >> 6] = bi;
-    }
-    __syncthreads();
-    double pv = s_val[0];
-    int piv = s_idx[0];
-    for (int w = 1; w < nt / 64; ++w)
-      if (s_val[w] > pv || (s_val[w] == pv && s_idx[w] < piv)) { pv = s_val[w]; piv = s_idx[w]; }
-    if (!(pv > 0.0)) {
+    key = wave_max_u32(key);
+    if (key == 0) {  // uniform: every wave saw the same column
       if (tid == 0) *status = -1;
-      return;  // uniform: every thread saw the same pv
+      return;
     }
-    if (piv != k) {
-      for (int c = k + tid; c < W; c += nt) {
-        const double2 t = A[(int64_t)k * W + c];
-        A[(int64_t)k * W + c] = A[(int64_t)piv * W + c];
-        A[(int64_t)piv * W + c] = t;
+    const int p = 63 - (int)(key & 63u);
+    used |= p == lane;
+    const double2 inv = cinv(A[p * W + k]);
+    if (tid == 0) {
+      s_prow[k] = p;
+      s_pinv[k] = inv;
+    }
+    // a thread takes a column and every 16th row (at most four)
+    for (int c = k + 1 + tid % 32; c < W; c += 32) {
+      const double2 pc = cmul(A[p * W + c], inv);
+      double fr[4], fi[4], vr[4], vi[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = tid / 32 + 16 * u, rr = r < nb ? r : p;
+        const double2 f = A[rr * W + k], v = A[rr * W + c];
+        fr[u] = f.x; fi[u] = f.y; vr[u] = v.x; vi[u] = v.y;
       }
-    }
-    __syncthreads();
-    const double2 akk = A[(int64_t)k * W + k];
-    const int rows = nb - k - 1, cols = W - k - 1;
-    for (int64_t q = tid; q < (int64_t)rows * cols; q += nt) {
-      const int r = k + 1 + (int)(q / cols);
-      const int c = k + 1 + (int)(q % cols);
-      const double2 f = cdiv(A[(int64_t)r * W + k], akk);
-      A[(int64_t)r * W + c] = csub(A[(int64_t)r * W + c], cmul(f, A[(int64_t)k * W + c]));
-    }
-    __syncthreads();
-  }
-  // back substitution on the n_gen right-hand columns
-  for (int k = nb - 1; k >= 0; --k) {
-    for (int g = tid; g < ng; g += nt) {
-      double2 acc = A[(int64_t)k * W + nb + g];
-      for (int j = k + 1; j < nb; ++j) acc = csub(acc, cmul(A[(int64_t)k * W + j], A[(int64_t)j * W + nb + g]));
-      A[(int64_t)k * W + nb + g] = cdiv(acc, A[(int64_t)k * W + k]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = tid / 32 + 16 * u;
+        if (r < nb && r != p)
+          A[r * W + c] = make_double2(vr[u] - (fr[u] * pc.x - fi[u] * pc.y), vi[u] - (fr[u] * pc.y + fi[u] * pc.x));
+      }
     }
     __syncthreads();
   }
   for (int q = tid; q < ng * ng; q += nt) {
-    const int i = q / ng, k = q % ng;
+    const int i = q / ng, g = q % ng, b = net.gen_bus[i];
     const double2 yg = make_double2(0.0, -1.0 / net.xdp[i]);
-    double2 v = (i == k) ? yg : make_double2(0.0, 0.0);
-    v = cadd(v, cmul(yg, A[(int64_t)net.gen_bus[i] * W + nb + k]));  // -(Y_AB X), Y_AB = -yg
+    double2 v = (i == g) ? yg : make_double2(0.0, 0.0);
+    const double2 x = cmul(A[s_prow[b] * W + nb + g], s_pinv[b]);
+    v = cadd(v, cmul(yg, x));  // -(Y_AB X), Y_AB = -yg
     Yred[q] = v;
   }
-  if (tid == 0) *status = s_bad;
+  if (tid == 0) *status = 0;
 }
 
 // ---------------------------------------------------------------------------
 // Large networks (the augmented system does not fit LDS): Kron's node
 // elimination on the full admittance matrix of the buses and the generator
-// internal nodes (W = n_bus + n_gen, buses first), one launch per eliminated
-// bus k:  Y_ij -= Y_ik Y_kj / Y_kk  for all remaining i, j.  After the last bus
-// the generator block is Y_red.  The buses are eliminated in index order
-// without pivoting: the bus block of a network admittance matrix whose series
-// branches share one R/X ratio and whose shunts are loads and transient
-// reactances is diagonally dominant.  A zero pivot sets the status.
+// internal nodes (W = n_bus + n_gen, buses first), kKronBlk buses at a time:
+// with D the block's diagonal part, Y_ij -= Y_ik D^-1 Y_kj for all remaining i, j.
+// After the last bus the generator block is Y_red.  The buses are eliminated in
+// index order without pivoting: the bus block of a network admittance matrix
+// whose series branches share one R/X ratio and whose shunts are loads and
+// transient reactances is diagonally dominant.  A zero pivot sets the status.
+//
+// Bound by the chain of blocks: one launch per block, in which every
+// workgroup forms D^-1 Y_kj of its 64 columns (again in each tile: cheaper than
+// another launch) and updates a tile of 32 x 64, and the workgroup of the next
+// block's diagonal part inverts it before it ends.  780 buses and 200
+// machines: 3.9 ms with a launch per bus (780 launches of 4.6 us).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_kron_assemble(NetDev net, double2* __restrict__ A,
-                                                       int* status) {
+constexpr int kKronBlk = 32;   // buses per elimination block = rows of a tile
+constexpr int kKronCols = 64;  // columns of a tile
+
+// One wave per row: the lanes scan 64 branches (machines) at once, the first
+// lane adds the matching ones in index order.
+__global__ void __launch_bounds__(64) k_kron_assemble(NetDev net, double2* __restrict__ A,
+                                                      int* status) {
   const int nb = net.n_bus, ng = net.n_gen, W = nb + ng;
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r == 0) *status = 0;  // the elimination steps only ever set -1
-  if (r >= W) return;
-  double2* row = A + (int64_t)r * W;  // zeroed before the launch
+  const int r = blockIdx.x, lane = threadIdx.x;
+  if (r == 0 && lane == 0) *status = 0;  // the elimination steps only ever set -1
+  double2* row = A + (int64_t)r * W;      // zeroed before the launch
   if (r >= nb) {
-    const int g = r - nb;
-    const double2 yg = make_double2(0.0, -1.0 / net.xdp[g]);  // 1/(j X'd)
-    row[r] = yg;
-    row[net.gen_bus[g]] = make_double2(-yg.x, -yg.y);
+    if (lane == 0) {
+      const int g = r - nb;
+      const double2 yg = make_double2(0.0, -1.0 / net.xdp[g]);  // 1/(j X'd)
+      row[r] = yg;
+      row[net.gen_bus[g]] = make_double2(-yg.x, -yg.y);
+    }
     return;
   }
-  for (int k = 0; k < net.n_branch; ++k) {
-    const int f = net.from[k], t = net.to[k];
-    if (f != r && t != r) continue;
-    const double2 y = cdiv(make_double2(1.0, 0.0), make_double2(net.r[k], net.x[k]));
-    const double2 sh = make_double2(0.0, net.b ? 0.5 * net.b[k] : 0.0);
-    row[r] = cadd(row[r], cadd(y, sh));
-    const int o = (f == r) ? t : f;
-    row[o] = csub(row[o], y);
+  double2 diag = make_double2(0.0, 0.0);
+  for (int k0 = 0; k0 < net.n_branch; k0 += 64) {
+    const int k = k0 + lane;
+    const bool hit = k < net.n_branch && (net.from[k] == r || net.to[k] == r);
+    unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    while (m) {
+      const int kk = k0 + __builtin_ctzll(m);
+      m &= m - 1;
+      if (lane != 0) continue;
+      const int f = net.from[kk], t = net.to[kk];
+      const double2 y = cdiv(make_double2(1.0, 0.0), make_double2(net.r[kk], net.x[kk]));
+      diag = cadd(diag, cadd(y, make_double2(0.0, net.b ? 0.5 * net.b[kk] : 0.0)));
+      const int o = (f == r) ? t : f;
+      row[o] = csub(row[o], y);
+    }
   }
-  row[r] = cadd(row[r], make_double2(net.lg ? net.lg[r] : 0.0, net.lb ? net.lb[r] : 0.0));
-  for (int g = 0; g < ng; ++g) {
-    if (net.gen_bus[g] != r) continue;
-    const double2 yg = make_double2(0.0, -1.0 / net.xdp[g]);
-    row[r] = cadd(row[r], yg);
-    row[nb + g] = csub(row[nb + g], yg);
+  diag = cadd(diag, make_double2(net.lg ? net.lg[r] : 0.0, net.lb ? net.lb[r] : 0.0));
+  for (int g0 = 0; g0 < ng; g0 += 64) {
+    const int g = g0 + lane;
+    unsigned long long m = __builtin_amdgcn_ballot_w64(g < ng && net.gen_bus[g] == r);
+    while (m) {
+      const int gg = g0 + __builtin_ctzll(m);
+      m &= m - 1;
+      if (lane != 0) continue;
+      const double2 yg = make_double2(0.0, -1.0 / net.xdp[gg]);
+      diag = cadd(diag, yg);
+      row[nb + gg] = csub(row[nb + gg], yg);
+    }
+  }
+  if (lane == 0) row[r] = diag;
+}
+
+// Inverse of a kKronBlk x kKronBlk block by Gauss-Jordan without pivoting, 256
+// threads: thread t holds the entries (t / 8, t % 8 + 8 u), u = 0..3; the pivot row
+// and column of the next step pass through LDS (two buffers, one barrier per
+// step).  Entries past the block's kb rows are the identity's.
+struct KronInvLds {
+  double2 row[2][kKronBlk], col[2][kKronBlk];
+};
+__device__ __forceinline__ void kron_invert(double (&vr)[4], double (&vi)[4], int kb, KronInvLds& s,
+                                            int* status) {
+  const int i = threadIdx.x / 8, jb = threadIdx.x % 8;
+  auto publish = [&](int k) {
+    if (i == k) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s.row[k & 1][jb + 8 * u] = make_double2(vr[u], vi[u]);
+    }
+    if (jb == k % 8) {
+      const int h = k / 8;
+      const double r = h == 0 ? vr[0] : h == 1 ? vr[1] : h == 2 ? vr[2] : vr[3];
+      const double m = h == 0 ? vi[0] : h == 1 ? vi[1] : h == 2 ? vi[2] : vi[3];
+      s.col[k & 1][i] = make_double2(r, m);
+    }
+  };
+  publish(0);
+  __syncthreads();
+  for (int k = 0; k < kb; ++k) {
+    const double2 piv = s.row[k & 1][k], cik = s.col[k & 1][i];
+    if (!(piv.x != 0.0 || piv.y != 0.0) && threadIdx.x == 0) *status = -1;
+    const double2 inv = cinv(piv);
+    const double2 nc = cmul(make_double2(-cik.x, -cik.y), inv);  // -a_ik / a_kk
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = jb + 8 * u;
+      const double2 akj = s.row[k & 1][j];
+      // a_ij - a_ik a_kj / a_kk; the pivot row is scaled, column k holds the inverse's
+      const double2 f = i == k ? inv : nc;
+      const double2 p = cmul(f, akj);
+      const double br = i == k ? 0.0 : vr[u], bi = i == k ? 0.0 : vi[u];
+      vr[u] = j == k ? f.x : br + p.x;
+      vi[u] = j == k ? f.y : bi + p.y;
+    }
+    if (k + 1 < kb) publish(k + 1);
+    __syncthreads();
   }
 }
 
-// One elimination step: block (64, 4) covers 64 columns; row k scaled by
-// 1/Y_kk is formed once per block in LDS.
-__global__ void __launch_bounds__(256) k_kron_elim(double2* __restrict__ A, int W, int k,
-                                                   int* status) {
-  __shared__ double2 sk[64];
-  const int tx = threadIdx.x, ty = threadIdx.y;
-  const int j = k + 1 + blockIdx.x * 64 + tx;
-  const double2 akk = A[(int64_t)k * W + k];
-  if (!(akk.x != 0.0 || akk.y != 0.0)) {  // uniform
-    if (blockIdx.x == 0 && blockIdx.y == 0 && tx == 0 && ty == 0) *status = -1;
-    return;
+// The inverse of the first block's diagonal part (kb = its buses).
+__global__ void __launch_bounds__(256) k_kron_first(const double2* __restrict__ A, int W, int kb,
+                                                    double2* __restrict__ dinv, int* status) {
+  __shared__ KronInvLds s;
+  const int i = threadIdx.x / 8, jb = threadIdx.x % 8;
+  double vr[4], vi[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = jb + 8 * u;
+    const bool on = i < kb && j < kb;
+    vr[u] = on ? A[(int64_t)i * W + j].x : (i == j ? 1.0 : 0.0);
+    vi[u] = on ? A[(int64_t)i * W + j].y : 0.0;
   }
-  if (ty == 0) sk[tx] = j < W ? cdiv(A[(int64_t)k * W + j], akk) : make_double2(0.0, 0.0);
+  kron_invert(vr, vi, kb, s, status);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) dinv[i * kKronBlk + jb + 8 * u] = make_double2(vr[u], vi[u]);
+}
+
+// Elimination of the kb buses k0..k0 + kb - 1: tile (blockIdx.y, blockIdx.x) of
+// the trailing matrix (from row and column k1 = k0 + kb on).  dinv: the block's
+// inverse; dnext: receives the next block's (nbn buses, 0 after the last).
+__global__ void __launch_bounds__(256) k_kron_block(double2* __restrict__ A, int W, int k0, int kb,
+                                                    int nbn, const double2* __restrict__ dinv,
+                                                    double2* __restrict__ dnext, int* status) {
+  __shared__ double2 s_d[kKronBlk][kKronBlk];   // D^-1
+  __shared__ double2 s_t[kKronBlk][kKronCols];  // Y_kj of the tile's columns, then D^-1 Y_kj
+  __shared__ double2 s_l[kKronBlk][kKronBlk];   // Y_ik of the tile's rows
+  __shared__ KronInvLds s_inv;
+  const int tid = threadIdx.x, k1 = k0 + kb;
+  const int c0 = k1 + blockIdx.x * kKronCols, r0 = k1 + blockIdx.y * kKronBlk;
+  const double2 zero = make_double2(0.0, 0.0);
+  for (int q = tid; q < kKronBlk * kKronBlk; q += 256) {
+    const int i = q / kKronBlk, j = q % kKronBlk;
+    s_d[i][j] = dinv[q];
+    s_l[i][j] = (r0 + i < W && j < kb) ? A[(int64_t)(r0 + i) * W + k0 + j] : zero;
+  }
+  for (int q = tid; q < kKronBlk * kKronCols; q += 256) {
+    const int i = q / kKronCols, j = q % kKronCols;
+    s_t[i][j] = (i < kb && c0 + j < W) ? A[(int64_t)(k0 + i) * W + c0 + j] : zero;
+  }
   __syncthreads();
-  if (j >= W) return;
-  const double2 s = sk[tx];
-  for (int i = k + 1 + blockIdx.y * 4 + ty; i < W; i += gridDim.y * 4) {
-    double2* a = A + (int64_t)i * W;
-    a[j] = csub(a[j], cmul(a[k], s));
+  // thread: columns tx and tx + 32, rows 4 ty .. 4 ty + 3 of the tile
+  const int tx = tid % 32, ty = tid / 32;
+  double cr[4][2], ci[4][2];
+  auto product = [&](const double2 (*L)[kKronBlk]) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a) cr[a][0] = cr[a][1] = ci[a][0] = ci[a][1] = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < kKronBlk; ++k) {
+      const double2 x0 = s_t[k][tx], x1 = s_t[k][tx + 32];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const double2 l = L[4 * ty + a][k];
+        cr[a][0] = fma(l.x, x0.x, cr[a][0]);
+        cr[a][0] = fma(-l.y, x0.y, cr[a][0]);
+        ci[a][0] = fma(l.x, x0.y, ci[a][0]);
+        ci[a][0] = fma(l.y, x0.x, ci[a][0]);
+        cr[a][1] = fma(l.x, x1.x, cr[a][1]);
+        cr[a][1] = fma(-l.y, x1.y, cr[a][1]);
+        ci[a][1] = fma(l.x, x1.y, ci[a][1]);
+        ci[a][1] = fma(l.y, x1.x, ci[a][1]);
+      }
+    }
+  };
+  product(s_d);
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    s_t[4 * ty + a][tx] = make_double2(cr[a][0], ci[a][0]);
+    s_t[4 * ty + a][tx + 32] = make_double2(cr[a][1], ci[a][1]);
   }
+  __syncthreads();
+  product(s_l);
+  const bool inverts = nbn > 0 && blockIdx.x == 0 && blockIdx.y == 0;  // uniform
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = r0 + 4 * ty + a, c = c0 + tx + 32 * h;
+      double2 v = zero;
+      if (r < W && c < W) {
+        v = csub(A[(int64_t)r * W + c], make_double2(cr[a][h], ci[a][h]));
+        A[(int64_t)r * W + c] = v;
+      }
+      if (inverts && h == 0) s_d[4 * ty + a][tx] = v;  // read before the last barrier only
+    }
+  if (!inverts) return;
+  __syncthreads();
+  const int i = tid / 8, jb = tid % 8;
+  double vr[4], vi[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = jb + 8 * u;
+    const bool on = i < nbn && j < nbn;
+    vr[u] = on ? s_d[i][j].x : (i == j ? 1.0 : 0.0);
+    vi[u] = on ? s_d[i][j].y : 0.0;
+  }
+  kron_invert(vr, vi, nbn, s_inv, status);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) dnext[i * kKronBlk + jb + 8 * u] = make_double2(vr[u], vi[u]);
 }
 
 __global__ void __launch_bounds__(256) k_kron_extract(const double2* __restrict__ A, int nb, int ng,
@@ -210,26 +389,30 @@ __global__ void __launch_bounds__(256) k_kron_extract(const double2* __restrict_
   Yred[q] = A[(int64_t)(nb + i) * W + nb + k];
 }
 
+// The work matrix, then two inverses of diagonal blocks (in turn).
 size_t kron_work_bytes(int n_bus, int n_gen) {
   const size_t W = (size_t)n_bus + n_gen;
-  return W * W * sizeof(double2);
+  return (W * W + 2 * kKronBlk * kKronBlk) * sizeof(double2);
 }
 
 hipError_t launch_kron(const NetDev& net, double2* work, double2* Yred, int* status,
                        hipStream_t st) {
   const int nb = net.n_bus, ng = net.n_gen, W = nb + ng;
   if ((int64_t)nb * W <= kKronLdsComplex) {
-    hipLaunchKernelGGL(k_kron, dim3(1), dim3(256), 0, st, net, work, Yred, status);
+    hipLaunchKernelGGL(k_kron, dim3(1), dim3(512), 0, st, net, Yred, status);
     return hipGetLastError();
   }
   hipError_t e = launch_fill_i64((int64_t*)work, 0, (int64_t)W * W * 2, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_kron_assemble, dim3((unsigned)((W + 255) / 256)), dim3(256), 0, st, net, work,
-                     status);
-  for (int k = 0; k < nb; ++k) {
-    const int m = W - k - 1;
-    const unsigned gx = (unsigned)((m + 63) / 64), gy = (unsigned)std::min(64, (m + 3) / 4);
-    hipLaunchKernelGGL(k_kron_elim, dim3(gx, gy), dim3(64, 4), 0, st, work, W, k, status);
+  double2* dinv[2] = {work + (int64_t)W * W, work + (int64_t)W * W + kKronBlk * kKronBlk};
+  hipLaunchKernelGGL(k_kron_assemble, dim3((unsigned)W), dim3(64), 0, st, net, work, status);
+  hipLaunchKernelGGL(k_kron_first, dim3(1), dim3(256), 0, st, work, W, std::min(kKronBlk, nb),
+                     dinv[0], status);
+  for (int k0 = 0, q = 0; k0 < nb; k0 += kKronBlk, q ^= 1) {
+    const int kb = std::min(kKronBlk, nb - k0), k1 = k0 + kb, m = W - k1;
+    const dim3 grid((unsigned)((m + kKronCols - 1) / kKronCols), (unsigned)((m + kKronBlk - 1) / kKronBlk));
+    hipLaunchKernelGGL(k_kron_block, grid, dim3(256), 0, st, work, W, k0, kb,
+                       std::min(kKronBlk, nb - k1), dinv[q], dinv[q ^ 1], status);
   }
   hipLaunchKernelGGL(k_kron_extract, dim3((unsigned)((ng * ng + 255) / 256)), dim3(256), 0, st,
                      work, nb, ng, Yred);
