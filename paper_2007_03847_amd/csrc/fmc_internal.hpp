@@ -38,6 +38,15 @@ struct CanonLayout {
 
 // Packed coefficients of one integrator variant (NG machines, PM processes,
 // padded with inert entries), in the variant's arithmetic type.
+// Plain form (one trajectory per lane): Y, I0, res, D, 1/(2H) as they are.
+// Rotated form (lanes per trajectory, teams): every machine's quantities in the
+// frame of its own EMF at the operating point and scaled by its 1/(2H), so that
+// with eps_k = e^{j d_k} - 1 the acceleration is
+//   res - D u + inj - Re(eps_i conj J_i) - Re(conj(1 + eps_i) sum_k Z_ik eps_k),
+//   Z_ik = conj(E~0_i) Y_ik E~0_k / 2H_i (in yre, yim),
+//   J_i = conj(E~0_i) I0_i / 2H_i (in i0r, i0i),
+// and res, D and the 0/1 injections carry the 1/(2H_i) too; formed in FP64 and
+// rounded once.  The machines then exchange (1 - cos d, sin d) themselves.
 struct PackLayout {
   int NG, PM;
   __host__ __device__ constexpr int yre() const { return 0; }
@@ -53,7 +62,10 @@ struct PackLayout {
   __host__ __device__ constexpr int theta() const { return inv2h() + NG; }
   __host__ __device__ constexpr int sigma() const { return theta() + PM; }
   __host__ __device__ constexpr int xi0() const { return sigma() + PM; }
-  __host__ __device__ constexpr int size() const { return xi0() + PM; }
+  // the machine each process belongs to (-1 past P); unlike binc it does not
+  // change with a network event, so it says which lane owns a process
+  __host__ __device__ constexpr int owner() const { return xi0() + PM; }
+  __host__ __device__ constexpr int size() const { return owner() + PM; }
 };
 
 // Arguments of one time chunk of the batched integrator.
@@ -184,8 +196,8 @@ hipError_t launch_setup_post(const double* pre, int n, int P, const double2* Yp,
                              hipStream_t st);
 
 template <typename R>
-hipError_t launch_pack(const double* canon, int n, int P, const int32_t* gen, int NG, int PM,
-                       R* coef, hipStream_t st);
+hipError_t launch_pack(const double* canon, int n, int P, const int32_t* gen,
+                       const int32_t* owner, bool rotated, int NG, int PM, R* coef, hipStream_t st);
 
 hipError_t launch_stats_merge(const double2* partial, int64_t n_groups, int group_size,
                               int64_t N, int64_t S, int V, int n, int ddof,

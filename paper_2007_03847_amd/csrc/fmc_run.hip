@@ -319,8 +319,8 @@ int run_single(Context* c, const fmc_system* sys, const fmc_disturbance* dist,
   void* coef = nullptr;
   const PackLayout PL{vi.NG, vi.PM};
   if ((rc = c->ensure("coef", (size_t)PL.size() * bw, &coef))) return rc;
-  HIPCHK(f64 ? launch_pack<double>(canon, n, P, gen_d, vi.NG, vi.PM, (double*)coef, c->stream)
-             : launch_pack<float>(canon, n, P, gen_d, vi.NG, vi.PM, (float*)coef, c->stream));
+  HIPCHK(f64 ? launch_pack<double>(canon, n, P, gen_d, gen_d, vi.L > 1, vi.NG, vi.PM, (double*)coef, c->stream)
+             : launch_pack<float>(canon, n, P, gen_d, gen_d, false, vi.NG, vi.PM, (float*)coef, c->stream));
 
   // A network event: the post-event admittance (given, or the network reduced
   // with the tripped machine's internal node cut off by an infinite X'd), the
@@ -367,8 +367,8 @@ int run_single(Context* c, const fmc_system* sys, const fmc_disturbance* dist,
     if ((rc = c->ensure("canon_post", (size_t)CL.size() * sizeof(double), &cp))) return rc;
     HIPCHK(launch_setup_post(canon, n, P, Yp_d, Yinf_d, sys->V_inf, g, (double*)cp, c->stream));
     if ((rc = c->ensure("coef_post", (size_t)PL.size() * bw, &coef_post))) return rc;
-    HIPCHK(f64 ? launch_pack<double>((const double*)cp, n, P, genp_d, vi.NG, vi.PM, (double*)coef_post, c->stream)
-               : launch_pack<float>((const double*)cp, n, P, genp_d, vi.NG, vi.PM, (float*)coef_post, c->stream));
+    HIPCHK(f64 ? launch_pack<double>((const double*)cp, n, P, genp_d, gen_d, vi.L > 1, vi.NG, vi.PM, (double*)coef_post, c->stream)
+               : launch_pack<float>((const double*)cp, n, P, genp_d, gen_d, false, vi.NG, vi.PM, (float*)coef_post, c->stream));
     n_ref_post = n - (g >= 0 ? 1 : 0);
   }
 

@@ -19,6 +19,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "fmc_internal.hpp"
 
 namespace fmc {
@@ -33,31 +35,24 @@ using cptr = const __attribute__((address_space(4))) R*;
 // by FMA (exact enough for |k| < 2^20, far beyond the angles met here), then
 // the Taylor polynomials of sin and cos in r^2 (terms through r^15 / r^16 in
 // FP64, r^9 / r^10 in FP32; truncation below half an ulp on |r| <= pi/4), and
-// the quadrant of k.  When every active lane of the wave has |x| < 0.78 (the
-// usual case: the argument is half an angle's deviation from the operating
-// point), k is 0 for all of them, the reduction leaves r = x exactly and the
-// quadrant step is the identity: sincos_many then skips both with one
-// wave-uniform branch, with the same bits as the full path.
+// the quadrant of k.
 __device__ __forceinline__ bool sincos_all_small(bool small) {
   return __builtin_amdgcn_ballot_w64(!small) == 0;
 }
 
-// a*b + c as the three-operand FMA: the coefficients below stay in registers
-// of their own, read but never overwritten (the two-operand form ties the
-// addend to the result and costs a copy of the coefficient per use)
+// a*b + c as the three-operand FMA with the coefficient c in a scalar register
+// pair: the coefficients take no vector registers and no copies (the
+// two-operand form ties the addend to the result and costs a copy of the
+// coefficient per use)
 __device__ __forceinline__ double fma3(double a, double b, double c) {
   double d;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
   return d;
 }
 
-// the polynomials on the reduced argument r; F3 selects the three-operand
-// FMA for the Horner steps (the same rounding as fma(), so the same bits):
-// worth it where the coefficients stay resident in vector registers, not
-// where register pressure would have them rematerialised at every use
-template <bool F3 = true>
+// the polynomials on the reduced argument r
 __device__ __forceinline__ void sincos_poly(double r, double& sr, double& cr) {
-  auto f = [](double a, double b, double c) { return F3 ? fma3(a, b, c) : fma(a, b, c); };
+  auto f = [](double a, double b, double c) { return fma(a, b, c); };
   const double r2 = r * r;
   double ps = -1.0 / 1307674368000.0;
   ps = f(ps, r2, 1.0 / 6227020800.0);
@@ -101,7 +96,7 @@ __device__ __forceinline__ void sincos_r_nb(double x, double& s, double& c) {
   double r = fma(-k, 0x1.921fb54442d18p+0, x);
   r = fma(-k, 0x1.1a62633145c07p-54, r);
   double sr, cr;
-  sincos_poly<false>(r, sr, cr);
+  sincos_poly(r, sr, cr);
   const int q = (int)k;
   const double a = (q & 1) ? cr : sr;
   const double b = (q & 1) ? sr : cr;
@@ -123,26 +118,7 @@ __device__ __forceinline__ void sincos_r_nb(float x, float& s, float& c) {
   c = ((q + 1) & 2) ? -b : b;
 }
 
-// sin and cos of a lane's N angles with one wave-uniform decision: the
-// small-angle form for all of them when every active lane's angles are below
-// 0.78 (the same bits as the full path), else the full path; in
-// both branches the N evaluations are straight-line code the compiler can
-// interleave.
-template <typename R, int N>
-__device__ __forceinline__ void sincos_many(const R (&x)[N], R (&s)[N], R (&c)[N]) {
-  bool small = true;
-#pragma unroll
-  for (int k = 0; k < N; ++k) small = small && fabs(x[k]) < R(0.78);
-  if (sincos_all_small(small)) [[likely]] {
-#pragma unroll
-    for (int k = 0; k < N; ++k) sincos_poly(x[k], s[k], c[k]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < N; ++k) sincos_r_nb(x[k], s[k], c[k]);
-  }
-}
-
-// sin d and 1 - cos d of a lane's N angle deviations d.  When every active
+// sin d and 1 - cos d of a lane's angle deviations d (of N machines in M stages).  When every active
 // lane's angles are below half a radian (the usual case for deviations from the
 // operating point), both come straight from their Taylor polynomials in d^2
 // (sin through d^13 and 1 - cos through d^14 in FP64, d^7 and d^8 in FP32: the
@@ -181,24 +157,37 @@ __device__ __forceinline__ void rotation_poly(float d, float& sd, float& omc) {
   pc = fmaf(pc, r2, 0.5f);
   omc = r2 * pc;
 }
+template <typename R, int M, int N>
+__device__ __forceinline__ void rotation_stages(const R (&d)[M][N], const bool (&live)[N],
+                                                R (&sd)[M][N], R (&omc)[M][N]) {
+  bool small = true;
+#pragma unroll
+  for (int h = 0; h < M; ++h)
+#pragma unroll
+    for (int k = 0; k < N; ++k) small = small && (!live[k] || fabs(d[h][k]) < R(0.5));
+  if (sincos_all_small(small)) [[likely]] {
+#pragma unroll
+    for (int h = 0; h < M; ++h)
+#pragma unroll
+      for (int k = 0; k < N; ++k) rotation_poly(d[h][k], sd[h][k], omc[h][k]);
+  } else {
+#pragma unroll
+    for (int h = 0; h < M; ++h)
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        R sh, ch;
+        sincos_r_nb(live[k] ? d[h][k] * R(0.5) : R(0), sh, ch);
+        sd[h][k] = R(2) * sh * ch;
+        omc[h][k] = R(2) * sh * sh;
+      }
+  }
+}
 template <typename R, int N>
 __device__ __forceinline__ void rotation_many(const R (&d)[N], const bool (&live)[N], R (&sd)[N],
                                               R (&omc)[N]) {
-  bool small = true;
-#pragma unroll
-  for (int k = 0; k < N; ++k) small = small && (!live[k] || fabs(d[k]) < R(0.5));
-  if (sincos_all_small(small)) [[likely]] {
-#pragma unroll
-    for (int k = 0; k < N; ++k) rotation_poly(d[k], sd[k], omc[k]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      R sh, ch;
-      sincos_r_nb(live[k] ? d[k] * R(0.5) : R(0), sh, ch);
-      sd[k] = R(2) * sh * ch;
-      omc[k] = R(2) * sh * sh;
-    }
-  }
+  using A = const R (*)[1][N];
+  using B = R (*)[1][N];
+  rotation_stages<R, 1, N>(*(A)&d, live, *(B)&sd, *(B)&omc);
 }
 
 // The FP64 common-angle offset in two state slots: the exact bits of the
@@ -219,6 +208,29 @@ __device__ __forceinline__ double load_offset(const float* st, int64_t i0, int64
 }
 __device__ __forceinline__ double load_offset(const double* st, int64_t i0, int64_t) {
   return st[i0];
+}
+
+// d xi/dt of eq. 9 for a general Ito process whose row q sits in registers; root
+// and poly (wave-uniform): some lane has a process with a square-root or a
+// polynomial diffusion, so that a wave pays only for the forms it has.
+template <typename R>
+__device__ __forceinline__ R sde_rate(const R (&q)[kSdeCols], R x, R w, bool root, bool poly) {
+  const R mu = q[SDE_M0] + x * (q[SDE_M1] + x * q[SDE_M2]);
+  R sg = R(0), ssp = R(0);  // sigma and sigma sigma'
+  if (poly) {
+    sg = q[SDE_C0] + x * (q[SDE_C1] + x * q[SDE_C2]);
+    ssp = sg * (q[SDE_C1] + R(2) * q[SDE_C2] * x);
+  }
+  if (root) {
+    const R d = x - q[SDE_R];
+    const R g = q[SDE_C0] + x * (q[SDE_C1] + x * q[SDE_C2]) + q[SDE_C3] * fabs(d);
+    const R sgn = d > R(0) ? R(1) : (d < R(0) ? R(-1) : R(0));
+    const R dg = q[SDE_C1] + R(2) * q[SDE_C2] * x + q[SDE_C3] * sgn;
+    const bool pos = g > R(0), mine = q[SDE_FORM] == R(2);
+    sg = mine ? (pos ? sqrt(g) : R(0)) : sg;
+    ssp = mine ? (pos ? R(0.5) * dg : R(0)) : ssp;
+  }
+  return mu - q[SDE_K] * ssp + sg * w;
 }
 
 // d xi/dt of eq. 9 for a general Ito process (one row of IntegArgs::sde) at
@@ -244,23 +256,45 @@ __device__ __forceinline__ R sde_rhs(Ptr q, R x, R w, R& inj) {
   return mu - q[SDE_K] * ssp + sg * w;
 }
 
+// The packed coefficients as a lane reads them.  From memory: the pointer is
+// derived again at every stage, so that the compiler streams the machine data
+// through scalar loads instead of keeping it live in (spilled) registers across
+// stages and steps.  In vector registers, for systems of one or two machines
+// (14 or 46 values): their kernels are bound by latency, and a scalar load's
+// would be on every stage.
+template <typename R>
+struct CoefMem {
+  const R* p;
+  __device__ __forceinline__ cptr<R> stage() const {
+    const R* q = p;
+    asm volatile("" : "+s"(q));
+    return (cptr<R>)q;
+  }
+};
+template <typename R, int N>
+struct CoefReg {
+  R r[N];
+  __device__ __forceinline__ explicit CoefReg(const R* p) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      r[i] = p[i];
+      asm volatile("" : "+v"(r[i]));
+    }
+  }
+  __device__ __forceinline__ const R* stage() const { return r; }
+};
+
 // Right-hand side of the swing equations + the disturbances in deviation
 // form: OU from the packed theta and sigma, or (GEN) the general processes of
 // sdeg.  GEN is a separate instantiation so that the OU kernels keep their
 // register allocation.
-template <typename R, int NG, int PM, bool GEN>
-__device__ __forceinline__ void swing_rhs(const R* cfg, const R* sdeg, const R wb,
+template <typename R, int NG, int PM, bool GEN, typename CF>
+__device__ __forceinline__ void swing_rhs(const CF& coef, const R* sdeg, const R wb,
                                           const R (&yd)[NG], const R (&yw)[NG],
                                           const R (&yx)[PM], const R (&wv)[PM], R (&kd)[NG],
                                           R (&kw)[NG], R (&kx)[PM]) {
   constexpr PackLayout L{NG, PM};
-  // Re-derive the pointer at every stage: the compiler then streams the
-  // machine data through scalar loads instead of keeping it live in (spilled)
-  // registers across stages and steps.
-  // (One or two machines fit the scalar registers: there the reload would put a
-  // scalar load's latency on every stage of a latency-bound kernel.)
-  if constexpr (NG > 2) asm volatile("" : "+s"(cfg));
-  const cptr<R> cf = (cptr<R>)cfg;
+  const auto cf = coef.stage();
   // general processes first: their injections feed the machines
   R xin[GEN ? PM : 1];
   if constexpr (GEN) {
@@ -269,12 +303,18 @@ __device__ __forceinline__ void swing_rhs(const R* cfg, const R* sdeg, const R w
     for (int p = 0; p < PM; ++p) kx[p] = sde_rhs<R>(sq + p * kSdeCols, yx[p], wv[p], xin[p]);
   }
   R dc[NG], ds[NG];
-  R sdv[NG], omcv[NG];
   if constexpr (NG <= 2) {
+    R sd[NG], omc[NG];
     bool live[NG];
 #pragma unroll
     for (int k = 0; k < NG; ++k) live[k] = cf[L.c0() + k] != R(0) || cf[L.s0() + k] != R(0);
-    rotation_many(yd, live, sdv, omcv);
+    rotation_many(yd, live, sd, omc);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+      const R c0 = cf[L.c0() + k], s0 = cf[L.s0() + k];
+      dc[k] = -(c0 * omc[k] + s0 * sd[k]);
+      ds[k] = c0 * sd[k] - s0 * omc[k];
+    }
   } else {
     // the branch-free form: a lane's machines are interleaved by the compiler
     // around the scalar loads of their data
@@ -282,15 +322,12 @@ __device__ __forceinline__ void swing_rhs(const R* cfg, const R* sdeg, const R w
     for (int k = 0; k < NG; ++k) {
       R sh, ch;
       sincos_r_nb(yd[k] * R(0.5), sh, ch);
-      sdv[k] = R(2) * sh * ch;   // sin d
-      omcv[k] = R(2) * sh * sh;  // 1 - cos d
+      const R c0 = cf[L.c0() + k], s0 = cf[L.s0() + k];
+      const R sd = R(2) * sh * ch;   // sin d
+      const R omc = R(2) * sh * sh;  // 1 - cos d
+      dc[k] = -(c0 * omc + s0 * sd);
+      ds[k] = c0 * sd - s0 * omc;
     }
-  }
-#pragma unroll
-  for (int k = 0; k < NG; ++k) {
-    const R c0 = cf[L.c0() + k], s0 = cf[L.s0() + k];
-    dc[k] = -(c0 * omcv[k] + s0 * sdv[k]);
-    ds[k] = c0 * sdv[k] - s0 * omcv[k];
   }
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
@@ -401,6 +438,7 @@ __device__ __forceinline__ void reduce_steps(const IntegArgs<R>& a, double (*til
     const double k = row[0];  // the mean as an offset from the first sample: exact for equal ones
     double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
     int j = 0;
+#pragma unroll 4
     for (; j + 3 < cnt; j += 4) {
       q0 += row[j] - k;
       q1 += row[j + 1] - k;
@@ -410,6 +448,7 @@ __device__ __forceinline__ void reduce_steps(const IntegArgs<R>& a, double (*til
     for (; j < cnt; ++j) q0 += row[j] - k;
     const double mu = k + ((q0 + q1) + (q2 + q3)) / (double)cnt;
     q0 = q1 = q2 = q3 = 0.0;
+#pragma unroll 4
     for (j = 0; j + 3 < cnt; j += 4) {
       const double d0 = row[j] - mu, d1 = row[j + 1] - mu, d2 = row[j + 2] - mu, d3 = row[j + 3] - mu;
       q0 = fma(d0, d0, q0);
@@ -442,6 +481,8 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
   const int P = a.P;
   const R* __restrict__ cf = a.coef;
   const R* __restrict__ w = a.w;
+  using Coef = std::conditional_t<(NG <= 2), CoefReg<R, L.size()>, CoefMem<R>>;
+  const Coef coef{cf};
   const int slot = (valid && a.traj_slot) ? a.traj_slot[ns] : -1;
 
   R yd[NG], yw[NG], yx[PM];
@@ -500,7 +541,7 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
     R ad[NG], aw[NG], ax[PM];
     R td[NG], tw[NG], tx[PM];
     // stage 1
-    swing_rhs<R, NG, PM, GEN>(cf, GEN ? a.sde : nullptr, wb, yd, yw, yx, w0, kd, kw, kx);
+    swing_rhs<R, NG, PM, GEN>(coef, GEN ? a.sde : nullptr, wb, yd, yw, yx, w0, kd, kw, kx);
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       ad[i] = kd[i]; aw[i] = kw[i];
@@ -509,7 +550,7 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
 #pragma unroll
     for (int p = 0; p < PM; ++p) { ax[p] = kx[p]; tx[p] = yx[p] + h2 * kx[p]; }
     // stage 2
-    swing_rhs<R, NG, PM, GEN>(cf, GEN ? a.sde : nullptr, wb, td, tw, tx, w1, kd, kw, kx);
+    swing_rhs<R, NG, PM, GEN>(coef, GEN ? a.sde : nullptr, wb, td, tw, tx, w1, kd, kw, kx);
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       ad[i] += R(2) * kd[i]; aw[i] += R(2) * kw[i];
@@ -518,7 +559,7 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
 #pragma unroll
     for (int p = 0; p < PM; ++p) { ax[p] += R(2) * kx[p]; tx[p] = yx[p] + h2 * kx[p]; }
     // stage 3
-    swing_rhs<R, NG, PM, GEN>(cf, GEN ? a.sde : nullptr, wb, td, tw, tx, w1, kd, kw, kx);
+    swing_rhs<R, NG, PM, GEN>(coef, GEN ? a.sde : nullptr, wb, td, tw, tx, w1, kd, kw, kx);
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       ad[i] += R(2) * kd[i]; aw[i] += R(2) * kw[i];
@@ -527,7 +568,7 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
 #pragma unroll
     for (int p = 0; p < PM; ++p) { ax[p] += R(2) * kx[p]; tx[p] = yx[p] + dt * kx[p]; }
     // stage 4
-    swing_rhs<R, NG, PM, GEN>(cf, GEN ? a.sde : nullptr, wb, td, tw, tx, w2, kd, kw, kx);
+    swing_rhs<R, NG, PM, GEN>(coef, GEN ? a.sde : nullptr, wb, td, tw, tx, w2, kd, kw, kx);
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       yd[i] += dt6 * (ad[i] + kd[i]);
@@ -555,7 +596,8 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
       nbuf = 0;
     }
     if (nbuf == 0) s_first = s + 1;
-    emit_step<R, NG, PM, VM>(a, tile, nbuf++, lane, s + 1, slot, coff, yd, yw, yx);
+    emit_step<R, NG, PM, VM>(a, tile, D == 1 ? 0 : nbuf, lane, s + 1, slot, coff, yd, yw, yx);
+    ++nbuf;
     if (a.rrf_w) {
       const double u = rrf_u_lane<R, NG, PM>(a, coff, yd, yw, yx);
       racc += (s + 1 == a.S ? 0.5 : 1.0) * u * u;
@@ -610,9 +652,43 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// *p, the same for all lanes, into scalar registers
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  struct Words {
+    int w[sizeof(T) / 4];
+  };
+  const Words* s = reinterpret_cast<const Words*>(p);
+  Words v;
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) v.w[i] = __builtin_amdgcn_readfirstlane(s->w[i]);
+  return __builtin_bit_cast(T, v);
+}
+
 template <typename R> struct vec2;
 template <> struct vec2<double> { using type = double2; };
 template <> struct vec2<float> { using type = float2; };
+
+// Form of the network product of the group kernels.  FP64: rotated
+// (PackLayout), which saves the turn by E0 and the products with it.  FP32:
+// plain.  There the rounding of the coefficients is systematic over all samples,
+// and rounding Z_ik / 2H_i and Z_ki / 2H_k on their own breaks the balance
+// of the two machines' exchange that Y_ik = Y_ki keeps: the common angle drifts
+// (45 machines, 19 s: mean off by 1.9e-6 rotated, 5e-7 plain; 6 machines: variance
+// by 5.7e-6 and 3.6e-6).
+template <typename R>
+__host__ __device__ constexpr bool rotated_form() {
+  return sizeof(R) == 8;
+}
+
+// (1 - cos d, sin d) turned by E0: dE = E0 (e^{j d} - 1) = -omc + j sd
+template <typename R>
+__device__ __forceinline__ void turn(R e0r, R e0i, R& omc, R& sd) {
+  const R o = fma(e0i, sd, e0r * omc);
+  sd = fma(e0r, sd, -e0i * omc);
+  omc = o;
+}
 
 // Sizes of one group variant and the LDS it needs: the statistics tile (the
 // values of up to D consecutive output steps, reduced together with two
@@ -630,8 +706,10 @@ struct GroupShape {
   static constexpr int TB = TW * WPB;          // trajectories per workgroup
   static constexpr int VM = 2 * NG + PM;
   static constexpr size_t tile_bytes = (size_t)D * VM * (TB + 1) * sizeof(double);
-  static constexpr size_t xch_bytes = (size_t)(TB + 1) * XW * sizeof(R2);
-  static constexpr size_t lds_bytes = tile_bytes + xch_bytes + (TB + 1) * sizeof(int);
+  static constexpr size_t xch_bytes = (size_t)2 * (TB + 1) * XW * sizeof(R2);  // two stages
+  static constexpr size_t rrf_off = tile_bytes + xch_bytes;  // weights and offsets [2][VM]
+  static constexpr size_t bad_off = rrf_off + (size_t)2 * VM * sizeof(double);
+  static constexpr size_t lds_bytes = bad_off + (TB + 1) * sizeof(int);
 };
 
 // Mean and sum of squared deviations of row[0, cnt) (cnt >= 1) in one pass
@@ -646,7 +724,7 @@ __device__ __forceinline__ void row_stats(const double* row, int cnt, double& mu
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
   double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
   int j = 0;
-#pragma unroll 1
+#pragma unroll 2
   for (; j + 3 < cnt; j += 4) {
     const double d0 = row[j] - k, d1 = row[j + 1] - k, d2 = row[j + 2] - k, d3 = row[j + 3] - k;
     s0 += d0; s1 += d1; s2 += d2; s3 += d3;
@@ -672,26 +750,34 @@ struct GroupStats {
 
 // One workgroup integrates trajectories tile*TB .. tile*TB + TB - 1 of a
 // scenario over the steps [s_begin, s_end) of a.  Lane g of a trajectory owns
-// machines g*G .. g*G+G-1 (rows of Y in registers) and processes g, g+L, ...;
-// per stage the lanes exchange the rotated EMF deviations of their machines
-// and the stage values of their processes through LDS.  keep_state stores the
-// state for a following chunk.  GEN: the processes are the general Ito
-// processes of a.sde; the owner lane of a process evaluates its drift and
-// diffusion and publishes the power it injects, gain (xi - ref), in the
-// process's exchange slot (where the OU form publishes xi itself).
+// machines g*G .. g*G+G-1 (rows of Y in registers); per stage the lanes exchange
+// the rotated EMF deviations of their machines through LDS.  keep_state stores
+// the state for a following chunk.  GEN: the processes are the general Ito
+// processes of a.sde.
+//
+// Processes: with one machine per lane and at most one process at a machine, the
+// lane of the machine owns its process and adds the injection itself (no exchange:
+// the wave reads ten pairs per stage instead of fourteen values for ten machines
+// and four process slots, and drops the product with the 0/1 injection matrix);
+// else lane g owns processes g, g + L, ... and publishes the injected powers in
+// the exchange row.  Which of the two holds is the same for all waves and chunks:
+// it comes from the packed owner machines, which an event leaves alone.
 template <typename R, int NG, int PM, int L, int WPB, int D, bool GEN = false>
 __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
-                                          unsigned char* lds, GroupStats st, bool keep_state,
-                                          const R* sde_rows = nullptr) {
+                                          unsigned char* lds, GroupStats st, bool keep_state) {
   using Sh = GroupShape<R, NG, PM, L, WPB, D>;
   using R2 = typename Sh::R2;
   constexpr PackLayout Lp{NG, PM};
   constexpr int G = Sh::G, PQ = Sh::PQ, NGP = Sh::NGP, XW = Sh::XW, TW = Sh::TW, TB = Sh::TB,
                 VM = Sh::VM;
   double (*tile_buf)[VM][TB + 1] = reinterpret_cast<double (*)[VM][TB + 1]>(lds);
-  R2 (*xch)[XW] = reinterpret_cast<R2 (*)[XW]>(lds + Sh::tile_bytes);
-  int* bad_t = reinterpret_cast<int*>(lds + Sh::tile_bytes + Sh::xch_bytes);
-  const int tid = threadIdx.x;
+  R2 (*xch)[TB + 1][XW] = reinterpret_cast<R2 (*)[TB + 1][XW]>(lds + Sh::tile_bytes);
+  double* rrf_l = reinterpret_cast<double*>(lds + Sh::rrf_off);
+  int* bad_t = reinterpret_cast<int*>(lds + Sh::bad_off);
+  // opaque, so that a persistent kernel's tile loop does not keep every address of
+  // the set-up below in registers
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int wv = tid >> 6, ln = tid & 63;
   const bool lane_on = ln < TW * L;
   const int tl = lane_on ? wv * TW + ln / L : TB;
@@ -707,158 +793,205 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
   const R* __restrict__ w = a.w;
   const int slot = (valid && a.traj_slot) ? a.traj_slot[ns] : -1;
 
-  // per-lane machine data (rows of Y and the operating point of my machines)
-  R yr[G][NG], yi[G][NG], c0[G], s0[G], i0r[G], i0i[G], res[G], dmp[G], inv2h[G], binc[G][PM];
+  // per-lane machine data (PackLayout): FP64 rotated, rows of Z, J, res, D; FP32
+  // plain, rows of Y, I0, res, D, E0 and 1/2H
+  constexpr bool ROT = rotated_form<R>();
+  R zr[G][NG], zi[G][NG], jr[G], ji[G], res[G], dmp[G], e0r[G], e0i[G], inv2h[G];
+  bool live[G];
 #pragma unroll
   for (int q = 0; q < G; ++q) {
     const int i = g * G + q;
     const bool on = i < NG;
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
-      yr[q][k] = on ? cf[Lp.yre() + i * NG + k] : R(0);
-      yi[q][k] = on ? cf[Lp.yim() + i * NG + k] : R(0);
+      zr[q][k] = on ? cf[Lp.yre() + i * NG + k] : R(0);
+      zi[q][k] = on ? cf[Lp.yim() + i * NG + k] : R(0);
     }
-    c0[q] = on ? cf[Lp.c0() + i] : R(0);
-    s0[q] = on ? cf[Lp.s0() + i] : R(0);
-    i0r[q] = on ? cf[Lp.i0r() + i] : R(0);
-    i0i[q] = on ? cf[Lp.i0i() + i] : R(0);
+    jr[q] = on ? cf[Lp.i0r() + i] : R(0);
+    ji[q] = on ? cf[Lp.i0i() + i] : R(0);
     res[q] = on ? cf[Lp.res() + i] : R(0);
     dmp[q] = on ? cf[Lp.dmp() + i] : R(0);
-    inv2h[q] = on ? cf[Lp.inv2h() + i] : R(0);
-#pragma unroll
-    for (int p = 0; p < PM; ++p) binc[q][p] = on ? cf[Lp.binc() + i * PM + p] : R(0);
+    e0r[q] = ROT ? R(1) : (on ? cf[Lp.c0() + i] : R(0));
+    e0i[q] = ROT ? R(0) : (on ? cf[Lp.s0() + i] : R(0));
+    inv2h[q] = ROT ? R(1) : (on ? cf[Lp.inv2h() + i] : R(0));
+    // in service: the machine has an EMF
+    live[q] = lane_on && on && (cf[Lp.c0() + i] != R(0) || cf[Lp.s0() + i] != R(0));
   }
-  bool live[G];
+
+  // my processes: pid[r], or none (PM)
+  int pid[PQ];
+  bool local = false;
 #pragma unroll
-  for (int q = 0; q < G; ++q) live[q] = lane_on && (c0[q] != R(0) || s0[q] != R(0));
-  // GEN: the gain and reference of my processes' injections
-  R pgain[PQ], pref[PQ];
+  for (int r = 0; r < PQ; ++r) pid[r] = lane_on && g + L * r < P ? g + L * r : PM;
+  if constexpr (G == 1 && PQ == 1) {
+    int mine = PM, n_mine = 0;
 #pragma unroll
-  for (int r = 0; r < PQ; ++r) {
-    pgain[r] = R(0);
-    pref[r] = R(0);
-    if constexpr (GEN) {
-      const int p = g + L * r;
-      if (lane_on && p < a.P) {
-        pgain[r] = a.sde[p * kSdeCols + SDE_GAIN];
-        pref[r] = a.sde[p * kSdeCols + SDE_REF];
+    for (int p = PM - 1; p >= 0; --p)
+      if (lane_on && p < P && (int)cf[Lp.owner() + p] == g) {
+        mine = p;
+        ++n_mine;
       }
-    }
+    local = __builtin_amdgcn_ballot_w64(n_mine > 1) == 0;
+    if (local) pid[0] = mine;
   }
-  // my processes p = g + L r
   R theta[PQ], sigma[PQ];
   bool own[PQ];
   int64_t wofs[PQ];
+  R sde[GEN ? PQ : 1][kSdeCols];  // GEN: my processes' rows (zero: none)
+  bool root = false, poly = false;  // GEN: some lane has a process of the form
 #pragma unroll
   for (int r = 0; r < PQ; ++r) {
-    const int p = g + L * r;
-    own[r] = lane_on && p < P;
-    theta[r] = own[r] ? cf[Lp.theta() + p] : R(0);
-    sigma[r] = own[r] ? cf[Lp.sigma() + p] : R(0);
-    wofs[r] = own[r] ? (int64_t)p * N + ns : 0;
-  }
-
-  // the process slots p >= P of my trajectory's exchange row stay zero
-  if (g == 0) {
+    own[r] = pid[r] < PM;
+    theta[r] = !GEN && own[r] ? cf[Lp.theta() + pid[r]] : R(0);
+    sigma[r] = !GEN && own[r] ? cf[Lp.sigma() + pid[r]] : R(0);
+    wofs[r] = own[r] ? (int64_t)pid[r] * N + ns : 0;
+    if constexpr (GEN) {
 #pragma unroll
-    for (int p = 0; p < PM; ++p) xch[tl][NGP + p] = R2{R(0), R(0)};
-  }
-  wave_lds_sync();
-
-  auto rhs = [&](const R (&yd)[G], const R (&yw)[G], const R (&yx)[PQ], const R (&wv)[PQ],
-                 R (&kd)[G], R (&kw)[G], R (&kx)[PQ]) {
-    R dc[G], ds[G], hx[G], shs[G], chs[G];
-    // idle lanes (whose exchange row is shared scratch) and machines without
-    // EMF (padding, tripped) give dE = 0 at any angle: their angles are not
-    // passed on, so they cannot push the wave off the small-angle branch
-#pragma unroll
-    for (int q = 0; q < G; ++q) hx[q] = live[q] ? yd[q] * R(0.5) : R(0);
-    sincos_many(hx, shs, chs);
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-      const R sh = shs[q], ch = chs[q];
-      const R sd = R(2) * sh * ch;
-      const R omc = R(2) * sh * sh;
-      dc[q] = -(c0[q] * omc + s0[q] * sd);
-      ds[q] = c0[q] * sd - s0[q] * omc;
-      xch[tl][g * G + q] = R2{dc[q], ds[q]};
+      for (int c = 0; c < kSdeCols; ++c) sde[r][c] = own[r] ? a.sde[pid[r] * kSdeCols + c] : R(0);
+      root = root || sde[r][SDE_FORM] == R(2);
+      poly = poly || sde[r][SDE_FORM] == R(1);
     }
-    R gk[PQ];  // GEN: the processes' derivatives
+  }
+  if constexpr (GEN) {
+    root = __builtin_amdgcn_ballot_w64(root) != 0;
+    poly = __builtin_amdgcn_ballot_w64(poly) != 0;
+  }
+  // injection: local, the factor of my process at my machine; else the
+  // machines' rows of the injection matrix
+  R binl = R(0), binc[G][PM];
 #pragma unroll
-    for (int r = 0; r < PQ; ++r) {
-      R pub = yx[r];
-      if constexpr (GEN) {
-        // the injected power from registers (it feeds the exchange, on the
-        // stage's critical path); the drift and diffusion come from the rows
-        // staged in LDS (rows past P are zero; a lane that owns no process
-        // reads row 0)
-        const int p = g + L * r;
-        R inj;
-        gk[r] = sde_rhs<R>(sde_rows + (own[r] ? p : 0) * kSdeCols, yx[r], wv[r], inj);
-        pub = pgain[r] * (yx[r] - pref[r]);
-      }
-      if (own[r]) xch[tl][NGP + g + L * r] = R2{pub, R(0)};
+  for (int q = 0; q < G; ++q)
+#pragma unroll
+    for (int p = 0; p < PM; ++p) {
+      const int i = g * G + q;
+      binc[q][p] = i < NG ? cf[Lp.binc() + i * PM + p] : R(0);
+      if (G == 1 && PQ == 1 && local && p == pid[0]) binl = binc[q][p];
+    }
+
+  // the process slots p >= P of my trajectory's exchange rows stay zero
+  auto clear_slots = [&]() {
+    if (g == 0) {
+#pragma unroll
+      for (int p = 0; p < PM; ++p) xch[0][tl][NGP + p] = xch[1][tl][NGP + p] = R2{R(0), R(0)};
     }
     wave_lds_sync();
-    // two accumulator pairs (even / odd columns) halve the FMA dependency chains
-    R ir[G], ii[G], jr[G], ji[G];
+  };
+  clear_slots();
+
+  // RK4 of the swing equations in two exchanges per step: the angles of stages
+  // 1 and 2 are known at the start of the step (an angle's derivative is its
+  // speed), those of stages 3 and 4 once the accelerations of 1 and 2 are.  So
+  // stages 1 and 2, then 3 and 4, share one rotation, one exchange and one pass
+  // over the rows of Y.
+  //
+  // Network part of a pair of stages at angles d[h], h = 0, 1: rotation, exchange
+  // and, per machine, sum_k Z_ik eps_k (cr, ci); in the plain form sum_k Y_ik dE_k
+  // of the rotated EMFs' deviations dE = -omc + j sd, omc and sd then turned by E0.
+  R sd[2][G], omc[2][G], cr[2][G], ci[2][G];
+  auto network = [&](const R (&d)[2][G], const R (&pub)[2][PQ]) {
+    rotation_stages<R, 2, G>(d, live, sd, omc);
+    if constexpr (!ROT) {
 #pragma unroll
-    for (int q = 0; q < G; ++q) { ir[q] = R(0); ii[q] = R(0); jr[q] = R(0); ji[q] = R(0); }
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < G; ++q) turn(e0r[q], e0i[q], omc[h][q], sd[h][q]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        // a machine without EMF has a zero column of Z, whatever its angle has become
+        xch[h][tl][g * G + q] = R2{omc[h][q], sd[h][q]};
+        cr[h][q] = ci[h][q] = R(0);
+      }
+      if (!local) {
+#pragma unroll
+        for (int r = 0; r < PQ; ++r)
+          if (own[r]) xch[h][tl][NGP + pid[r]] = R2{pub[h][r], R(0)};
+      }
+    }
+    wave_lds_sync();
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
       // keep at most 8 exchange loads in flight: bounds the registers the
-      // scheduler would otherwise spend hoisting all NG loads
-      if ((k & 7) == 0 && k > 0) asm volatile("" ::: "memory");
-      const R2 e = xch[tl][k];
+      // scheduler would otherwise spend hoisting all of them
+      if ((k & 3) == 0 && k > 0) asm volatile("" ::: "memory");
 #pragma unroll
-      for (int q = 0; q < G; ++q) {
-        // complex MAC as four FMAs (no intermediate products)
-        if (k & 1) {
-          jr[q] = fma(yr[q][k], e.x, jr[q]);
-          jr[q] = fma(-yi[q][k], e.y, jr[q]);
-          ji[q] = fma(yr[q][k], e.y, ji[q]);
-          ji[q] = fma(yi[q][k], e.x, ji[q]);
-        } else {
-          ir[q] = fma(yr[q][k], e.x, ir[q]);
-          ir[q] = fma(-yi[q][k], e.y, ir[q]);
-          ii[q] = fma(yr[q][k], e.y, ii[q]);
-          ii[q] = fma(yi[q][k], e.x, ii[q]);
+      for (int h = 0; h < 2; ++h) {
+        const R2 e = xch[h][tl][k];  // eps = -e.x + j e.y
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+          // complex MAC as four FMAs; a dependent FMA issues as soon as the
+          // pipe is free, so one chain per component is enough
+          cr[h][q] = fma(-zr[q][k], e.x, cr[h][q]);
+          ci[h][q] = fma(-zi[q][k], e.x, ci[h][q]);
+          cr[h][q] = fma(-zi[q][k], e.y, cr[h][q]);
+          ci[h][q] = fma(zr[q][k], e.y, ci[h][q]);
         }
       }
     }
-    R inj[G];
+    if (local) wave_lds_sync();
+  };
+  // injected powers of my machines in stage h
+  auto injection = [&](int h, const R (&pub)[PQ], R (&inj)[G]) {
+    if (G == 1 && PQ == 1 && local) {  // wave-uniform
+      inj[0] = binl * pub[0];
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < G; ++q) inj[q] = R(0);
     // every process slot, the padding ones included (zero, as their columns
-    // of binc): no branch on P between the exchange reads and their use
+    // of binc)
 #pragma unroll
     for (int p = 0; p < PM; ++p) {
-      const R xp = xch[tl][NGP + p].x;
+      const R xp = xch[h][tl][NGP + p].x;
 #pragma unroll
       for (int q = 0; q < G; ++q) inj[q] += binc[q][p] * xp;
     }
     wave_lds_sync();
+  };
+  // accelerations of my machines in stage h at speeds u
+  auto accel = [&](int h, const R (&u)[G], const R (&inj)[G], R (&kw)[G]) {
 #pragma unroll
     for (int q = 0; q < G; ++q) {
-      ir[q] += jr[q];
-      ii[q] += ji[q];
-      const R dpe = dc[q] * i0r[q] + ds[q] * i0i[q] + (c0[q] + dc[q]) * ir[q] + (s0[q] + ds[q]) * ii[q];
-      const R F = res[q] - dpe - dmp[q] * yw[q] + inj[q];
-      kd[q] = a.wb * yw[q];
-      kw[q] = F * inv2h[q];
+      R F = res[q] - dmp[q] * u[q] + inj[q];
+      F = fma(omc[h][q], jr[q], F);
+      F = fma(-sd[h][q], ji[q], F);
+      if constexpr (ROT) {
+        F = fma(omc[h][q] - R(1), cr[h][q], F);
+        kw[q] = fma(-sd[h][q], ci[h][q], F);
+      } else {
+        F = fma(omc[h][q] - e0r[q], cr[h][q], F);
+        F = fma(-(e0i[q] + sd[h][q]), ci[h][q], F);
+        kw[q] = F * inv2h[q];
+      }
     }
-#pragma unroll
-    for (int r = 0; r < PQ; ++r) {
-      if constexpr (GEN)
-        kx[r] = own[r] ? gk[r] : R(0);
-      else
-        kx[r] = -theta[r] * yx[r] + sigma[r] * wv[r];
-    }
+  };
+  // derivative of my process r at x with path value wv, and what it injects
+  auto rate = [&](int r, R x, R wv) {
+    if constexpr (GEN)
+      return sde_rate(sde[r], x, wv, root, poly);
+    else
+      return sigma[r] * wv - theta[r] * x;
+  };
+  auto power = [&](int r, R x) {
+    if constexpr (GEN)
+      return sde[r][SDE_GAIN] * (x - sde[r][SDE_REF]);
+    else
+      return x;
   };
 
   // RRF sum of trajectory tid of this tile (threads tid < TB; see IntegArgs::rrf_w)
   double racc = 0.0;
-  if (a.rrf_w && a.s_begin > 0 && tid < cnt) racc = a.rrf_acc[tile * TB + tid];
+  if (a.rrf_w) {
+    if (a.s_begin > 0 && tid < cnt) racc = a.rrf_acc[tile * TB + tid];
+    // the weights and the outputs' offsets, read by every term of every step
+    // (visible after the first flush's barrier)
+    for (int v = tid; v < V; v += 64 * WPB) {
+      rrf_l[v] = a.rrf_w[v];
+      rrf_l[VM + v] = v < n ? a.delta0[v] : 0.0;
+    }
+  }
   // Reduce the buffered steps [s_first, s_first + nb): thread q of the
   // workgroup takes rows (step, variable) q, q + 64 WPB, ...
   auto flush = [&](int64_t s_first, int nb) {
@@ -877,38 +1010,55 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
         *dst = make_double2(old.x + dl * (nb2 / tot), old.y + m2 + dl * dl * (na * nb2 / tot));
       }
     }
-    // the epilogue's RRF: thread j sums trajectory j's buffered steps in order
-    if (a.rrf_w && tid < cnt) {
-      for (int b = 0; b < nb; ++b) {
+    // the epilogue's RRF: a thread per (buffered step, trajectory) forms u and leaves
+    // h u^2 in its trajectory's exchange row (free between steps), then thread j
+    // adds trajectory j's in step order
+    if (a.rrf_w) {
+      static_assert((size_t)D * TB * sizeof(double) <= Sh::xch_bytes, "room for the RRF terms");
+      double* term = reinterpret_cast<double*>(lds + Sh::tile_bytes);
+      for (int q = tid; q < nb * TB; q += 64 * WPB) {
+        const int b = q / TB, j = q - b * TB;
         const int64_t s = s_first + b;
         double u = 0.0;
-        for (int v = 0; v < V; ++v) {
-          const double y = tile_buf[b][v][tid];
-          u += a.rrf_w[v] * (v < n ? a.delta0[v] + y : y);
-        }
-        racc += (s == 0 || s == a.S ? 0.5 : 1.0) * u * u;
+#pragma unroll 4
+        for (int v = 0; v < V; ++v) u += rrf_l[v] * (rrf_l[VM + v] + tile_buf[b][v][j]);
+        term[q] = (s == 0 || s == a.S ? 0.5 : 1.0) * u * u;
       }
+      __syncthreads();
+      if (tid < cnt)
+        for (int b = 0; b < nb; ++b) racc += term[b * TB + tid];
+      __syncthreads();
+      clear_slots();
     }
     __syncthreads();
   };
   int nbuf = 0;
   int64_t s_first = 0;
   double coff = 0.0;  // common-angle offset of my trajectory (see IntegArgs::recenter)
+  // Where my outputs go in a buffered step's rows; machines and processes that do
+  // not exist write the padding column TB (idle lanes are in it anyway), so
+  // that no lane branches.
+  int od[G], ow[G], ox[PQ];
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    const int i = g * G + q;
+    od[q] = i < n ? i * (TB + 1) + tl : TB;
+    ow[q] = i < n ? (n + i) * (TB + 1) + tl : TB;
+  }
+#pragma unroll
+  for (int r = 0; r < PQ; ++r) ox[r] = own[r] ? (2 * n + pid[r]) * (TB + 1) + tl : TB;
+  const bool traced = __builtin_amdgcn_ballot_w64(slot >= 0) != 0;  // some lane stores a trajectory
   auto emit = [&](int64_t s, const R (&yd)[G], const R (&yw)[G], const R (&yx)[PQ]) {
     if (nbuf == 0) s_first = s;
-    double (*tb)[TB + 1] = tile_buf[nbuf];
+    double* tb = &tile_buf[nbuf][0][0];
 #pragma unroll
     for (int q = 0; q < G; ++q) {
-      const int i = g * G + q;
-      if (lane_on && i < n) {
-        tb[i][tl] = coff + (double)yd[q];
-        tb[n + i][tl] = (double)yw[q];
-      }
+      tb[od[q]] = coff + (double)yd[q];
+      tb[ow[q]] = (double)yw[q];
     }
 #pragma unroll
-    for (int r = 0; r < PQ; ++r)
-      if (own[r]) tb[2 * n + g + L * r][tl] = (double)yx[r];
-    if (slot >= 0) {
+    for (int r = 0; r < PQ; ++r) tb[ox[r]] = (double)yx[r];
+    if (traced && slot >= 0) {
       // every lane of a selected trajectory writes its own outputs
       double* o = a.traj + ((int64_t)slot * (a.S + 1) + s) * V;
 #pragma unroll
@@ -921,7 +1071,7 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
       }
 #pragma unroll
       for (int r = 0; r < PQ; ++r)
-        if (own[r]) o[2 * n + g + L * r] = (double)yx[r];
+        if (own[r]) o[2 * n + pid[r]] = (double)yx[r];
     }
     if (++nbuf == D) {
       flush(s_first, nbuf);
@@ -935,7 +1085,7 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
 #pragma unroll
     for (int q = 0; q < G; ++q) { yd[q] = R(0); yw[q] = R(0); }
 #pragma unroll
-    for (int r = 0; r < PQ; ++r) yx[r] = own[r] ? cf[Lp.xi0() + g + L * r] : R(0);
+    for (int r = 0; r < PQ; ++r) yx[r] = own[r] ? cf[Lp.xi0() + pid[r]] : R(0);
     emit(0, yd, yw, yx);
   } else {
 #pragma unroll
@@ -950,63 +1100,98 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
   }
 
   const R dt = a.dt, h2 = a.dt * R(0.5), dt6 = a.dt / R(6);
+  const R hw2 = h2 * a.wb, hw = dt * a.wb, dw6 = dt6 * a.wb;
   const R inv_n = R(1) / (R)a.n_ref;
   const int64_t colstride = (int64_t)P * N;
-  // KLE path values of my processes: the two new stage columns of step s are
-  // loaded one step ahead so their latency overlaps the previous step.
-  R w0[PQ], w1[PQ], w2[PQ];
+  // KLE path values of my processes: the two new stage columns of a step are
+  // loaded two steps ahead (a step of a lone wave is shorter than the latency
+  // of memory).
+  // A lane without a process reads the first process's path (its sigma is
+  // zero), the last steps read the last columns again: no lane branches.
+  R w0[PQ], w1[PQ], w2[PQ], n1[PQ], n2[PQ];
+  auto column = [&](int64_t s) {  // first column of step s of this chunk
+    return (2 * (s < a.s_end ? s : a.s_end - 1) - a.c_base) * colstride;
+  };
+  {
+    const int64_t c1 = column(a.s_begin + 1);
 #pragma unroll
-  for (int r = 0; r < PQ; ++r) {
-    w0[r] = own[r] ? w[wofs[r]] : R(0);
-    w1[r] = own[r] ? w[colstride + wofs[r]] : R(0);
-    w2[r] = own[r] ? w[2 * colstride + wofs[r]] : R(0);
+    for (int r = 0; r < PQ; ++r) {
+      w0[r] = w[wofs[r]];
+      w1[r] = w[colstride + wofs[r]];
+      w2[r] = w[2 * colstride + wofs[r]];
+      n1[r] = w[c1 + colstride + wofs[r]];
+      n2[r] = w[c1 + 2 * colstride + wofs[r]];
+    }
   }
   for (int64_t s = a.s_begin; s < a.s_end; ++s) {
-    const int64_t cl = 2 * s - a.c_base;
-    const bool more = s + 1 < a.s_end;
-    R n1[PQ], n2[PQ];
+    const int64_t c2 = column(s + 2);
+    R m1[PQ], m2[PQ];
 #pragma unroll
     for (int r = 0; r < PQ; ++r) {
-      n1[r] = (more && own[r]) ? w[(cl + 3) * colstride + wofs[r]] : R(0);
-      n2[r] = (more && own[r]) ? w[(cl + 4) * colstride + wofs[r]] : R(0);
+      m1[r] = w[c2 + colstride + wofs[r]];
+      m2[r] = w[c2 + 2 * colstride + wofs[r]];
     }
-    R kd[G], kw[G], kx[PQ], ad[G], aw[G], ax[PQ], td[G], tw[G], tx[PQ];
-    rhs(yd, yw, yx, w0, kd, kw, kx);
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-      ad[q] = kd[q]; aw[q] = kw[q];
-      td[q] = yd[q] + h2 * kd[q]; tw[q] = yw[q] + h2 * kw[q];
-    }
-#pragma unroll
-    for (int r = 0; r < PQ; ++r) { ax[r] = kx[r]; tx[r] = yx[r] + h2 * kx[r]; }
-    rhs(td, tw, tx, w1, kd, kw, kx);
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-      ad[q] += R(2) * kd[q]; aw[q] += R(2) * kw[q];
-      td[q] = yd[q] + h2 * kd[q]; tw[q] = yw[q] + h2 * kw[q];
-    }
-#pragma unroll
-    for (int r = 0; r < PQ; ++r) { ax[r] += R(2) * kx[r]; tx[r] = yx[r] + h2 * kx[r]; }
-    rhs(td, tw, tx, w1, kd, kw, kx);
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-      ad[q] += R(2) * kd[q]; aw[q] += R(2) * kw[q];
-      td[q] = yd[q] + dt * kd[q]; tw[q] = yw[q] + dt * kw[q];
-    }
-#pragma unroll
-    for (int r = 0; r < PQ; ++r) { ax[r] += R(2) * kx[r]; tx[r] = yx[r] + dt * kx[r]; }
-    rhs(td, tw, tx, w2, kd, kw, kx);
-#pragma unroll
-    for (int q = 0; q < G; ++q) {
-      yd[q] += dt6 * (ad[q] + kd[q]);
-      yw[q] += dt6 * (aw[q] + kw[q]);
-    }
+    // the four stage values of my processes (they do not see the machines)
+    R pub[4][PQ];
 #pragma unroll
     for (int r = 0; r < PQ; ++r) {
-      yx[r] += dt6 * (ax[r] + kx[r]);
+      const R x1 = yx[r], k1 = rate(r, x1, w0[r]);
+      const R x2 = x1 + h2 * k1, k2 = rate(r, x2, w1[r]);
+      const R x3 = x1 + h2 * k2, k3 = rate(r, x3, w1[r]);
+      const R x4 = x1 + dt * k3, k4 = rate(r, x4, w2[r]);
+      pub[0][r] = power(r, x1);
+      pub[1][r] = power(r, x2);
+      pub[2][r] = power(r, x3);
+      pub[3][r] = power(r, x4);
+      yx[r] = x1 + dt6 * (((k1 + R(2) * k2) + R(2) * k3) + k4);
       w0[r] = w2[r];
       w1[r] = n1[r];
       w2[r] = n2[r];
+      n1[r] = m1[r];
+      n2[r] = m2[r];
+    }
+    // the angles' derivatives are w_b times the stage speeds: their sum runs
+    // over the speeds, and w_b sits in the step constants
+    R d[2][G], u[2][G], kw[G], inj[G], su[G], sa[G];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      d[0][q] = yd[q];
+      d[1][q] = yd[q] + hw2 * yw[q];
+    }
+    network(d, *reinterpret_cast<const R (*)[2][PQ]>(&pub[0]));
+    injection(0, pub[0], inj);
+    accel(0, yw, inj, kw);
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      u[0][q] = yw[q] + h2 * kw[q];
+      su[q] = yw[q] + R(2) * u[0][q];
+      sa[q] = kw[q];
+      d[0][q] = yd[q] + hw2 * u[0][q];
+    }
+    injection(1, pub[1], inj);
+    accel(1, u[0], inj, kw);
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      u[1][q] = yw[q] + h2 * kw[q];
+      su[q] += R(2) * u[1][q];
+      sa[q] += R(2) * kw[q];
+      d[1][q] = yd[q] + hw * u[1][q];
+    }
+    network(d, *reinterpret_cast<const R (*)[2][PQ]>(&pub[2]));
+    injection(0, pub[2], inj);
+    accel(0, u[1], inj, kw);
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      u[0][q] = yw[q] + dt * kw[q];
+      su[q] += u[0][q];
+      sa[q] += R(2) * kw[q];
+    }
+    injection(1, pub[3], inj);
+    accel(1, u[0], inj, kw);
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      yd[q] += dw6 * su[q];
+      yw[q] += dt6 * (sa[q] + kw[q]);
     }
     if (a.recenter && ((s + 1) & 7) == 0) {
       // every eighth step (of the absolute step count, so time chunks keep the
@@ -1019,16 +1204,17 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
       R part = R(0);
 #pragma unroll
       for (int q = 0; q < G; ++q)
-        if (g * G + q < n && (c0[q] != R(0) || s0[q] != R(0))) part += yd[q];
-      xch[tl][g] = R2{part, R(0)};
+        if (live[q]) part += yd[q];
+      xch[0][tl][g] = R2{part, R(0)};
       wave_lds_sync();
       R sum = R(0);
-      for (int k = 0; k < L; ++k) sum += xch[tl][k].x;
+      for (int k = 0; k < L; ++k) sum += xch[0][tl][k].x;
       wave_lds_sync();
       const R ref = sum * inv_n;
       coff += (double)ref;
 #pragma unroll
-      for (int q = 0; q < G; ++q) yd[q] -= ref;
+      for (int q = 0; q < G; ++q)  // padding machines stay at rest
+        if (g * G + q < n) yd[q] -= ref;
     }
     emit(s + 1, yd, yw, yx);
   }
@@ -1094,13 +1280,8 @@ k_rk4_group_gen(IntegArgs<R> a) {
   constexpr int D = WPB == 1 ? 4 : 8;
   using Sh = GroupShape<R, NG, PM, L, WPB, D>;
   __shared__ __attribute__((aligned(16))) unsigned char lds[Sh::lds_bytes];
-  // the processes' rows (PM of them, zero past P) staged in LDS once: they
-  // are read by the owner lanes at every stage
-  __shared__ R sde_l[PM * kSdeCols];
-  for (int i = threadIdx.x; i < PM * kSdeCols; i += 64 * WPB) sde_l[i] = a.sde[i];
-  __syncthreads();
   GroupStats st{reinterpret_cast<double2*>(a.partial) + (int64_t)blockIdx.x * (a.S + 1) * a.V, 0};
-  group_run<R, NG, PM, L, WPB, D, true>(a, blockIdx.x, lds, st, true, sde_l);
+  group_run<R, NG, PM, L, WPB, D, true>(a, blockIdx.x, lds, st, true);
 }
 
 }  // namespace fmc

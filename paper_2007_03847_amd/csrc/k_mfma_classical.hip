@@ -52,7 +52,7 @@ hipError_t launch_pack_mc(const double* canon, int n, int P, const int32_t* gen,
 hipError_t launch_pack_batch(const BatchVariantInfo& b, const double* canon, int n, int P,
                              const int32_t* gen, float* coef, hipStream_t st) {
   if (b.prod != 0) return launch_pack_mc(canon, n, P, gen, b.NG, b.prod == 2, coef, st);
-  return launch_pack<float>(canon, n, P, gen, b.NG, b.PM, coef, st);
+  return launch_pack<float>(canon, n, P, gen, gen, false, b.NG, b.PM, coef, st);
 }
 
 // Persistent matrix-core kernels, one per block count NB (a kernel's register

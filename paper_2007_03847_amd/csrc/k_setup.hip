@@ -592,30 +592,45 @@ hipError_t launch_setup_post(const double* pre, int n, int P, const double2* Yp,
   return hipGetLastError();
 }
 
-// Packed, padded coefficients of a variant in its arithmetic type.
+// Packed, padded coefficients of a variant in its arithmetic type (PackLayout).
 template <typename R>
 __global__ void __launch_bounds__(256) k_pack(const double* __restrict__ cn, int n, int P,
-                                              const int32_t* __restrict__ gen, int NG, int PM,
-                                              R* __restrict__ coef) {
+                                              const int32_t* __restrict__ gen,
+                                              const int32_t* __restrict__ owner, bool rotated,
+                                              int NG, int PM, R* __restrict__ coef) {
   CanonLayout C{n, P};
   PackLayout L{NG, PM};
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= L.size()) return;
+  auto emf = [&](int i) { return make_double2(cn[C.c0() + i], cn[C.s0() + i]); };
+  auto conj_emf = [&](int i) { return make_double2(cn[C.c0() + i], -cn[C.s0() + i]); };
+  auto scale = [&](int i) { return rotated ? cn[C.inv2h() + i] : 1.0; };
   double v = 0.0;
-  if (q < L.yim()) {
-    const int i = q / NG, k = q % NG;
-    if (i < n && k < n) v = cn[C.yre() + (int64_t)i * n + k];
-  } else if (q < L.binc()) {
-    const int e = q - L.yim(), i = e / NG, k = e % NG;
-    if (i < n && k < n) v = cn[C.yim() + (int64_t)i * n + k];
+  if (q < L.binc()) {
+    const int e = q < L.yim() ? q : q - L.yim(), i = e / NG, k = e % NG;
+    if (i < n && k < n) {
+      double2 y = make_double2(cn[C.yre() + (int64_t)i * n + k], cn[C.yim() + (int64_t)i * n + k]);
+      if (rotated) y = cmul(cmul(conj_emf(i), y), emf(k));
+      v = (q < L.yim() ? y.x : y.y) * scale(i);
+    }
   } else if (q < L.c0()) {
     const int e = q - L.binc(), i = e / PM, p = e % PM;
-    v = (i < n && p < P && gen[p] == i) ? 1.0 : 0.0;
+    v = (i < n && p < P && gen[p] == i) ? scale(i) : 0.0;
   } else if (q < L.theta()) {
     const int e = q - L.c0(), f = e / NG, i = e % NG;
     // fields c0, s0, i0r, i0i, res, dmp, inv2h in canonical order
     const int64_t base[7] = {C.c0(), C.s0(), C.i0r(), C.i0i(), C.res(), C.dmp(), C.inv2h()};
-    if (i < n) v = cn[base[f] + i];
+    if (i < n) {
+      v = cn[base[f] + i];
+      if (rotated && (f == 2 || f == 3)) {
+        const double2 J = cmul(conj_emf(i), make_double2(cn[C.i0r() + i], cn[C.i0i() + i]));
+        v = f == 2 ? J.x : J.y;
+      }
+      if (f >= 2 && f <= 5) v *= scale(i);
+    }
+  } else if (q >= L.owner()) {
+    const int p = q - L.owner();
+    v = p < P ? (double)owner[p] : -1.0;
   } else {
     const int e = q - L.theta(), f = e / PM, p = e % PM;
     const int64_t base[3] = {C.theta(), C.sigma(), C.xi0()};
@@ -625,17 +640,17 @@ __global__ void __launch_bounds__(256) k_pack(const double* __restrict__ cn, int
 }
 
 template <typename R>
-hipError_t launch_pack(const double* canon, int n, int P, const int32_t* gen, int NG, int PM,
-                       R* coef, hipStream_t st) {
+hipError_t launch_pack(const double* canon, int n, int P, const int32_t* gen,
+                       const int32_t* owner, bool rotated, int NG, int PM, R* coef, hipStream_t st) {
   PackLayout L{NG, PM};
   hipLaunchKernelGGL(k_pack<R>, dim3((L.size() + 255) / 256), dim3(256), 0, st, canon, n, P, gen,
-                     NG, PM, coef);
+                     owner, rotated, NG, PM, coef);
   return hipGetLastError();
 }
-template hipError_t launch_pack<double>(const double*, int, int, const int32_t*, int, int,
-                                        double*, hipStream_t);
-template hipError_t launch_pack<float>(const double*, int, int, const int32_t*, int, int, float*,
-                                       hipStream_t);
+template hipError_t launch_pack<double>(const double*, int, int, const int32_t*, const int32_t*,
+                                        bool, int, int, double*, hipStream_t);
+template hipError_t launch_pack<float>(const double*, int, int, const int32_t*, const int32_t*, bool,
+                                       int, int, float*, hipStream_t);
 
 // Ordered merge of per-group statistics into mean and variance (Alg. 1 step
 // 4): partial[g * gstride + q] holds (mean, M2) of group g's samples for
