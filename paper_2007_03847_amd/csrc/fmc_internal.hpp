@@ -211,10 +211,17 @@ hipError_t launch_stats_merge_rows(const double2* partial, int64_t gstride, int6
 
 // Integrator variants: NG machines, PM processes, L lanes per trajectory,
 // WPB waves per workgroup; a workgroup integrates group_size() trajectories.
+// team: a tile of 16 trajectories shared by the workgroup's waves (k_team.hip),
+// four lanes per trajectory in each wave, two machines per lane.
 struct VariantInfo {
   int id, NG, PM, L, WPB;
-  int group_size() const { return (64 / L) * WPB; }
+  bool team = false;
+  int group_size() const { return team ? 16 : (64 / L) * WPB; }
   int G() const { return (NG + L - 1) / L; }
+  int PQ() const { return (PM + L - 1) / L; }
+  // rows of the state buffer (n_groups * 64 * WPB values each); a team's tile
+  // takes 256 WPB + 160 values (team_state)
+  int state_rows() const { return team ? 6 : 2 * G() + PQ() + kOffsetRows; }
 };
 int n_variants();
 const VariantInfo& variant(int i);
@@ -226,6 +233,8 @@ hipError_t launch_integrate_gen_f64(int variant_id, const IntegArgs<double>& a, 
                                     hipStream_t st);
 hipError_t launch_integrate_gen_f32(int variant_id, const IntegArgs<float>& a, int64_t n_groups,
                                     hipStream_t st);
+template <typename R>
+hipError_t launch_team(const VariantInfo& v, const IntegArgs<R>& a, int64_t n_groups, hipStream_t st);
 hipError_t launch_integrate_f32(int variant_id, const IntegArgs<float>& a, int64_t n_groups,
                                 hipStream_t st);
 // Implicit trapezoid (FP64, classical machines) on the shape of a

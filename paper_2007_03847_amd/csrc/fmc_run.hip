@@ -135,7 +135,7 @@ int run_chunks(Context* c, const fmc_params* par, int vid, int n, int P, int64_t
   int rc;
   if ((rc = c->ensure("w", (size_t)(2 * Sc + 1) * P * N * bw, &w[0]))) return rc;
   if ((rc = c->ensure("w1", (size_t)(2 * Sc + 1) * P * N * bw, &w[1]))) return rc;
-  if ((rc = c->ensure("state", (size_t)(2 * vi.NG + vi.PM + kOffsetRows) * lanes * bw, &state))) return rc;
+  if ((rc = c->ensure("state", (size_t)vi.state_rows() * lanes * bw, &state))) return rc;
   if ((rc = ensure_gstream(c))) return rc;
   hipStream_t ks = c->gstream;
   // merge of the rows completed by chunk [s0, s1] (row 0 with the first)
@@ -207,7 +207,9 @@ int run_chunks(Context* c, const fmc_params* par, int vid, int n, int P, int64_t
     a.s_end = s1;
     a.c_base = 2 * s0;
     ct.int0.push_back(evp.record());
-    if constexpr (sizeof(R) == 8)
+    if (vi.team)
+      e = launch_team<R>(vi, a, n_groups, c->stream);
+    else if constexpr (sizeof(R) == 8)
       e = trap ? launch_trap_f64(vid, a, n_groups, c->stream)
                : launch_integrate_f64(vid, a, n_groups, c->stream);
     else
@@ -279,11 +281,11 @@ int run_single(Context* c, const fmc_system* sys, const fmc_disturbance* dist,
   const bool trap = par->integrator == FMC_TRAP;
   const bool lane_only = trap;
   int vid = par->variant >= 0 ? par->variant
-                              : (lane_only ? -1 : pick_variant(c, n, P, N, par->precision));
+                              : (lane_only ? -1 : pick_variant(c, n, P, N, par->precision, dist->proc != nullptr));
   if (lane_only && vid < 0) {
     for (int i = 0; i < n_variants(); ++i) {
       const VariantInfo& v = variant(i);
-      if (v.L != 1 || v.NG < n || v.PM < P || (trap && v.NG > kTrapMaxGen)) continue;
+      if (v.L != 1 || v.team || v.NG < n || v.PM < P || (trap && v.NG > kTrapMaxGen)) continue;
       if (vid < 0 || v.NG * v.NG + v.PM < variant(vid).NG * variant(vid).NG + variant(vid).PM) vid = i;
     }
   }
@@ -291,7 +293,9 @@ int run_single(Context* c, const fmc_system* sys, const fmc_disturbance* dist,
     return fail(FMC_EINVAL, "no integrator variant for n=" + std::to_string(n) + ", P=" + std::to_string(P));
   const VariantInfo& vi = variant(vid);
   if (vi.NG < n || vi.PM < P) return fail(FMC_EINVAL, "variant too small for the system");
-  if (trap && (vi.L != 1 || vi.NG > kTrapMaxGen))
+  if (vi.team && dist->proc)
+    return fail(FMC_EINVAL, "the team variants take Ornstein-Uhlenbeck disturbances only");
+  if (trap && (vi.L != 1 || vi.team || vi.NG > kTrapMaxGen))
     return fail(FMC_EINVAL, "the implicit trapezoid runs on one-trajectory-per-lane variants of at "
                             "most 16 machines");
   const double f0 = sys->f0_hz > 0.0 ? sys->f0_hz : 60.0;
@@ -319,7 +323,7 @@ int run_single(Context* c, const fmc_system* sys, const fmc_disturbance* dist,
   void* coef = nullptr;
   const PackLayout PL{vi.NG, vi.PM};
   if ((rc = c->ensure("coef", (size_t)PL.size() * bw, &coef))) return rc;
-  HIPCHK(f64 ? launch_pack<double>(canon, n, P, gen_d, gen_d, vi.L > 1, vi.NG, vi.PM, (double*)coef, c->stream)
+  HIPCHK(f64 ? launch_pack<double>(canon, n, P, gen_d, gen_d, vi.L > 1 || vi.team, vi.NG, vi.PM, (double*)coef, c->stream)
              : launch_pack<float>(canon, n, P, gen_d, gen_d, false, vi.NG, vi.PM, (float*)coef, c->stream));
 
   // A network event: the post-event admittance (given, or the network reduced
@@ -367,7 +371,7 @@ int run_single(Context* c, const fmc_system* sys, const fmc_disturbance* dist,
     if ((rc = c->ensure("canon_post", (size_t)CL.size() * sizeof(double), &cp))) return rc;
     HIPCHK(launch_setup_post(canon, n, P, Yp_d, Yinf_d, sys->V_inf, g, (double*)cp, c->stream));
     if ((rc = c->ensure("coef_post", (size_t)PL.size() * bw, &coef_post))) return rc;
-    HIPCHK(f64 ? launch_pack<double>((const double*)cp, n, P, genp_d, gen_d, vi.L > 1, vi.NG, vi.PM, (double*)coef_post, c->stream)
+    HIPCHK(f64 ? launch_pack<double>((const double*)cp, n, P, genp_d, gen_d, vi.L > 1 || vi.team, vi.NG, vi.PM, (double*)coef_post, c->stream)
                : launch_pack<float>((const double*)cp, n, P, genp_d, gen_d, false, vi.NG, vi.PM, (float*)coef_post, c->stream));
     n_ref_post = n - (g >= 0 ? 1 : 0);
   }

@@ -38,6 +38,9 @@ static const std::vector<VariantInfo>& lane_table() {
 #define FMC_X(NG, PM, L, WPB) v.push_back(VariantInfo{id++, NG, PM, L, WPB});
     FMC_VARIANTS(FMC_X)
 #undef FMC_X
+#define FMC_X(NG, NB) v.push_back(VariantInfo{id++, NG, 8, 4 * NB, NB, true});
+    FMC_TEAM_VARIANTS(FMC_X)
+#undef FMC_X
     return v;
   }();
   return t;
@@ -46,32 +49,52 @@ static const std::vector<VariantInfo>& lane_table() {
 int n_variants() { return (int)lane_table().size(); }
 const VariantInfo& variant(int i) { return lane_table()[i]; }
 
-// Choice used when no tuned one is cached.  A lanes-per-trajectory variant
-// with one machine per lane (L >= NG >= n) and at most as many padding
-// machines as real ones comes first: the fewest padding machines, then four
-// waves per workgroup (measured on the 10-machine
-// workload at N = 1e4: L = 10 x 4 waves 9.9 ms per FP64 pass, the other
-// L = 10 shapes 12.3-12.7, L = 16 17-23, two machines per lane 11.9, one
-// trajectory per lane 102).  Otherwise a cost model: per-step work of one
-// workgroup-wave times the number of waves that run back to back on the
-// busiest SIMD (1024 SIMDs, occupancy ignored), plus a padding penalty.
-int choose_variant(int n, int P, int64_t N) {
+// Choice used when no tuned one is cached.
+//
+// Above ten machines (and Ornstein-Uhlenbeck disturbances) the smallest team
+// variant that fits.  Measured, ms per call of 200 steps, team against the best
+// of the other forms: FP64 11 machines 0.76 / 1.0 (300 samples) and 2.0 / 3.5
+// (2e4), 24 machines 0.96 / 5.3 (3000), 50 machines 2.2 / 41.6 (3000); at 10
+// machines the lanes form stays ahead (0.52 / 0.76 and 1.41 / 1.85).  In FP32 a
+// lane's row of Y still fits its registers up to 24 machines, and the lanes form
+// wins while its waves are few: 12 and 16 machines 0.49 / 0.61 at 300, 0.63 / 0.76
+// at 8000, 1.38 / 1.12 at 2e4 samples; 24 machines 0.62 / 0.71 at 300, 0.76 / 0.72
+// at 3000; 32 machines 0.86 / 0.81 at 300.  Hence the sample counts below.
+//
+// Otherwise a lanes-per-trajectory variant with one machine per lane (L >= NG
+// >= n) and at most as many padding machines as real ones comes first: the fewest
+// padding machines, then four waves per workgroup (fewer groups to merge; at 1e4
+// samples of 10 machines 2.55 ms per 1000 FP64 steps against 2.58 and 2.85 with
+// two and one), or two while an FP64 run has fewer waves than half the chip's 1024
+// SIMDs (1000 samples 1.54 / 1.73 ms, 4000 samples 2.14 / 2.02).  Otherwise a cost
+// model: per-step work of one workgroup-wave times the number of waves that run
+// back to back on the busiest SIMD (1024 SIMDs, occupancy ignored), plus a
+// padding penalty.
+int choose_variant(int n, int P, int64_t N, int precision, bool general) {
   int best = -1;
+  const bool f64 = precision == FMC_F64;
+  const bool few = !f64 && ((n <= 16 && N <= 12000) || (n <= 24 && N <= 1500));
+  if (n > 10 && !general && !few)
+    for (const auto& v : lane_table())
+      if (v.team && v.NG >= n && v.PM >= P) return v.id;  // ascending NG
   for (const auto& v : lane_table()) {
+    if (v.team) continue;
     if (v.L == 1 || v.G() != 1 || v.NG < n || v.NG > 2 * n || v.PM < std::max(P, 1)) continue;
     if (best < 0) {
       best = v.id;
       continue;
     }
     const VariantInfo& b = lane_table()[best];
+    const int wpb = f64 && N * v.L < 64 * 512 ? 2 : 4;
     const bool better = v.NG < b.NG || (v.NG == b.NG && v.L < b.L) ||
-                        (v.NG == b.NG && v.L == b.L && v.WPB == 4 && b.WPB != 4);
+                        (v.NG == b.NG && v.L == b.L &&
+                         std::abs(v.WPB - wpb) < std::abs(b.WPB - wpb));
     if (better) best = v.id;
   }
   if (best >= 0) return best;
   double best_cost = 0.0;
   for (const auto& v : lane_table()) {
-    if (v.NG < n || v.PM < std::max(P, 1)) continue;
+    if (v.team || v.NG < n || v.PM < std::max(P, 1)) continue;
     const double G = v.G();
     const double lane_work = G * v.NG * 4.0 + G * 40.0 + v.PM * 4.0 + (v.L > 1 ? v.NG * 2.0 : 0.0);
     const double waves = std::ceil((double)N * v.L / 64.0);
@@ -94,13 +117,13 @@ std::string tune_key(int n, int P, int64_t N, int precision) {
          std::to_string(precision);
 }
 
-int pick_variant(Context* c, int n, int P, int64_t N, int precision) {
+int pick_variant(Context* c, int n, int P, int64_t N, int precision, bool general) {
   auto it = c->tuned.find(tune_key(n, P, N, precision));
   if (it != c->tuned.end() && it->second >= 0 && it->second < n_variants()) {
     const VariantInfo& v = variant(it->second);
-    if (v.NG >= n && v.PM >= P) return it->second;
+    if (v.NG >= n && v.PM >= P && !(v.team && general)) return it->second;
   }
-  return choose_variant(n, P, N);
+  return choose_variant(n, P, N, precision, general);
 }
 
 // Tuner cache file: one {"key": ..., "variant": ...} object per line.
@@ -753,7 +776,8 @@ int fmc_autotune(fmc_context* ctx, const fmc_scenario* scen, int32_t* variant_ou
   for (int id = 0; id < n_variants(); ++id) {
     const VariantInfo& vi = variant(id);
     if (vi.NG < n || vi.PM < P) continue;
-    if (trap && (vi.L != 1 || vi.NG > kTrapMaxGen)) continue;
+    if (trap && (vi.L != 1 || vi.team || vi.NG > kTrapMaxGen)) continue;
+    if (vi.team && scen->dist->proc) continue;
     par.variant = id;
     fmc_report rep;
     fmc_outputs out{};

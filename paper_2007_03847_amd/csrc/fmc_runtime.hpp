@@ -78,9 +78,10 @@ int stage_scenario(Context* c, const fmc_system* sys, const fmc_disturbance* dis
 // under `tag` (a tag per network that may be in flight at the same time).
 int kron_on_device(Context* c, const fmc_network* net, double2* Yd, int* st_dev,
                    const char* tag = "net");
-int choose_variant(int n, int P, int64_t N);
+int choose_variant(int n, int P, int64_t N, int precision, bool general);
 std::string tune_key(int n, int P, int64_t N, int precision);
-int pick_variant(Context* c, int n, int P, int64_t N, int precision);
+// general: the scenario has general Ito processes (no team variant)
+int pick_variant(Context* c, int n, int P, int64_t N, int precision, bool general);
 // Batched variants: whether one may run (n, P, precision), and the untuned
 // choice of the served form.
 bool batch_fits(const BatchVariantInfo& b, int n, int P, int precision);

@@ -670,7 +670,7 @@ template <typename R> struct vec2;
 template <> struct vec2<double> { using type = double2; };
 template <> struct vec2<float> { using type = float2; };
 
-// Form of the network product of the group kernels.  FP64: rotated
+// Form of the network product of the group and team kernels.  FP64: rotated
 // (PackLayout), which saves the turn by E0 and the products with it.  FP32:
 // plain.  There the rounding of the coefficients is systematic over all samples,
 // and rounding Z_ik / 2H_i and Z_ki / 2H_k on their own breaks the balance

@@ -40,6 +40,18 @@
   X(32, 8, 32, 4)       \
   X(50, 8, 50, 4)
 
+// Team variants (k_team.hip): X(NG machines, NB waves per tile of 16
+// trajectories, eight machines per wave), eight processes; Ornstein-Uhlenbeck
+// disturbances only.  Their ids follow FMC_VARIANTS.  The largest takes the
+// 50 machines that the other forms take.
+#define FMC_TEAM_VARIANTS(X) \
+  X(16, 2)                   \
+  X(24, 3)                   \
+  X(32, 4)                   \
+  X(40, 5)                   \
+  X(48, 6)                   \
+  X(50, 7)
+
 // Variants of the persistent batched integrator (FP32, 4 waves per
 // workgroup): X(NG machines, PM processes, L lanes per trajectory), in three
 // size classes compiled as separate persistent kernels (the register
