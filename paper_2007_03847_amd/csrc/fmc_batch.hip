@@ -24,6 +24,7 @@ namespace fmc {
 namespace {
 
 constexpr int64_t kBatchChunk = 250;     // steps per chunk (tick)
+constexpr int kClassStreams = 4;            // a process has four hardware queues
 constexpr int64_t kBatchMaxItems = 512;  // work items per scenario
 constexpr int64_t kTuneFill = 32768;     // tuner trial samples: two 64-trajectory tiles per CU
 
@@ -174,7 +175,7 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
   if (nsc < 1 || !scen || !outs) return fail(FMC_EINVAL, "empty batch");
   HIPCHK(hipSetDevice(c->device));
   if (!c->bstream) HIPCHK(hipStreamCreateWithFlags(&c->bstream, hipStreamNonBlocking));
-  for (int k = 0; k < kBatchClasses; ++k)
+  for (int k = 0; k < kSideStreams; ++k)
     if (!c->cstream[k]) HIPCHK(hipStreamCreateWithFlags(&c->cstream[k], hipStreamNonBlocking));
   for (auto& e : c->cev)
     if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -231,8 +232,8 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
       return rc;
     }
     if (p.vid < 0 || p.vid >= n_batch_variants()) return fail(FMC_EINVAL, "no batched variant");
-    p.bv = batch_variant(p.vid);
-    if (!batch_fits(p.bv, p.n, p.P, p.par->precision))
+    p.bv = batch_variant_for(p.vid, p.n);
+    if (!batch_fits(batch_variant(p.vid), p.n, p.P, p.par->precision))
       return fail(FMC_EINVAL, "batched variant does not fit the scenario (size, or a BF16 x3 "
                               "product for an FMC_F32 scenario)");
     p.tiles = (p.N + p.bv.TB - 1) / p.bv.TB;
@@ -273,7 +274,7 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
     p.Sc = std::min<int64_t>(p.S, p.par->time_chunk > 0 ? p.par->time_chunk : kBatchChunk);
     p.ticks = (p.S + p.Sc - 1) / p.Sc;
     n_ticks = std::max(n_ticks, p.ticks);
-    p.tiles_per_item = (p.tiles + kBatchMaxItems - 1) / kBatchMaxItems;
+    p.tiles_per_item = batch_item_tiles(p.bv, p.tiles, kBatchMaxItems);
     p.n_items = (p.tiles + p.tiles_per_item - 1) / p.tiles_per_item;
     p.item0 = n_items;
     n_items += p.n_items;
@@ -342,7 +343,7 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
   void *status = nullptr, *counters = nullptr, *heads = nullptr;
   if ((rc = c->ensure("b_status", (size_t)nsc * 16, &status))) return rc;
   if ((rc = c->ensure("b_counters", (size_t)nsc * 16, &counters))) return rc;
-  if ((rc = c->ensure("b_heads", (size_t)n_ticks * 16 * 4, &heads))) return rc;
+  if ((rc = c->ensure("b_heads", (size_t)n_ticks * kBatchClasses * 4, &heads))) return rc;
   // ---- items (static) and, per tick and size class, the queue of the items
   // of the scenarios active in that tick (longest first)
   std::vector<BatchItem> items(n_items);
@@ -472,13 +473,13 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
     // per-scenario setup (reduction, operating point, packing, basis, design),
     // scenarios spread round-robin over the side streams
     {
-      bool used[kBatchClasses] = {};
-      HIPCHK(hipEventRecord(c->cev[kBatchClasses], st));
+      bool used[kSideStreams] = {};
+      HIPCHK(hipEventRecord(c->cev[kSideStreams], st));
       for (int i = 0; i < nsc; ++i) {
         Plan& p = plans[i];
-        const int x = i % kBatchClasses;
+        const int x = i % kSideStreams;
         const hipStream_t s = c->cstream[x];
-        if (!used[x]) HIPCHK(hipStreamWaitEvent(s, c->cev[kBatchClasses], 0));
+        if (!used[x]) HIPCHK(hipStreamWaitEvent(s, c->cev[kSideStreams], 0));
         used[x] = true;
         if (p.kron) {
           HIPCHK(launch_kron(p.nd, p.kwork, p.ybuf, (int*)status + 4 * i + 1, s));
@@ -490,7 +491,7 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
         if (!p.par->zeta_in)
           HIPCHK(launch_lhs(p.par->seed, (int32_t)p.M, p.N, p.par->sampler, p.strata, p.zeta, s));
       }
-      for (int x = 0; x < kBatchClasses; ++x)
+      for (int x = 0; x < kSideStreams; ++x)
         if (used[x]) {
           HIPCHK(hipEventRecord(c->cev[x], c->cstream[x]));
           HIPCHK(hipStreamWaitEvent(st, c->cev[x], 0));
@@ -501,23 +502,23 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
       HIPCHK(launch_fill_i64((int64_t*)counters + 2 * i, 0, 1, st));
       HIPCHK(launch_fill_i64((int64_t*)counters + 2 * i + 1, LLONG_MAX, 1, st));
     }
-    HIPCHK(launch_fill_i64((int64_t*)heads, 0, n_ticks * 8, st));
+    HIPCHK(launch_fill_i64((int64_t*)heads, 0, n_ticks * kBatchClasses / 2, st));
     for (int64_t k = 0; k < n_ticks; ++k) {
       // The tick's per-scenario launches of one phase (paths, merges) are
       // small: they are spread round-robin over the side streams (forked
       // from st, joined back) so that they run side by side.
       auto spread = [&](auto&& launch) -> int {
-        bool used[kBatchClasses] = {};
-        HIPCHK(hipEventRecord(c->cev[kBatchClasses], st));
+        bool used[kSideStreams] = {};
+        HIPCHK(hipEventRecord(c->cev[kSideStreams], st));
         int j = 0;
         for (auto& p : plans) {
           if (p.ticks <= k) continue;
-          const int x = j++ % kBatchClasses;
-          if (!used[x]) HIPCHK(hipStreamWaitEvent(c->cstream[x], c->cev[kBatchClasses], 0));
+          const int x = j++ % kSideStreams;
+          if (!used[x]) HIPCHK(hipStreamWaitEvent(c->cstream[x], c->cev[kSideStreams], 0));
           used[x] = true;
           HIPCHK(launch(p, c->cstream[x]));
         }
-        for (int x = 0; x < kBatchClasses; ++x)
+        for (int x = 0; x < kSideStreams; ++x)
           if (used[x]) {
             HIPCHK(hipEventRecord(c->cev[x], c->cstream[x]));
             HIPCHK(hipStreamWaitEvent(st, c->cev[x], 0));
@@ -532,31 +533,38 @@ int run_batch_impl(Context* c, int32_t nsc, const fmc_scenario* scen, fmc_output
                    : launch_kle_bf16x3(zeta, p.phi, p.C, p.P, p.K, p.N, 2 * (s1 - s0) + 1, 2 * s0, p.w, s);
       });
       if (rc) return rc;
-      // the tick's size classes: one launch each; with more than one, each on
-      // its own stream (fork after the paths, join before the merges) so that
-      // the classes share the chip instead of each running partly filled
-      int n_act = 0;
-      for (int cl = 0; cl < kBatchClasses; ++cl)
-        n_act += ord_off[k * kBatchClasses + cl + 1] > ord_off[k * kBatchClasses + cl];
-      if (n_act > 1) HIPCHK(hipEventRecord(c->cev[kBatchClasses], st));
+      // the tick's size classes: one launch each, side by side on kClassStreams of
+      // the side streams (fork after the paths, join before the merges) so that the
+      // classes share the chip instead of each running partly filled; the
+      // costliest first onto the stream with the least work
+      std::vector<std::pair<double, int>> cls;
       for (int cl = 0; cl < kBatchClasses; ++cl) {
+        double cost = 0.0;
+        for (int64_t o = ord_off[k * kBatchClasses + cl]; o < ord_off[k * kBatchClasses + cl + 1]; ++o)
+          cost += icost[order_flat[o]];
+        if (cost > 0.0) cls.push_back({cost, cl});
+      }
+      std::stable_sort(cls.begin(), cls.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+      const int n_str = std::min((int)cls.size(), kClassStreams);
+      double load[kClassStreams] = {};
+      if (n_str > 1) {
+        HIPCHK(hipEventRecord(c->cev[kSideStreams], st));
+        for (int x = 0; x < n_str; ++x) HIPCHK(hipStreamWaitEvent(c->cstream[x], c->cev[kSideStreams], 0));
+      }
+      for (const auto& [cost, cl] : cls) {
         const int64_t o0 = ord_off[k * kBatchClasses + cl], o1 = ord_off[k * kBatchClasses + cl + 1];
-        if (o1 == o0) continue;
         const int grid = (int)std::min<int64_t>(o1 - o0, (int64_t)bpc[cl] * prop.multiProcessorCount);
         BatchArgs b{args_d + (size_t)k * nsc, items_d, order_d + o0, (int32_t)(o1 - o0),
-                    (int32_t*)heads + k * 16 + 2 * cl};
-        if (n_act > 1) {
-          HIPCHK(hipStreamWaitEvent(c->cstream[cl], c->cev[kBatchClasses], 0));
-          HIPCHK(launch_persistent(cl, b, grid, c->cstream[cl]));
-          HIPCHK(hipEventRecord(c->cev[cl], c->cstream[cl]));
-        } else {
-          HIPCHK(launch_persistent(cl, b, grid, st));
-        }
+                    (int32_t*)heads + k * kBatchClasses + cl};
+        const int x = (int)(std::min_element(load, load + n_str) - load);
+        load[x] += cost;
+        HIPCHK(launch_persistent(cl, b, grid, n_str > 1 ? c->cstream[x] : st));
       }
-      if (n_act > 1)
-        for (int cl = 0; cl < kBatchClasses; ++cl)
-          if (ord_off[k * kBatchClasses + cl + 1] > ord_off[k * kBatchClasses + cl])
-            HIPCHK(hipStreamWaitEvent(st, c->cev[cl], 0));
+      if (n_str > 1)
+        for (int x = 0; x < n_str; ++x) {
+          HIPCHK(hipEventRecord(c->cev[x], c->cstream[x]));
+          HIPCHK(hipStreamWaitEvent(st, c->cev[x], 0));
+        }
       // rows completed by this tick: s0+1..s1 (and row 0 in the first chunk)
       rc = spread([&](Plan& p, hipStream_t s) {
         const int64_t s0 = k * p.Sc, s1 = std::min<int64_t>(p.S, s0 + p.Sc);

@@ -233,10 +233,10 @@ hipError_t launch_integrate_gen_f64(int variant_id, const IntegArgs<double>& a, 
                                     hipStream_t st);
 hipError_t launch_integrate_gen_f32(int variant_id, const IntegArgs<float>& a, int64_t n_groups,
                                     hipStream_t st);
-template <typename R>
-hipError_t launch_team(const VariantInfo& v, const IntegArgs<R>& a, int64_t n_groups, hipStream_t st);
 hipError_t launch_integrate_f32(int variant_id, const IntegArgs<float>& a, int64_t n_groups,
                                 hipStream_t st);
+template <typename R>
+hipError_t launch_team(const VariantInfo& v, const IntegArgs<R>& a, int64_t n_groups, hipStream_t st);
 // Implicit trapezoid (FP64, classical machines) on the shape of a
 // one-trajectory-per-lane variant with at most kTrapMaxGen machines.
 constexpr int kTrapMaxGen = 16;
@@ -257,32 +257,61 @@ struct BatchArgs {
   int32_t n_items;
   int32_t* head;                 // queue counter, zero before the launch
 };
-// prod: how a variant forms the network current: 0 lanes and FMAs (classes
-// 0-2), 1 FP32 matrix cores, 2 BF16 x3 matrix cores (classes 3-6, one per
-// count of 16-machine blocks: 1, 2, 3, 4).
+// prod: how a variant forms the network product: 0 lanes and FMAs (classes
+// 0-2), 1 FP32 matrix cores (teams, classes 3-9: two to eight waves of eight
+// machines each, by the scenario's machines), 2 BF16 x3 matrix cores (classes
+// 10-13, one per count of 16-machine blocks).
 struct BatchVariantInfo {
   int id, NG, PM, L, TB, cls, prod;
+  int team_waves() const { return cls - 1; }  // prod 1
 };
-constexpr int kBatchClasses = 7;
+// Tiles per workgroup of a team of nb waves in the batched and served forms: a CU's
+// four SIMDs take a workgroup's waves rounded up to a multiple of four, so the
+// teams of five and six run in pairs (k_team.hpp).
+constexpr int batch_teams(int nb) { return nb == 5 || nb == 6 ? 2 : 1; }
+constexpr int kBatchClasses = 14;
+constexpr int kSideStreams = 7;   // streams a batch's per-scenario launches are spread over
 // Correlation reduction of the design (FMC_LHS_DECOR): the Cholesky factor is
 // computed by one workgroup with the diagonal in LDS, and ranks are int32.
 constexpr int kDecorMaxM = 1024;
 constexpr int64_t kDecorMaxN = 2147483647;
+// Tiles of a work item when a scenario is cut into at most max_items.  A team's
+// tiles are a half or a quarter of the other matrix-core variants' (16 or 32
+// trajectories): their items are powers of two of them.
+inline int64_t batch_item_tiles(const BatchVariantInfo& b, int64_t tiles, int64_t max_items) {
+  const int64_t k = (tiles + max_items - 1) / max_items;
+  if (b.prod != 1) return k;
+  int64_t q = 1;
+  while (q < k) q *= 2;
+  return q;
+}
 int n_batch_variants();
 BatchVariantInfo batch_variant(int i);
+// The variant as it runs a scenario of n machines: a team's waves, machine slots
+// and class follow n.
+inline BatchVariantInfo batch_variant_for(int i, int n) {
+  BatchVariantInfo b = batch_variant(i);
+  if (b.prod == 1) {
+    const int nb = n <= 16 ? 2 : (n + 7) / 8;
+    b.NG = 8 * nb;
+    b.cls = nb + 1;
+    b.TB = 16 * batch_teams(nb);
+  }
+  return b;
+}
 int persistent_blocks_per_cu(int cls);
 hipError_t launch_persistent(int cls, const BatchArgs& b, int grid, hipStream_t st);
 hipError_t launch_fill_i64(int64_t* p, int64_t v, int64_t n, hipStream_t st);
 
-// Matrix-core classical variants (classes 3-6): up to kMcMaxGen machines and
+// BF16 x3 matrix-core variants (classes 10-13): up to kMcMaxGen machines and
 // kMcMaxProc processes, 64 trajectories per workgroup tile.
 constexpr int kMcMaxGen = 64;
 constexpr int kMcMaxProc = 8;
 // Coefficient block of a matrix-core variant (n_pad machines): machine-major
 // constants [n_pad][8] = C0 S0 I0R I0I | RES DMP INV2H 0 (two 16-byte groups),
 // the process block theta, sigma, xi0, machine index [4][kMcMaxProc], then Y
-// in the A-operand order of the variant's product (the FP32 pairs of
-// k_pack_fd_y or the BF16 hi/lo vectors of k_pack_fd_y16).
+// in the A-operand order of the product (the BF16 hi/lo vectors of
+// k_pack_fd_y16).
 struct McPack {
   int n_pad;
   static constexpr int kStride = 8;
@@ -292,25 +321,31 @@ struct McPack {
   __host__ __device__ constexpr int proc() const { return n_pad * kStride; }
   __host__ __device__ constexpr int consts() const { return n_pad * kStride + 4 * kMcMaxProc; }
   __host__ __device__ constexpr int frag() const { return consts(); }  // 16-byte aligned
-  __host__ __device__ constexpr int size(bool bf) const {
-    return frag() + (bf ? (n_pad / 16) * (n_padk() / 32) * 64 * 16 : (n_pad / 16) * (n_pad / 4) * 64 * 2);
+  __host__ __device__ constexpr int size() const {
+    return frag() + (n_pad / 16) * (n_padk() / 32) * 64 * 16;
   }
 };
-hipError_t launch_pack_mc(const double* canon, int n, int P, const int32_t* gen, int n_pad, bool bf,
+hipError_t launch_pack_mc(const double* canon, int n, int P, const int32_t* gen, int n_pad,
                           float* coef, hipStream_t st);
+// nb: waves of the team (2 to 8)
+int persistent_team_blocks_per_cu(int nb);
+hipError_t launch_persistent_team(int nb, const BatchArgs& b, int grid, hipStream_t st);
 // nb: 16-machine blocks of the class (1 to 4)
 int persistent_mc_blocks_per_cu(int nb);
 hipError_t launch_persistent_mc(int nb, const BatchArgs& b, int grid, hipStream_t st);
-// State buffer of a batched variant (floats) for `tiles` trajectory tiles:
-// 2 G + PQ rows (G = ceil(NG / L), PQ = ceil(PM / L)) of 256 lanes per tile;
-// the lane classes address it [row][lanes], classes 3-6 [tile][wave][row][64].
+// State buffer of a batched variant (floats) for `tiles` trajectory tiles: the
+// lane classes and the BF16 x3 classes take 2 G + PQ rows (G = ceil(NG / L), PQ =
+// ceil(PM / L)) and the offset's of 256 lanes per tile, addressed [row][lanes] by
+// the former and [tile][wave][row][64] by the latter; a team's tile takes
+// team_state values.
 inline size_t batch_state_floats(const BatchVariantInfo& b, int64_t tiles) {
+  if (b.prod == 1) return (size_t)(256 * b.team_waves() + 160) * (size_t)(tiles * b.TB / 16);
   const int G = (b.NG + b.L - 1) / b.L, PQ = (b.PM + b.L - 1) / b.L;
   return (size_t)(2 * G + PQ + kOffsetRows) * (size_t)tiles * 64 * 4;
 }
 // Coefficient block size (floats) and packing of a batched variant.
 inline size_t batch_coef_floats(const BatchVariantInfo& b) {
-  return b.prod != 0 ? (size_t)McPack{b.NG}.size(b.prod == 2) : (size_t)PackLayout{b.NG, b.PM}.size();
+  return b.prod == 2 ? (size_t)McPack{b.NG}.size() : (size_t)PackLayout{b.NG, b.PM}.size();
 }
 hipError_t launch_pack_batch(const BatchVariantInfo& b, const double* canon, int n, int P,
                              const int32_t* gen, float* coef, hipStream_t st);

@@ -39,9 +39,13 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 
-constexpr size_t kTickBytes = size_t(16) << 20;  // per-tick upload region (args, items, orders)
+constexpr size_t kTickBytes = size_t(32) << 20;  // per-tick upload region (args, items, orders)
 constexpr int64_t kMaxItems = 1024;             // work items per request
 constexpr int kMaxActive = 256;                 // requests admitted at once
+// A process has four hardware queues; launches on more streams than that wait for
+// each other in one of them (three size classes on a stream each of fifteen: two of
+// them one after the other, 1.65 ms per tick of 100 steps; on four lanes 1.35 ms).
+constexpr int kLanes = 4;
 constexpr int64_t kDefaultChunk = 200;          // steps per tick
 constexpr int64_t kDefaultChunkFd = 12;         // steps per tick of a flux-decay request
 constexpr size_t kAlign = serve::kAlign;
@@ -170,15 +174,26 @@ int plan_request(Request& r, const fmc_system* s, const fmc_disturbance* d, cons
   if (vid < 0) vid = default_batch_variant(r.n, r.P, p->precision);
   if (vid < 0 || vid >= n_batch_variants()) return fail(FMC_EINVAL, "no batched variant fits the request");
   r.vid = vid;
-  r.bv = batch_variant(vid);
-  if (!batch_fits(r.bv, r.n, r.P, p->precision))
+  r.bv = batch_variant_for(vid, r.n);
+  if (!batch_fits(batch_variant(vid), r.n, r.P, p->precision))
     return fail(FMC_EINVAL, "variant does not fit the request (size, or a BF16 x3 product for "
                             "an FMC_F32 request)");
   r.Sc = std::min<int64_t>(S, p->time_chunk > 0 ? p->time_chunk : kDefaultChunk);
+  // A team's tiles are 16 trajectories; items of 64 leave a request of a few
+  // thousand samples on a few dozen workgroups.  Items of 32 hold twice the rows,
+  // so they come with half the chunk: the request's device size does not grow
+  // (the halved path window outweighs the extra row 0 of a chunk from 40 steps).
+  // A chunk the caller sets is kept, with items of 64.
+  int64_t min_tiles = 1;
+  if (r.bv.prod == 1) {
+    const bool half = p->time_chunk <= 0 && r.Sc >= 40;
+    if (half) r.Sc = (r.Sc + 1) / 2;
+    min_tiles = (half ? 32 : 64) / r.bv.TB;
+  }
   r.tiles = (r.N + r.bv.TB - 1) / r.bv.TB;
   r.cost_tile = (double)r.S * r.bv.TB * (8.0 * r.bv.NG * r.bv.NG + 45.0 * r.bv.NG + 4.0 * r.P);
   // fine items (up to kMaxItems): a request alone still spreads over the chip
-  r.tiles_per_item = (r.tiles + kMaxItems - 1) / kMaxItems;
+  r.tiles_per_item = std::max(min_tiles, batch_item_tiles(r.bv, r.tiles, kMaxItems));
   r.n_items = (r.tiles + r.tiles_per_item - 1) / r.tiles_per_item;
   return FMC_OK;
 }
@@ -244,10 +259,10 @@ struct ServeState {
   char* arena_base = nullptr;
   unsigned char* tick_dev = nullptr;  // upload region of a tick (outside the arena)
   hipStream_t st = nullptr;
-  // per tick, the size classes and the flux-decay integrators run on their
-  // own streams (forked from st after the paths, joined before the merges)
-  hipStream_t lst[kBatchClasses + 1] = {};
-  hipEvent_t lev[kBatchClasses + 2] = {};  // [k]: lane k done, [kBatchClasses + 1]: fork
+  // lanes of a tick: st and lst (forked from st, joined back): the paths, then
+  // the size classes and the flux-decay integrators run side by side on them
+  hipStream_t lst[kLanes - 1] = {};
+  hipEvent_t lev[kLanes] = {};  // [0]: fork, [k]: lane k done
   unsigned char* pin = nullptr;  // page-locked staging of a tick
   size_t pin_cap = 0;
   int n_cu = 0, bpc[kBatchClasses] = {};
@@ -383,14 +398,32 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
   std::vector<double> icost;
   icost.reserve(n_items);
   std::vector<std::pair<FdArgs, int64_t>> fd_launch;
+  auto lane = [&](int k) { return k == 0 ? st : ss->lst[k - 1]; };
+  auto fork = [&](int n) -> hipError_t {  // lanes 1 .. n - 1 after what st has
+    if (n < 2) return hipSuccess;
+    hipError_t e = hipEventRecord(ss->lev[0], st);
+    for (int k = 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(lane(k), ss->lev[0], 0);
+    return e;
+  };
+  auto join = [&](int n) -> hipError_t {  // st after lanes 1 .. n - 1
+    hipError_t e = hipSuccess;
+    for (int k = 1; k < n && e == hipSuccess; ++k) {
+      e = hipEventRecord(ss->lev[k], lane(k));
+      if (e == hipSuccess) e = hipStreamWaitEvent(st, ss->lev[k], 0);
+    }
+    return e;
+  };
+  const int path_lanes = std::min(na, kLanes);
+  SCHK(fork(path_lanes));
   for (int i = 0; i < na; ++i) {
     Request& r = *act[i];
     const int64_t s0 = r.s_next, s1 = std::min<int64_t>(r.S, s0 + r.Sc);
     const int64_t cols = 2 * (s1 - s0) + 1;
+    const hipStream_t ks = lane(i % path_lanes);
     if (r.par.precision == FMC_F32)
-      SCHK(launch_kle_f64_to_f32(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, st));
+      SCHK(launch_kle_f64_to_f32(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, ks));
     else
-      SCHK(launch_kle_bf16x3(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, st));
+      SCHK(launch_kle_bf16x3(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, ks));
     if (r.fd) {
       FdArgs f{};
       f.coef = r.coef;
@@ -465,6 +498,7 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
     r.s_next = s1;
     if (s1 == r.S) finishing.push_back(act[i]);
   }
+  SCHK(join(path_lanes));
   for (auto& o : order)
     std::stable_sort(o.begin(), o.end(), [&](int32_t x, int32_t y) { return icost[x] > icost[y]; });
   std::vector<int32_t> flat;
@@ -492,37 +526,33 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
   SCHK(hipMemcpyAsync(dp, hp, o, hipMemcpyHostToDevice, st));
   pin_off += o;
   int32_t* heads = (int32_t*)ss->tick_dev;
-  SCHK(launch_fill_i64((int64_t*)heads, 0, 8, st));
-  // lanes of the tick: the size classes with items, then the flux-decay
-  // integrators (one after another on the last lane)
-  bool on[kBatchClasses + 1];
-  int n_on = 0;
-  for (int k = 0; k < kBatchClasses; ++k) n_on += on[k] = off[k + 1] > off[k];
-  n_on += on[kBatchClasses] = !fd_launch.empty();
-  const bool fork = n_on > 1;
-  if (fork) SCHK(hipEventRecord(ss->lev[kBatchClasses + 1], st));
-  auto lane = [&](int k) {
-    if (!fork) return st;
-    (void)hipStreamWaitEvent(ss->lst[k], ss->lev[kBatchClasses + 1], 0);
-    return ss->lst[k];
-  };
+  SCHK(launch_fill_i64((int64_t*)heads, 0, kBatchClasses / 2, st));
+  // the size classes with items, the costliest first onto the lane with the least
+  // work; the flux-decay integrators, one after another, count as a class
+  std::vector<std::pair<double, int>> cls;
   for (int k = 0; k < kBatchClasses; ++k) {
-    if (!on[k]) continue;
+    double cost = 0.0;
+    for (int32_t q : order[k]) cost += icost[q];
+    if (off[k + 1] > off[k]) cls.push_back({cost, k});
+  }
+  if (!fd_launch.empty()) cls.push_back({HUGE_VAL, kBatchClasses});
+  std::stable_sort(cls.begin(), cls.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  const int class_lanes = std::min((int)cls.size(), kLanes);
+  double load[kLanes] = {};
+  SCHK(fork(class_lanes));
+  for (const auto& [cost, k] : cls) {
+    const int x = (int)(std::min_element(load, load + class_lanes) - load);
+    load[x] += cost;
+    if (k == kBatchClasses) {
+      for (auto& f : fd_launch) SCHK(launch_rk4_fd(f.first, f.second, lane(x)));
+      continue;
+    }
     const int64_t nk = off[k + 1] - off[k];
     const int grid = (int)std::min<int64_t>(nk, (int64_t)ss->bpc[k] * ss->n_cu);
-    BatchArgs b{args_d, items_d, order_d + off[k], (int32_t)nk, heads + 2 * k};
-    SCHK(launch_persistent(k, b, grid, lane(k)));
+    BatchArgs b{args_d, items_d, order_d + off[k], (int32_t)nk, heads + k};
+    SCHK(launch_persistent(k, b, grid, lane(x)));
   }
-  if (on[kBatchClasses]) {
-    const hipStream_t ls = lane(kBatchClasses);
-    for (auto& f : fd_launch) SCHK(launch_rk4_fd(f.first, f.second, ls));
-  }
-  if (fork)
-    for (int k = 0; k <= kBatchClasses; ++k)
-      if (on[k]) {
-        SCHK(hipEventRecord(ss->lev[k], ss->lst[k]));
-        SCHK(hipStreamWaitEvent(st, ss->lev[k], 0));
-      }
+  SCHK(join(class_lanes));
   // rows completed by this tick: s0+1..s1 (and row 0 in a request's first chunk)
   for (int i = 0; i < na; ++i) {
     Request& r = *act[i];

@@ -65,17 +65,19 @@ __device__ __forceinline__ void batch_tiles(const IntegArgs<float>& a, const Bat
 #define FMC_COUNT(NG, PM, L) ++id;
 
 template <int C>
-__global__ void __launch_bounds__(64 * kBatchWPB) k_rk4_persistent(BatchArgs b) {
+__global__ void __launch_bounds__(64 * kBatchWPB)
+    __attribute__((amdgpu_waves_per_eu(C <= 1 ? 2 : 1))) k_rk4_persistent(BatchArgs b) {
+  // two waves per SIMD where that costs no spills or a few (class 1: 31)
   __shared__ __attribute__((aligned(16))) unsigned char lds[BatchClass<C>::lds()];
   __shared__ int s_item;
   for (;;) {
     __syncthreads();  // everyone has read the previous s_item
     if (threadIdx.x == 0) s_item = atomicAdd(b.head, 1);
     __syncthreads();
-    const int q = s_item;
+    const int q = __builtin_amdgcn_readfirstlane(s_item);
     if (q >= b.n_items) break;  // uniform over the workgroup
-    const BatchItem it = b.items[b.order[q]];
-    const IntegArgs<float> a = b.scen[it.scen];
+    const BatchItem it = load_uniform(b.items + b.order[q]);
+    const IntegArgs<float> a = load_uniform(b.scen + it.scen);
     int id = 0;
     if constexpr (C == 0) {
       FMC_BATCH_CLASS0(FMC_DISPATCH)
@@ -113,10 +115,12 @@ BatchVariantInfo batch_variant(int i) {
   cls = 2;
   FMC_BATCH_CLASS2(FMC_X)
 #undef FMC_X
-  // classes 3-6 (NB = 1 to 4): 16 NB machines, kMcMaxProc processes, 4 lanes
-  // per trajectory in the state layout, 64-trajectory tiles
-#define FMC_X(NB, BF)                                                                  \
-  if (i == id) return BatchVariantInfo{id, 16 * NB, kMcMaxProc, 4, 64, 2 + NB, 1 + BF}; \
+  // matrix cores: up to 16 NB machines, kMcMaxProc processes; FP32 products on
+  // teams (tiles of 16 trajectories, class by the scenario: batch_variant_for),
+  // BF16 x3 products with 4 lanes per trajectory and tiles of 64
+#define FMC_X(NB, BF)                                                                       \
+  if (i == id)                                                                              \
+    return BatchVariantInfo{id, 16 * NB, kMcMaxProc, 4, BF ? 64 : 16, BF ? 9 + NB : 3, 1 + BF}; \
   ++id;
   FMC_BATCH_MFMA(FMC_X)
 #undef FMC_X
@@ -124,7 +128,8 @@ BatchVariantInfo batch_variant(int i) {
 }
 
 hipError_t launch_persistent(int cls, const BatchArgs& b, int grid, hipStream_t st) {
-  if (cls >= 3) return launch_persistent_mc(cls - 2, b, grid, st);
+  if (cls >= 10) return launch_persistent_mc(cls - 9, b, grid, st);
+  if (cls >= 3) return launch_persistent_team(cls - 1, b, grid, st);
   if (cls == 0)
     hipLaunchKernelGGL(k_rk4_persistent<0>, dim3((unsigned)grid), dim3(64 * kBatchWPB), 0, st, b);
   else if (cls == 1)
@@ -135,7 +140,8 @@ hipError_t launch_persistent(int cls, const BatchArgs& b, int grid, hipStream_t 
 }
 
 int persistent_blocks_per_cu(int cls) {
-  if (cls >= 3) return persistent_mc_blocks_per_cu(cls - 2);
+  if (cls >= 10) return persistent_mc_blocks_per_cu(cls - 9);
+  if (cls >= 3) return persistent_team_blocks_per_cu(cls - 1);
   int nb = 0;
   hipError_t e;
   if (cls == 0)

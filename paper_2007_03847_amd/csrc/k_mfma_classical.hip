@@ -1,4 +1,4 @@
-// k_mfma_classical.hip -- classes 3-6 of the persistent batched integrator:
+// k_mfma_classical.hip -- classes 10-13 of the persistent batched integrator:
 // classical machines with the network current on the matrix cores (the
 // device code is in k_mfma_classical.hpp), and the packing of its
 // coefficient block.
@@ -39,19 +39,18 @@ __global__ void __launch_bounds__(256) k_pack_mc(const double* __restrict__ cn, 
 }
 
 hipError_t launch_pack_mc(const double* canon, int n, int P, const int32_t* gen, int n_pad,
-                          bool bf, float* coef, hipStream_t st) {
+                          float* coef, hipStream_t st) {
   const McPack K{n_pad};
   hipLaunchKernelGGL(k_pack_mc, dim3((unsigned)((K.consts() + 255) / 256)), dim3(256), 0, st,
                      canon, n, P, gen, n_pad, coef);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return bf ? launch_pack_fd_y16(canon, n, n_pad, K.n_padk(), coef + K.frag(), st)
-            : launch_pack_fd_y(canon, n, n_pad, reinterpret_cast<float2*>(coef + K.frag()), st);
+  return launch_pack_fd_y16(canon, n, n_pad, K.n_padk(), coef + K.frag(), st);
 }
 
 hipError_t launch_pack_batch(const BatchVariantInfo& b, const double* canon, int n, int P,
                              const int32_t* gen, float* coef, hipStream_t st) {
-  if (b.prod != 0) return launch_pack_mc(canon, n, P, gen, b.NG, b.prod == 2, coef, st);
+  if (b.prod == 2) return launch_pack_mc(canon, n, P, gen, b.NG, coef, st);
   return launch_pack<float>(canon, n, P, gen, gen, false, b.NG, b.PM, coef, st);
 }
 
@@ -61,10 +60,10 @@ hipError_t launch_pack_batch(const BatchVariantInfo& b, const double* canon, int
 // (ranges of 64-trajectory tiles of one scenario) until the queue is empty,
 // as the lane classes do.
 #define FMC_MC_DISPATCH(NBV, BF)                                                    \
-  if constexpr (NBV == NB)                                                          \
+  if constexpr (BF && NBV == NB)                                                    \
     if (it.variant == id)                                                           \
       for (int64_t t = it.tile0; t < it.tile1; ++t)                                 \
-        mc_tile<BF != 0, NBV>(a, t, S, GroupStats{rows, (t - it.tile0) * mc::kTile}); \
+        mc_tile<NBV>(a, t, S, GroupStats{rows, (t - it.tile0) * mc::kTile});        \
   ++id;
 
 // NB = 1 to 3 are held to 256 registers (two waves per SIMD; for NB = 3 at
@@ -79,10 +78,10 @@ __global__ void __launch_bounds__(64 * mc::kWaves)
     __syncthreads();  // everyone has read the previous s_item
     if (threadIdx.x == 0) s_item = atomicAdd(b.head, 1);
     __syncthreads();
-    const int q = s_item;
+    const int q = __builtin_amdgcn_readfirstlane(s_item);
     if (q >= b.n_items) break;  // uniform over the workgroup
-    const BatchItem it = b.items[b.order[q]];
-    const IntegArgs<float> a = b.scen[it.scen];
+    const BatchItem it = load_uniform(b.items + b.order[q]);
+    const IntegArgs<float> a = load_uniform(b.scen + it.scen);
     // with a state buffer the rows hold the chunk's steps s_begin..s_end
     double2* rows = a.state ? it.rows - a.s_begin * a.V : it.rows;
     int id = batch_n_lane_variants();

@@ -1,13 +1,13 @@
 // k_mfma_classical.hpp -- classical machines with the network current on the
-// matrix cores (the batched and served forms' size classes for larger systems).
+// matrix cores in three BF16 products (variants of the batched and served forms
+// that run when asked for).
 //
 // Same deviation form as the lane-per-machine integrators: per RK4 stage
 // dE~ = E~0 (e^{j dd} - 1), dPe = Re(dE~ conj I0) + Re(E~ conj dI) with
 // dI = Y dE~, and the swing equations.  Here a wave owns a tile of 16
 // trajectories and computes dI for all of them as the real product
-// [Re dI; Im dI] = [Yr -Yi; Yi Yr][Re dE~; Im dE~] on v_mfma_f32_16x16x4f32
-// (or, for BF16 x3 scenarios, three BF16 products per real product on
-// v_mfma_f32_16x16x32_bf16), with dE~ in the wave's own LDS tile and Y read
+// [Re dI; Im dI] = [Yr -Yi; Yi Yr][Re dE~; Im dE~], three BF16 products per real
+// product on v_mfma_f32_16x16x32_bf16, with dE~ in the wave's own LDS tile and Y read
 // in A-operand order from the scenario's coefficient block (L2).  The
 // accumulator layout (lane l holds rows 4(l/16)+r of column l%16) makes lane l
 // the owner of machines 16b + 4(l/16) + r of trajectory l%16, for blocks
@@ -35,10 +35,9 @@ constexpr int kTile = kT * kWaves;
 constexpr int kNP = kMcMaxGen;    // largest n_pad
 constexpr int kVM = 2 * kNP + kMcMaxProc;
 
-// Static LDS of the class: constants, per-wave dE~ tiles (the larger of the
-// FP32 and BF16 forms), two buffers of per-wave statistics, per-trajectory
-// flags.
-constexpr int kBtileFloats = (2 * kNP * kT > 16 * (2 * kNP + 8)) ? 2 * kNP * kT : 16 * (2 * kNP + 8);
+// Static LDS of the class: constants, per-wave dE~ tiles, two buffers of
+// per-wave statistics, per-trajectory flags.
+constexpr int kBtileFloats = 16 * (2 * kNP + 8);
 struct Lds {
   float cst[McPack::kMaxConsts];
   float btile[kWaves][kBtileFloats];
@@ -86,15 +85,17 @@ __device__ __forceinline__ double row16_sum(double v) {
 // over the steps [s_begin, s_end) of a, with the machines padded to 16 NB.
 // st.rows is addressed by global step; st.prev trajectories of the work item
 // are already merged into it.
-template <bool BF, int NB>
+template <int NB>
 __device__ __forceinline__ void mc_tile(const IntegArgs<float>& a, int64_t tile, mc::Lds& S,
                                         GroupStats st) {
   using namespace mc;
-  constexpr int n_pad = 16 * NB, KH = n_pad / 4, kQ = 4 * NB;
+  constexpr int n_pad = 16 * NB, kQ = 4 * NB;
   constexpr int n_padk = 32 * ((n_pad + 31) / 32), KS16 = n_padk / 32, BS = 2 * n_padk + 8;
   constexpr McPack K{n_pad};
   const int n = a.n, P = a.P, V = a.V;
-  const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, g = l >> 4, t = l & 15;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // opaque: see group_run
+  const int wv = tid >> 6, l = tid & 63, g = l >> 4, t = l & 15;
   const int64_t N = a.N;
   const int64_t traj = tile * kTile + wv * kT + t;
   const bool valid = traj < N;
@@ -243,13 +244,10 @@ __device__ __forceinline__ void mc_tile(const IntegArgs<float>& a, int64_t tile,
   float* B = S.btile[wv];
   __bf16* bh = reinterpret_cast<__bf16*>(B);
   __bf16* bl = bh + 16 * BS;
-  const float* Bf = B + g * kT + t;
   const int bfo = t * BS + 8 * g;
-  if constexpr (BF) {
-    // rows n_pad .. n_padk of the tile are never written: zero them
-    for (int q = l; q < 16 * BS; q += 64) B[q] = 0.0f;
-    wave_lds_sync();
-  }
+  // rows n_pad .. n_padk of the tile are never written: zero them
+  for (int q = l; q < 16 * BS; q += 64) B[q] = 0.0f;
+  wave_lds_sync();
 
   const float dt = a.dt, h2 = 0.5f * a.dt, dt6 = a.dt / 6.0f, wb = a.wb;
   const float inv_n = 1.0f / (float)n;
@@ -297,17 +295,12 @@ __device__ __forceinline__ void mc_tile(const IntegArgs<float>& a, int64_t tile,
         const float sdd = 2.0f * sh * ch, omc = 2.0f * sh * sh;
         dEr[q] = -(c.x * omc + c.y * sdd);  // zero for padding machines (E~0 = 0)
         dEi[q] = c.x * sdd - c.y * omc;
-        if constexpr (BF) {
-          const __bf16 rh = (__bf16)dEr[q], ih = (__bf16)dEi[q];
-          const int o = t * BS + m;
-          bh[o] = rh;
-          bl[o] = (__bf16)(dEr[q] - (float)rh);
-          bh[o + n_padk] = ih;
-          bl[o + n_padk] = (__bf16)(dEi[q] - (float)ih);
-        } else {
-          B[m * kT + t] = dEr[q];
-          B[(n_pad + m) * kT + t] = dEi[q];
-        }
+        const __bf16 rh = (__bf16)dEr[q], ih = (__bf16)dEi[q];
+        const int o = t * BS + m;
+        bh[o] = rh;
+        bl[o] = (__bf16)(dEr[q] - (float)rh);
+        bh[o + n_padk] = ih;
+        bl[o + n_padk] = (__bf16)(dEi[q] - (float)ih);
       }
       wave_lds_sync();
       // dI = Y dE~ for my machine blocks.  With one block the lane's Y
@@ -317,55 +310,39 @@ __device__ __forceinline__ void mc_tile(const IntegArgs<float>& a, int64_t tile,
       // (spilled) registers.
       const float* cf = a.coef;
       if constexpr (NB > 1) asm volatile("" : "+v"(cf));
-      const float2* ap = reinterpret_cast<const float2*>(cf + K.frag()) + l;
       const u32x4* aq = reinterpret_cast<const u32x4*>(cf + K.frag()) + (int64_t)l * 4;
       f32x4 ar[NB], ai[NB];
 #pragma unroll
       for (int b = 0; b < NB; ++b) { ar[b] = f32x4{0.f, 0.f, 0.f, 0.f}; ai[b] = ar[b]; }
-      if constexpr (BF) {
-        const u32x4 sgn = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+      const u32x4 sgn = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
 #pragma unroll
-        for (int k = 0; k < KS16; ++k) {
-          const bf8_t rh_ = *reinterpret_cast<const bf8_t*>(bh + bfo + 32 * k);
-          const bf8_t rl_ = *reinterpret_cast<const bf8_t*>(bl + bfo + 32 * k);
-          const bf8_t ih_ = *reinterpret_cast<const bf8_t*>(bh + bfo + n_padk + 32 * k);
-          const bf8_t il_ = *reinterpret_cast<const bf8_t*>(bl + bfo + n_padk + 32 * k);
+      for (int k = 0; k < KS16; ++k) {
+        const bf8_t rh_ = *reinterpret_cast<const bf8_t*>(bh + bfo + 32 * k);
+        const bf8_t rl_ = *reinterpret_cast<const bf8_t*>(bl + bfo + 32 * k);
+        const bf8_t ih_ = *reinterpret_cast<const bf8_t*>(bh + bfo + n_padk + 32 * k);
+        const bf8_t il_ = *reinterpret_cast<const bf8_t*>(bl + bfo + n_padk + 32 * k);
 #pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const u32x4* av = aq + (int64_t)(b * KS16 + k) * 64 * 4;
-            const u32x4 u0 = av[0], u1 = av[1], u2 = av[2], u3 = av[3];
-            const bf8_t yrh = __builtin_bit_cast(bf8_t, u0), yrl = __builtin_bit_cast(bf8_t, u1);
-            const bf8_t yih = __builtin_bit_cast(bf8_t, u2), yil = __builtin_bit_cast(bf8_t, u3);
-            const bf8_t nih = __builtin_bit_cast(bf8_t, u2 ^ sgn);
-            const bf8_t nil = __builtin_bit_cast(bf8_t, u3 ^ sgn);
-            // Re dI = Yr Re dE - Yi Im dE, Im dI = Yi Re dE + Yr Im dE, each
-            // product as hi*lo + lo*hi + hi*hi
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrl, rh_, ar[b], 0, 0, 0);
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, rl_, ar[b], 0, 0, 0);
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, rh_, ar[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yil, rh_, ai[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yih, rl_, ai[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yih, rh_, ai[b], 0, 0, 0);
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nil, ih_, ar[b], 0, 0, 0);
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, il_, ar[b], 0, 0, 0);
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, ih_, ar[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrl, ih_, ai[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, il_, ai[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, ih_, ai[b], 0, 0, 0);
-          }
-        }
-      } else {
-#pragma unroll 4
-        for (int k = 0; k < KH; ++k) {
-          const float br = Bf[k * 4 * kT], bi = Bf[(k * 4 + n_pad) * kT];
-#pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            const float2 av = ap[(int64_t)(b * KH + k) * 64];
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, br, ar[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, br, ai[b], 0, 0, 0);
-            ar[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bi, ar[b], 0, 0, 0);
-            ai[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bi, ai[b], 0, 0, 0);
-          }
+        for (int b = 0; b < NB; ++b) {
+          const u32x4* av = aq + (int64_t)(b * KS16 + k) * 64 * 4;
+          const u32x4 u0 = av[0], u1 = av[1], u2 = av[2], u3 = av[3];
+          const bf8_t yrh = __builtin_bit_cast(bf8_t, u0), yrl = __builtin_bit_cast(bf8_t, u1);
+          const bf8_t yih = __builtin_bit_cast(bf8_t, u2), yil = __builtin_bit_cast(bf8_t, u3);
+          const bf8_t nih = __builtin_bit_cast(bf8_t, u2 ^ sgn);
+          const bf8_t nil = __builtin_bit_cast(bf8_t, u3 ^ sgn);
+          // Re dI = Yr Re dE - Yi Im dE, Im dI = Yi Re dE + Yr Im dE, each
+          // product as hi*lo + lo*hi + hi*hi
+          ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrl, rh_, ar[b], 0, 0, 0);
+          ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, rl_, ar[b], 0, 0, 0);
+          ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, rh_, ar[b], 0, 0, 0);
+          ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yil, rh_, ai[b], 0, 0, 0);
+          ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yih, rl_, ai[b], 0, 0, 0);
+          ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yih, rh_, ai[b], 0, 0, 0);
+          ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nil, ih_, ar[b], 0, 0, 0);
+          ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, il_, ar[b], 0, 0, 0);
+          ar[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nih, ih_, ar[b], 0, 0, 0);
+          ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrl, ih_, ai[b], 0, 0, 0);
+          ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, il_, ai[b], 0, 0, 0);
+          ai[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yrh, ih_, ai[b], 0, 0, 0);
         }
       }
       // injections of my machines (the matrix cores, as above)

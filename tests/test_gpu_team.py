@@ -81,6 +81,29 @@ def test_team_is_the_default_above_ten_machines(ctx, n, N, prec, team):
     assert (r["report"]["variant_id"] >= TEAM0) == team
 
 
+# The batched and served forms: teams of two to eight waves, the ones of five and
+# six in pairs (tiles of 32); full, ragged and single tiles, several tiles per item
+BATCH = [(12, 3, 33), (16, 8, 16), (17, 2, 47), (24, 8, 31), (32, 4, 65), (33, 8, 32), (40, 1, 33),
+         (41, 5, 31), (48, 8, 80), (49, 2, 17), (56, 8, 33), (57, 1, 15), (64, 8, 100)]
+
+
+@pytest.mark.parametrize("n,P,N", BATCH)
+def test_team_batched_and_served(ctx, n, P, N):
+    vid = 17 if n <= 16 else 11 if n <= 32 else 12 if n <= 48 else 13
+    sc = workloads.multimachine(n_gen=n, n_dist=P, N=N, K=9, T=0.25, net_seed=400 + n)
+    o = oracle.run(sc)
+    outs = [ctx.run_batch([sc], variant=vid)[0], ctx.submit(sc, variant=vid).wait(),
+            ctx.submit(sc, variant=vid, time_chunk=17).wait(),
+            ctx.run_batch([sc], variant=vid, time_chunk=17)[0]]
+    for r in outs:
+        assert r["report"]["variant_id"] == vid
+        assert mean_err(_np(r["mean"]), o["mean"], o["var"]) <= 1e-4
+        assert rel_err(_np(r["var"]), o["var"]) <= 1e-4
+    # time chunks keep the bits
+    assert np.array_equal(_np(outs[0]["mean"]), _np(outs[3]["mean"]))
+    assert np.array_equal(_np(outs[0]["var"]), _np(outs[3]["var"]))
+
+
 @pytest.mark.parametrize("vid,n", [(TEAM0, 1), (TEAM0, 3), (TEAM0 + 1, 10), (TEAM0 + 5, 50)])
 def test_team_variant_by_id(ctx, vid, n):
     """A team variant asked for by id, with most of its machines padding."""
