@@ -11,10 +11,16 @@
 // Steps on the stream, all FP64:
 //   k_dc_mean    row means                        M workgroups
 //   k_dc_cov     lower-triangle 64x64 tiles of C  x sample slices, then k_dc_cov_sum
-//   k_dc_chol    Cholesky by 32-column blocks     one workgroup (M <= 1024)
-//   k_dc_whiten  substitution by 32-row blocks    residuals of 4-16 samples in LDS
-//   k_dc_range .. k_dc_rank   ranks in each row   buckets + prefix sums, O(N) expected
+//   k_dc_chol    Cholesky by 16-column blocks     one workgroup (M <= 1024)
+//   k_dc_whiten  substitution by 16-row blocks    a wave per 16 samples
+//   k_dc_rank_row             ranks in each row   buckets + prefix sums, O(N) expected;
+//                a workgroup per row in LDS, k_dc_range .. k_dc_rank for longer rows
 //   k_dc_apply   rearrangement                    one thread per entry
+// The products (covariance, trailing updates, substitution) run on the FP64 matrix
+// cores, v_mfma_f64_16x16x4: lane l holds row l%16, column l/16 of A, row l/16,
+// column l%16 of B, and rows 4 r + l/16 of column l%16 of the result (r = 0..3),
+// so a result's register r is the B operand of step r of a product with it.
+// 300 rows of 1e4 samples: 1.72 -> 0.68 ms for the whole design.
 // Ranks order equal values by the lower sample index and always form a
 // permutation, so every gather stays in bounds whatever the values are.
 #include <hip/hip_runtime.h>
@@ -28,12 +34,35 @@ namespace fmc {
 
 namespace {
 
-constexpr int kDcCovTile = 64;  // covariance tile edge (4x4 entries per thread)
-constexpr int kDcChunk = 16;    // samples per LDS stage of the covariance
-constexpr int kDcBlk = 32;      // block of the Cholesky factor and of the substitution
-constexpr int kDcSlab = 64;     // rows of L staged at a time by the substitution
-constexpr int kDcCholThreads = 1024;  // one thread per row below a block (M <= 1024)
-constexpr int kDcPanelRows = 384;     // rows of a block of L held in LDS (101 KB)
+constexpr int kDcCovTile = 64;  // covariance tile edge (32x32 entries per wave)
+constexpr int kDcChunk = 32;    // samples per LDS stage of the covariance
+constexpr int kDcT = 16;        // matrix-core tile: block of the factor and of the substitution
+constexpr int kDcStride = 36;   // LDS row stride of the 32 samples (no bank conflicts)
+constexpr int kDcCholThreads = 512;
+// Longest rows ranked in LDS: two 32-bit words per entry, and with its value.
+constexpr int64_t kDcRowMax = 20000, kDcRowValues = 10200;
+constexpr int kDcRankThreads = 1024;
+
+typedef double d4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ d4v mma(double a, double b, d4v c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// value of v in lane i of each row of 16 lanes (i a constant after unrolling)
+__device__ __forceinline__ double row_lane(double v, int i) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  switch (i) {
+#define FMC_X(K) \
+  case K:        \
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x150 + K, 0xF, 0xF, false), \
+                            __builtin_amdgcn_update_dpp(0, lo, 0x150 + K, 0xF, 0xF, false));
+    FMC_X(0) FMC_X(1) FMC_X(2) FMC_X(3) FMC_X(4) FMC_X(5) FMC_X(6) FMC_X(7)
+    FMC_X(8) FMC_X(9) FMC_X(10) FMC_X(11) FMC_X(12) FMC_X(13) FMC_X(14) FMC_X(15)
+#undef FMC_X
+  }
+  return v;
+}
 
 __global__ void __launch_bounds__(256) k_dc_mean(int64_t N, const double* __restrict__ X,
                                                  double* __restrict__ mean) {
@@ -52,8 +81,10 @@ __global__ void __launch_bounds__(256) k_dc_mean(int64_t N, const double* __rest
 
 // Partial sample cross-products of the centred rows over one slice of the
 // samples (blockIdx.y), for one 64x64 tile (ta, tb), ta >= tb, of C
-// (blockIdx.x enumerates the lower-triangle tiles).  Thread (ty, tx) holds the
-// 4x4 entries (ty + 16u, tx + 16v); chunks of 16 samples are staged in LDS.
+// (blockIdx.x enumerates the lower-triangle tiles).  Wave w holds the 32x32 entries
+// (w / 2, w % 2) as four matrix tiles; chunks of 32 samples are staged in LDS.
+// (As 4x4 entries per thread on the vector units the products took 90 us at 300
+// rows of 1e4 samples; 48 us here.)
 __global__ void __launch_bounds__(256) k_dc_cov(int M, int64_t N, int64_t per,
                                                 const double* __restrict__ X,
                                                 const double* __restrict__ mean,
@@ -66,41 +97,61 @@ __global__ void __launch_bounds__(256) k_dc_cov(int M, int64_t N, int64_t per,
   const int tb = t;
   const int64_t nb0 = (int64_t)blockIdx.y * per;
   const int64_t nb1 = std::min<int64_t>(N, nb0 + per);
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  __shared__ double sa[kDcChunk][kDcCovTile + 1], sb[kDcChunk][kDcCovTile + 1];
-  double acc[4][4] = {};
+  const int wave = threadIdx.x / 64, l = threadIdx.x % 64, c = l & 15, g = l >> 4;
+  const int wa = 32 * (wave / 2), wb = 32 * (wave % 2);
+  __shared__ double sa[kDcCovTile][kDcStride], sb[kDcCovTile][kDcStride];
+  d4v acc[2][2] = {};
+  // a thread's entries of a chunk: sample tid % 32 of rows tid / 32 + 8 u, loaded a
+  // chunk ahead
+  constexpr int kU = kDcCovTile * kDcChunk / 256;
+  const int kk = threadIdx.x % kDcChunk, r0 = threadIdx.x / kDcChunk;
+  double xa[kU], xb[kU], ma[kU], mb[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const int ra = ta * kDcCovTile + r0 + 8 * u, rb = tb * kDcCovTile + r0 + 8 * u;
+    ma[u] = ra < M ? mean[ra] : 0.0;
+    mb[u] = rb < M ? mean[rb] : 0.0;
+  }
+  auto load = [&](int64_t n0) {
+    const int64_t n = n0 + kk;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int ra = ta * kDcCovTile + r0 + 8 * u, rb = tb * kDcCovTile + r0 + 8 * u;
+      xa[u] = ra < M && n < nb1 ? X[(int64_t)ra * N + n] : ma[u];
+      xb[u] = rb < M && n < nb1 ? X[(int64_t)rb * N + n] : mb[u];
+    }
+  };
+  load(nb0);
   for (int64_t n0 = nb0; n0 < nb1; n0 += kDcChunk) {
     __syncthreads();
-    for (int q = threadIdx.x; q < kDcCovTile * kDcChunk; q += 256) {
-      const int r = q / kDcChunk, k = q % kDcChunk;
-      const int64_t n = n0 + k;
-      const int ra = ta * kDcCovTile + r, rb = tb * kDcCovTile + r;
-      sa[k][r] = (ra < M && n < nb1) ? X[(int64_t)ra * N + n] - mean[ra] : 0.0;
-      sb[k][r] = (rb < M && n < nb1) ? X[(int64_t)rb * N + n] - mean[rb] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      sa[r0 + 8 * u][kk] = xa[u] - ma[u];
+      sb[r0 + 8 * u][kk] = xb[u] - mb[u];
     }
+    if (n0 + kDcChunk < nb1) load(n0 + kDcChunk);
     __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < kDcChunk; ++k) {
-      double va[4], vb[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        va[u] = sa[k][ty + 16 * u];
-        vb[u] = sb[k][tx + 16 * u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(va[u], vb[v], acc[u][v]);
+    for (int k = 0; k < kDcChunk; k += 4) {
+      const double a0 = sa[wa + c][k + g], a1 = sa[wa + 16 + c][k + g];
+      const double b0 = sb[wb + c][k + g], b1 = sb[wb + 16 + c][k + g];
+      acc[0][0] = mma(a0, b0, acc[0][0]);
+      acc[0][1] = mma(a0, b1, acc[0][1]);
+      acc[1][0] = mma(a1, b0, acc[1][0]);
+      acc[1][1] = mma(a1, b1, acc[1][1]);
     }
   }
   double* out = P + (int64_t)blockIdx.y * M * M;
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int a = ta * kDcCovTile + ty + 16 * u, b = tb * kDcCovTile + tx + 16 * v;
-      if (a < M && b < M) out[(int64_t)a * M + b] = acc[u][v];
-    }
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ra = ta * kDcCovTile + wa + 16 * u + 4 * r + g;
+        const int rb = tb * kDcCovTile + wb + 16 * v + c;
+        if (ra < M && rb < M) out[(int64_t)ra * M + rb] = acc[u][v][r];
+      }
 }
 
 // C = sum of the slices' partials (in slice order) / (N - 1), both triangles.
@@ -118,176 +169,222 @@ __global__ void __launch_bounds__(256) k_dc_cov_sum(int M, int64_t N, int n_slic
   Cv[(int64_t)b * M + a] = v;
 }
 
-// Cholesky of the M x M matrix A by blocks of 32 columns, one workgroup:
-// the diagonal block is factored in LDS, the rows below it are solved one
-// per thread, and the trailing matrix is updated one wave per row, from the
-// rows' block of L in LDS once they fit (panel_rows rows).  L is
-// written transposed to LT (LT[k][i] = L[i][k], the layout the substitution
-// reads); A's lower triangle is overwritten.  A pivot of at most 1e-12 of its
-// diagonal entry marks a row that is (to rounding) a combination of the rows
-// before it: *status is set and LT is made the identity, so that the later
-// steps leave the design as it is.
-__global__ void __launch_bounds__(kDcCholThreads) k_dc_chol(int M, int panel_rows,
-                                                            double* __restrict__ A,
+// Cholesky of the M x M matrix A (both triangles; not overwritten) by columns of
+// 16x16 tiles, one workgroup.  For block column j a wave forms the tiles
+// (ti, j), ti = j + wave, j + wave + 16, ..., of A - sum_k L_k L_k^T on the matrix
+// cores, transposed (rows of block j, columns of block ti), and keeps them in LDS; wave 0,
+// which has the diagonal tile, factors it (a row per lane) and inverts the factor,
+// and the other tiles are multiplied by that inverse: as in the substitution below a
+// tile's registers are the operand of that product.  Two barriers per block column
+// and no pass over the trailing matrix.  L is written transposed to LT (LT[k][i] =
+// L[i][k], the layout the substitution reads), the inverses of its diagonal blocks
+// to Di in the order of a matrix A operand (Di[b][s][l]: row l%16, column
+// 4 s + l/16).  Bound by the chain of the 16 pivots of each diagonal tile: 300
+// rows 546 -> 230 us (before, blocks of 32 columns factored in LDS with four
+// barriers per column, and a trailing update on the vector units).
+//
+// A pivot of at most 1e-12 of its diagonal entry marks a row that is (to rounding) a
+// combination of the rows before it: *status is set and LT is made the identity,
+// so that the later steps leave the design as it is.
+__global__ void __launch_bounds__(kDcCholThreads) k_dc_chol(int M, const double* __restrict__ A,
                                                             double* __restrict__ LT,
+                                                            double* __restrict__ Di,
                                                             int32_t* __restrict__ status) {
-  extern __shared__ double s_panel[];  // [panel_rows][kDcBlk + 1] block of L below the diagonal
-  __shared__ double s_d0[kDecorMaxM];
-  __shared__ double s_D[kDcBlk][kDcBlk + 1];
-  __shared__ double s_row[kDcCholThreads / 64][kDcBlk];  // one row of the block of L per wave
+  extern __shared__ double s_T[];  // the block column's tiles [nt][4][64]: a lane's registers
+  __shared__ double s_D[kDcT][kDcT + 1];  // the diagonal tile
+  __shared__ double s_Di[kDcT * kDcT];    // the inverse of its factor, operand order
   __shared__ int s_bad;
-  const int tid = threadIdx.x;
-  const int wave = tid / 64, lane = tid % 64, n_waves = blockDim.x / 64;
-  for (int i = tid; i < M; i += blockDim.x) s_d0[i] = A[(int64_t)i * M + i];
+  const int tid = threadIdx.x, wave = tid / 64, l = tid % 64, c = l & 15, g = l >> 4;
+  const int nt = (M + kDcT - 1) / kDcT;
   if (tid == 0) s_bad = 0;
-  for (int j0 = 0; j0 < M; j0 += kDcBlk) {
-    const int nb = std::min(kDcBlk, M - j0);
-    __syncthreads();
-    for (int q = tid; q < kDcBlk * kDcBlk; q += blockDim.x) {
-      const int r = q / kDcBlk, cc = q % kDcBlk;
-      s_D[r][cc] = (r < nb && cc <= r) ? A[(int64_t)(j0 + r) * M + j0 + cc] : 0.0;
-    }
-    for (int c = 0; c < nb; ++c) {
-      __syncthreads();
-      if (tid == 0) {
-        const double d = s_D[c][c];
-        if (!(d > 1e-12 * s_d0[j0 + c])) s_bad = 1;
-        s_D[c][c] = s_bad ? 1.0 : sqrt(d);
-      }
-      __syncthreads();
-      if (s_bad) break;  // uniform: shared flag read after the barrier
-      if (tid > c && tid < nb) s_D[tid][c] /= s_D[c][c];
-      __syncthreads();
-      for (int q = tid; q < kDcBlk * kDcBlk; q += blockDim.x) {
-        const int r = q / kDcBlk, k = q % kDcBlk;
-        if (k > c && k <= r && r < nb) s_D[r][k] -= s_D[r][c] * s_D[k][c];
-      }
-    }
-    __syncthreads();
-    if (s_bad) break;
-    for (int q = tid; q < nb * nb; q += blockDim.x) {
-      const int r = q / nb, cc = q % nb;
-      if (cc <= r) LT[(int64_t)(j0 + cc) * M + j0 + r] = s_D[r][cc];
-    }
-    // rows below the block (at most 1023 of them): L[i][j0 + c] by
-    // substitution against the block, one row per thread
-    const int i = j0 + nb + tid;
-    if (i < M) {
-      double l[kDcBlk];
+  __syncthreads();
+  for (int j = 0; j < nt; ++j) {
+    const int ra = kDcT * j + c;  // column of LT of the A operand (row of block j)
+    const int la = (ra < M ? ra : 0) + g * M;
+#pragma unroll 1
+    for (int ti = j + wave; ti < nt; ti += kDcCholThreads / 64) {
+      const int rb = kDcT * ti + c;
+      const int lb = (rb < M ? rb : 0) + g * M;
+      d4v a0, a1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int c = 0; c < kDcBlk; ++c) {
-        if (c < nb) {
-          double sv = A[(int64_t)i * M + j0 + c];
+      for (int r = 0; r < 4; ++r) {
+        const int row = kDcT * j + 4 * r + g;
+        a0[r] = row < M && rb < M ? A[(int64_t)row * M + rb] : 0.0;
+      }
+#pragma unroll 4
+      for (int k = 0; k < j; ++k) {
 #pragma unroll
-          for (int k = 0; k < c; ++k) sv -= l[k] * s_D[c][k];
-          l[c] = sv / s_D[c][c];
-          LT[(int64_t)(j0 + c) * M + i] = l[c];
-          if (i - j0 - nb < panel_rows) s_panel[(i - j0 - nb) * (kDcBlk + 1) + c] = l[c];
+        for (int s = 0; s < 4; ++s) {
+          const double* row = LT + (kDcT * k + 4 * s) * M;  // (M <= 1024: 32-bit offsets)
+          const double va = row[la], vb = row[lb];
+          if (s & 1)
+            a1 = mma(ra < M ? -va : 0.0, rb < M ? vb : 0.0, a1);
+          else
+            a0 = mma(ra < M ? -va : 0.0, rb < M ? vb : 0.0, a0);
         }
       }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_T[((ti - j) * 4 + r) * 64 + l] = a0[r] + a1[r];
+    }
+    if (wave == 0) {
+      const int nb = std::min(kDcT, M - kDcT * j);
+      int c = l & 15;  // opaque: the masks and addresses below are not kept across blocks
+      asm volatile("" : "+v"(c));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_D[4 * r + g][c] = s_T[r * 64 + l];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // row c of the tile per lane (each quarter of the wave has all of them); rows
+      // past M are the identity
+      double a[kDcT];
+#pragma unroll
+      for (int k = 0; k < kDcT; ++k) a[k] = c < nb && k <= c ? s_D[c][k] : (k == c ? 1.0 : 0.0);
+      const double d0 = c < nb ? A[(int64_t)(kDcT * j + c) * M + kDcT * j + c] : 0.0;
+      // the inverse by the same row operations on the identity: x[m] = row c, column m
+      double x[kDcT];
+#pragma unroll
+      for (int m = 0; m < kDcT; ++m) x[m] = m == c ? 1.0 : 0.0;
+      bool bad = false;
+#pragma unroll
+      for (int k = 0; k < kDcT; ++k) {
+        double d = row_lane(a[k], k);
+        if (!(d > 1e-12 * row_lane(d0, k))) {
+          bad = true;
+          d = 1.0;
+        }
+        // 1 / sqrt(d) from the hardware estimate and two Newton steps
+        double y = __builtin_amdgcn_rsq(d);
+        y = y * fma(-0.5 * d * y, y, 1.5);
+        y = y * fma(-0.5 * d * y, y, 1.5);
+        const double rt = d * y;
+        const double lk = c == k ? fma(fma(-rt, rt, d), 0.5 * y, rt) : a[k] * y;
+        a[k] = lk;
+#pragma unroll
+        for (int m = k + 1; m < kDcT; ++m) a[m] = fma(-lk, row_lane(lk, m), a[m]);
+#pragma unroll
+        for (int m = 0; m <= k; ++m) {
+          const double xk = row_lane(x[m], k) * y;
+          x[m] = c == k ? xk : (c > k ? fma(-lk, xk, x[m]) : x[m]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (bad && l == 0) s_bad = 1;
+      if (g == 0) {  // entry (c, m): step m / 4, lane c + 16 (m % 4)
+#pragma unroll
+        for (int m = 0; m < kDcT; ++m) {
+          const int e = (m >> 2) * 64 + 16 * (m & 3) + c;
+          s_Di[e] = x[m];
+          Di[(int64_t)j * kDcT * kDcT + e] = x[m];
+        }
+#pragma unroll
+        for (int k = 0; k < kDcT; ++k)
+          if (k <= c && c < nb) LT[(int64_t)(kDcT * j + k) * M + kDcT * j + c] = a[k];
+      }
+    }
+    __syncthreads();
+    if (s_bad) break;  // uniform: shared flag read after the barrier
+#pragma unroll 1
+    for (int ti = j + wave; ti < nt; ti += kDcCholThreads / 64) {
+      if (ti == j) continue;  // a tile below: block j is whole
+      d4v z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) z = mma(s_Di[s * 64 + l], s_T[((ti - j) * 4 + s) * 64 + l], z);
+      const int col = kDcT * ti + c;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (col < M) LT[(int64_t)(kDcT * j + 4 * r + g) * M + col] = z[r];
     }
     __syncthreads();  // the block's columns of LT are complete
-    const int base = j0 + nb;
-    if (M - base <= panel_rows) {
-      // trailing update from the rows' block of L held in LDS, one wave per row
-      for (int i2 = base + wave; i2 < M; i2 += n_waves) {
-        const double* pi = s_panel + (i2 - base) * (kDcBlk + 1);
-        for (int k = base + lane; k <= i2; k += 64) {
-          const double* pk = s_panel + (k - base) * (kDcBlk + 1);
-          double acc = A[(int64_t)i2 * M + k];
-          for (int c = 0; c < nb; ++c) acc -= pi[c] * pk[c];
-          A[(int64_t)i2 * M + k] = acc;
-        }
-      }
-      continue;
-    }
-    // trailing update, one wave per row i2: the row's block of L is staged in
-    // the wave's slot of LDS, the 32 loads of each column k are issued at once
-    double* li = s_row[wave];
-    for (int i2 = j0 + nb + wave; i2 < M; i2 += n_waves) {
-      if (lane < kDcBlk) li[lane] = lane < nb ? LT[(int64_t)(j0 + lane) * M + i2] : 0.0;
-      __builtin_amdgcn_wave_barrier();
-      for (int h = 0; h < nb; h += 16) {
-        double lh[16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) lh[c] = li[h + c];
-        for (int k = j0 + nb + lane; k <= i2; k += 64) {
-          double lk[16];
-#pragma unroll
-          for (int c = 0; c < 16; ++c)
-            lk[c] = h + c < nb ? LT[(int64_t)(j0 + h + c) * M + k] : 0.0;
-          double acc = A[(int64_t)i2 * M + k];
-#pragma unroll
-          for (int c = 0; c < 16; ++c) acc -= lh[c] * lk[c];
-          A[(int64_t)i2 * M + k] = acc;
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
   }
-  __syncthreads();
   if (s_bad) {
-    for (int64_t q = tid; q < (int64_t)M * M; q += blockDim.x)
+    for (int64_t q = tid; q < (int64_t)M * M; q += kDcCholThreads)
       LT[q] = (q / M == q % M) ? 1.0 : 0.0;
+    for (int q = tid; q < nt * kDcT * kDcT; q += kDcCholThreads) {
+      const int e = q % (kDcT * kDcT);
+      Di[q] = e % 16 == 4 * (e / 64) + e % 64 / 16 ? 1.0 : 0.0;
+    }
   }
   if (tid == 0) *status = s_bad;
 }
 
-// Z[:, n] = L^{-1} (X[:, n] - mean) by blocks of 32 rows: a workgroup holds
-// the residuals of spw samples for every row in LDS ([M][spw]); within a block
-// the scores z_k = s_k / L_kk are found one after another against the block's
-// diagonal part of L (in LDS), then taken off every row below the block at
-// once.  Thread t owns sample t % spw and rows (t / spw) + g * (256 / spw).
-__global__ void __launch_bounds__(256) k_dc_whiten(int M, int64_t N, int spw,
-                                                   const double* __restrict__ X,
-                                                   const double* __restrict__ mean,
-                                                   const double* __restrict__ LT,
-                                                   double* __restrict__ Z) {
-  extern __shared__ double s_dyn[];
-  double* s_res = s_dyn;                       // [M][spw] residuals
-  double* s_z = s_dyn + (size_t)M * spw;       // [kDcBlk][spw] the block's scores
-  double* s_d = s_z + kDcBlk * spw;            // [kDcBlk][kDcBlk + 1] LT of the block
-  double* s_slab = s_d + kDcBlk * (kDcBlk + 1);  // [kDcBlk][kDcSlab] LT below the block
-  const int j = threadIdx.x % spw, g = threadIdx.x / spw, G = 256 / spw;
-  const int64_t n = (int64_t)blockIdx.x * spw + j;
+// Z[:, n] = L^{-1} (X[:, n] - mean) by blocks of 16 rows, a wave per 16 samples:
+// block b is the residual X_b - mean - sum_k L_bk Z_k on the matrix cores, then the
+// product with the inverse of L_bb.  The scores of the wave's samples stay in LDS
+// ([M][16]); a lane reads back what it wrote itself (operand layouts, see the top),
+// so there is no barrier.  Bound by the reads of L (half of M^2 values per wave,
+// from L2) and the chain of matrix operations of a wave: 300 rows of 1e4 samples,
+// 625 waves, 496 -> 80 us (a substitution by rows on the vector units before).
+__global__ void __launch_bounds__(64) k_dc_whiten(int M, int64_t N, const double* __restrict__ X,
+                                                  const double* __restrict__ mean,
+                                                  const double* __restrict__ LT,
+                                                  const double* __restrict__ Di,
+                                                  double* __restrict__ Z) {
+  extern __shared__ double s_z[];  // [16 n_blk][16]
+  const int l = threadIdx.x, c = l & 15, g = l >> 4;
+  const int64_t n = (int64_t)blockIdx.x * kDcT + c;
   const bool ok = n < N;
-  for (int i = g; i < M; i += G) s_res[i * spw + j] = ok ? X[(int64_t)i * N + n] - mean[i] : 0.0;
-  for (int b0 = 0; b0 < M; b0 += kDcBlk) {
-    const int nb = std::min(kDcBlk, M - b0);
-    __syncthreads();
-    for (int q = threadIdx.x; q < kDcBlk * kDcBlk; q += 256) {
-      const int k = q / kDcBlk, i = q % kDcBlk;
-      s_d[k * (kDcBlk + 1) + i] =
-          (k < nb && i < nb && i >= k) ? LT[(int64_t)(b0 + k) * M + b0 + i] : 0.0;
+  const int n_blk = (M + kDcT - 1) / kDcT;
+  auto residual = [&](int b, d4v& x) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = kDcT * b + 4 * r + g;
+      x[r] = ok && row < M ? X[(int64_t)row * N + n] - mean[row] : 0.0;
     }
-    for (int k = 0; k < nb; ++k) {
-      __syncthreads();
-      const double zk = s_res[(b0 + k) * spw + j] / s_d[k * (kDcBlk + 1) + k];
-      if (g == 0) s_z[k * spw + j] = zk;
-      for (int i = k + 1 + g; i < nb; i += G)
-        s_res[(b0 + i) * spw + j] -= s_d[k * (kDcBlk + 1) + i] * zk;
+  };
+  // L comes in batches of four blocks, the next one's loads (the next row of
+  // blocks' first batch at the end of a row) ahead of this one's products
+  constexpr int kB = 4;
+  auto load = [&](int b, int k0, double (&v)[kB][4]) {
+    const int row = kDcT * b + c;
+    const double* lt = LT + (row < M ? row : 0) + (int64_t)g * M;
+#pragma unroll
+    for (int q = 0; q < kB; ++q)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + q < b ? k0 + q : 0;  // (a block of the row; not used)
+        v[q][s] = lt[(int64_t)(kDcT * k + 4 * s) * M];
+      }
+  };
+  d4v next;
+  double cur[kB][4], nxt[kB][4];
+  residual(0, next);
+  load(std::min(1, n_blk - 1), 0, cur);
+  for (int b = 0; b < n_blk; ++b) {
+    d4v acc = next, acc1 = {0.0, 0.0, 0.0, 0.0};
+    if (b + 1 < n_blk) residual(b + 1, next);  // loads ahead of this block's products
+    const bool in = kDcT * b + c < M;  // (a row past M read what LT does not hold)
+    for (int k0 = 0; k0 < b; k0 += kB) {
+      if (k0 + kB < b)
+        load(b, k0 + kB, nxt);
+      else
+        load(b + 1 < n_blk ? b + 1 : b, 0, nxt);
+#pragma unroll
+      for (int q = 0; q < kB; ++q) {
+        if (k0 + q < b) {  // uniform
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const double zv = s_z[(kDcT * (k0 + q) + 4 * s + g) * kDcT + c];
+            if (s & 1)
+              acc1 = mma(in ? -cur[q][s] : 0.0, zv, acc1);
+            else
+              acc = mma(in ? -cur[q][s] : 0.0, zv, acc);
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kB; ++q)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) cur[q][s] = nxt[q][s];
     }
-    __syncthreads();
-    // the block's scores go out here, not inside the steps above: a barrier
-    // waits for the workgroup's outstanding stores
-    for (int k = g; k < nb; k += G)
-      if (ok) Z[(int64_t)(b0 + k) * N + n] = s_z[k * spw + j];
-    // rows below the block, kDcSlab at a time: the block's columns of L for
-    // those rows are staged in LDS with coalesced loads, then every thread
-    // updates its rows from there
-    for (int r0 = b0 + nb; r0 < M; r0 += kDcSlab) {
-      const int nr = std::min(kDcSlab, M - r0);
-      __syncthreads();  // the previous slab has been read
-      for (int q = threadIdx.x; q < kDcBlk * kDcSlab; q += 256) {
-        const int k = q / kDcSlab, i = q % kDcSlab;
-        s_slab[k * kDcSlab + i] = (k < nb && i < nr) ? LT[(int64_t)(b0 + k) * M + r0 + i] : 0.0;
-      }
-      __syncthreads();
-      for (int i = g; i < nr; i += G) {
-        double acc = s_res[(r0 + i) * spw + j];
-        for (int k = 0; k < nb; ++k) acc -= s_slab[k * kDcSlab + i] * s_z[k * spw + j];
-        s_res[(r0 + i) * spw + j] = acc;
-      }
+    d4v z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) z = mma(Di[(int64_t)b * 256 + s * 64 + l], acc[s] + acc1[s], z);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int zr = kDcT * b + 4 * r + g;
+      s_z[zr * kDcT + c] = z[r];
+      if (ok && zr < M) Z[(int64_t)zr * N + n] = z[r];
     }
   }
 }
@@ -427,6 +524,118 @@ __global__ void __launch_bounds__(256) k_dc_rank(int64_t N, const double* __rest
   if (inv) inv[row + r] = (int32_t)n;
 }
 
+// The ranks of a row (as k_dc_range .. k_dc_rank) by one workgroup, counts and
+// order in LDS: [N + 1] bucket offsets, [N] entries by bucket and, with VALUES, their
+// values (rows up to kDcRowValues; else the values of a bucket's entries are read
+// from memory again).  A thread keeps its entries in registers.  The global form's
+// counters and orders make six passes with an atomic per entry and pass to L2: 350
+// us for 300 rows of 1e4, 42 us here.
+template <bool VALUES>
+__global__ void __launch_bounds__(kDcRankThreads) k_dc_rank_row(int N, const double* __restrict__ V,
+                                                                int32_t* __restrict__ R,
+                                                                int32_t* __restrict__ inv) {
+  constexpr int64_t kMax = VALUES ? kDcRowValues : kDcRowMax;
+  constexpr int kPer = (int)((kMax + kDcRankThreads - 1) / kDcRankThreads);
+  extern __shared__ double s_val[];  // with VALUES [N]; then [N + 1] offsets, the order [N]
+  int32_t* s_off = reinterpret_cast<int32_t*>(VALUES ? s_val + N : s_val);
+  int32_t* s_perm = s_off + N + 1;
+  __shared__ double s_lo[kDcRankThreads / 64], s_hi[kDcRankThreads / 64];
+  __shared__ int32_t s_sum[kDcRankThreads / 64];
+  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+  const int64_t row = (int64_t)blockIdx.x * N;
+  const double* v = V + row;
+  double x[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int n = tid + j * kDcRankThreads;
+    x[j] = v[n < N ? n : N - 1];
+  }
+  double lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    if (isfinite(x[j])) {
+      lo = fmin(lo, x[j]);
+      hi = fmax(hi, x[j]);
+    }
+  }
+  for (int w = 32; w > 0; w >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, w, 64));
+    hi = fmax(hi, __shfl_xor(hi, w, 64));
+  }
+  if (lane == 0) {
+    s_lo[wave] = lo;
+    s_hi[wave] = hi;
+  }
+  for (int q = tid; q <= N; q += kDcRankThreads) s_off[q] = 0;
+  __syncthreads();
+  for (int w = 0; w < kDcRankThreads / 64; ++w) {
+    lo = fmin(lo, s_lo[w]);
+    hi = fmax(hi, s_hi[w]);
+  }
+  const double span = hi - lo;
+  const double scale = (lo <= hi && span > 0.0 && span < INFINITY) ? (double)N / span : 0.0;
+  if (!(lo <= hi)) lo = 0.0;
+  int32_t bkt[kPer], slot[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int n = tid + j * kDcRankThreads;
+    if (n < N) {
+      const double f = (x[j] - lo) * scale;
+      bkt[j] = !(f >= 0.0) ? 0 : !(f < (double)N) ? N - 1 : (int32_t)f;  // NaN, -inf; +inf, top
+      slot[j] = atomicAdd(&s_off[bkt[j]], 1);
+    }
+  }
+  __syncthreads();
+  {  // exclusive prefix sum of the counts: a run of buckets per thread
+    const int per = (N + kDcRankThreads - 1) / kDcRankThreads;
+    const int q0 = tid * per, q1 = min(N, q0 + per);
+    int32_t mine = 0;
+    for (int q = q0; q < q1; ++q) mine += s_off[q];
+    int32_t up = mine;  // inclusive over the wave
+    for (int w = 1; w < 64; w <<= 1) {
+      const int32_t o = __shfl_up(up, w, 64);
+      if (lane >= w) up += o;
+    }
+    if (lane == 63) s_sum[wave] = up;
+    __syncthreads();
+    int32_t o = up - mine;
+    for (int w = 0; w < wave; ++w) o += s_sum[w];
+    for (int q = q0; q < q1; ++q) {
+      const int32_t cq = s_off[q];
+      s_off[q] = o;
+      o += cq;
+    }
+    if (tid == 0) s_off[N] = N;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int n = tid + j * kDcRankThreads;
+    if (n < N) {
+      const int32_t p = s_off[bkt[j]] + slot[j];
+      s_perm[p] = n;
+      if constexpr (VALUES) s_val[p] = x[j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int n = tid + j * kDcRankThreads;
+    if (n < N) {
+      const int32_t o0 = s_off[bkt[j]], o1 = s_off[bkt[j] + 1];
+      const uint64_t key = order_key(x[j]);
+      int32_t r = o0;
+      for (int32_t p = o0; p < o1; ++p) {
+        const int32_t m = s_perm[p];
+        const uint64_t km = order_key(VALUES ? s_val[p] : v[m]);
+        r += (km < key) || (km == key && m < n);
+      }
+      if (R) R[row + n] = r;
+      if (inv) inv[row + r] = n;
+    }
+  }
+}
+
 // inv[i][strata[i][n]] = n for a design whose strata are known (an LHS
 // design: the order of a row's values is the order of their strata).
 __global__ void __launch_bounds__(256) k_dc_invert(int64_t N, const int32_t* __restrict__ strata,
@@ -475,19 +684,6 @@ struct CovPlan {
   }
 };
 
-// Samples per substitution workgroup: the largest of 16, 8, 4 whose LDS
-// (residuals, block scores, diagonal block, slab of L) stays within 80 KB.
-size_t whiten_lds(int32_t M, int spw) {
-  return ((size_t)M * spw + (size_t)kDcBlk * spw + (size_t)kDcBlk * (kDcBlk + 1) +
-          (size_t)kDcBlk * kDcSlab) *
-         sizeof(double);
-}
-int whiten_spw(int32_t M) {
-  int spw = 16;
-  while (spw > 4 && whiten_lds(M, spw) > 80 * 1024) spw /= 2;
-  return spw;
-}
-
 struct RankBufs {
   double2* lohi;
   int32_t *bkt, *off, *fill, *perm;
@@ -496,6 +692,17 @@ struct RankBufs {
 // Ranks of the rows of V[M][N] (R and/or inv, see k_dc_rank).
 void launch_rank(int32_t M, int64_t N, const double* V, const RankBufs& b, int32_t* R,
                  int32_t* inv, hipStream_t st) {
+  const size_t words = (size_t)(2 * N + 1) * sizeof(int32_t);
+  if (N <= kDcRowValues) {
+    hipLaunchKernelGGL(k_dc_rank_row<true>, dim3((unsigned)M), dim3(kDcRankThreads),
+                       words + (size_t)N * sizeof(double), st, (int)N, V, R, inv);
+    return;
+  }
+  if (N <= kDcRowMax) {
+    hipLaunchKernelGGL(k_dc_rank_row<false>, dim3((unsigned)M), dim3(kDcRankThreads), words, st,
+                       (int)N, V, R, inv);
+    return;
+  }
   const unsigned gs = (unsigned)((N + 255) / 256);
   const int64_t MN = (int64_t)M * N;
   hipLaunchKernelGGL(k_dc_range, dim3((unsigned)M), dim3(256), 0, st, N, V, b.lohi);
@@ -516,7 +723,7 @@ size_t decorrelate_workspace(int32_t M, int64_t N) {
   const CovPlan cp(M, N);
   return (size_t)M * N * (sizeof(double) + 7 * sizeof(int32_t)) +
          ((size_t)cp.n_slices + 2) * M * M * sizeof(double) + 3 * (size_t)M * sizeof(double2) +
-         7 * 256;
+         (size_t)(M + kDcT - 1) / kDcT * 256 * sizeof(double) + 8 * 256;
 }
 
 int decorrelate_design(Context* c, int32_t M, int64_t N, double* zeta, int32_t* strata,
@@ -525,7 +732,7 @@ int decorrelate_design(Context* c, int32_t M, int64_t N, double* zeta, int32_t* 
     return fail(FMC_EINVAL, "correlation reduction needs M <= 1024 and M < N < 2^31");
   const size_t MN = (size_t)M * N;
   const CovPlan cp(M, N);
-  void *z, *rz, *inv, *bkt, *off, *fill, *perm, *part, *cv, *lt, *mean, *lohi, *sts;
+  void *z, *rz, *inv, *bkt, *off, *fill, *perm, *part, *cv, *lt, *di, *mean, *lohi, *sts;
   int rc;
   if ((rc = c->ensure("dc_z", MN * sizeof(double), &z))) return rc;
   if ((rc = c->ensure("dc_rz", MN * sizeof(int32_t), &rz))) return rc;
@@ -537,6 +744,7 @@ int decorrelate_design(Context* c, int32_t M, int64_t N, double* zeta, int32_t* 
   if ((rc = c->ensure("dc_part", (size_t)cp.n_slices * M * M * sizeof(double), &part))) return rc;
   if ((rc = c->ensure("dc_c", (size_t)M * M * sizeof(double), &cv))) return rc;
   if ((rc = c->ensure("dc_lt", (size_t)M * M * sizeof(double), &lt))) return rc;
+  if ((rc = c->ensure("dc_di", (size_t)(M + kDcT - 1) / kDcT * 256 * sizeof(double), &di))) return rc;
   if ((rc = c->ensure("dc_mean", (size_t)M * sizeof(double), &mean))) return rc;
   if ((rc = c->ensure("dc_lohi", (size_t)M * sizeof(double2), &lohi))) return rc;
   if ((rc = c->ensure("dc_status", 256, &sts))) return rc;
@@ -545,18 +753,16 @@ int decorrelate_design(Context* c, int32_t M, int64_t N, double* zeta, int32_t* 
   int32_t* status = (int32_t*)sts;
   const RankBufs rb{(double2*)lohi, (int32_t*)bkt, (int32_t*)off, (int32_t*)fill, (int32_t*)perm};
   const unsigned gs = (unsigned)((N + 255) / 256);
-  const int spw = whiten_spw(M);
   hipLaunchKernelGGL(k_dc_mean, dim3((unsigned)M), dim3(256), 0, st, N, zeta, mu);
   hipLaunchKernelGGL(k_dc_cov, dim3(cp.n_tiles, (unsigned)cp.n_slices), dim3(256), 0, st, M, N,
                      cp.per, zeta, mu, (double*)part);
   hipLaunchKernelGGL(k_dc_cov_sum, dim3((unsigned)(((int64_t)M * M + 255) / 256)), dim3(256), 0, st,
                      M, N, cp.n_slices, (const double*)part, (double*)cv);
-  const int panel_rows = std::min(M, kDcPanelRows);
-  hipLaunchKernelGGL(k_dc_chol, dim3(1), dim3(kDcCholThreads),
-                     (size_t)panel_rows * (kDcBlk + 1) * sizeof(double), st, M, panel_rows,
-                     (double*)cv, (double*)lt, status);
-  hipLaunchKernelGGL(k_dc_whiten, dim3((unsigned)((N + spw - 1) / spw)), dim3(256),
-                     whiten_lds(M, spw), st, M, N, spw, zeta, mu, (const double*)lt, Z);
+  const size_t tiles = (size_t)((M + kDcT - 1) / kDcT) * kDcT * kDcT * sizeof(double);
+  hipLaunchKernelGGL(k_dc_chol, dim3(1), dim3(kDcCholThreads), tiles, st, M, (const double*)cv,
+                     (double*)lt, (double*)di, status);
+  hipLaunchKernelGGL(k_dc_whiten, dim3((unsigned)((N + kDcT - 1) / kDcT)), dim3(64),
+                     tiles, st, M, N, zeta, mu, (const double*)lt, (const double*)di, Z);
   launch_rank(M, N, Z, rb, (int32_t*)rz, nullptr, st);
   // the design's own ranks, kept only as their inverse (the entry of each
   // rank); an LHS design's strata are those ranks
