@@ -142,13 +142,14 @@ hipError_t launch_mix_design(const double* S, int32_t P, int32_t K, int64_t N, c
 hipError_t launch_lhs(uint64_t seed, int32_t M, int64_t N, int32_t sampler, int32_t* strata,
                       double* zeta, hipStream_t st);
 hipError_t launch_basis(int32_t kind, int32_t K, int64_t S, double T, double* phi, hipStream_t st);
-// max_blocks > 0 caps the workgroups (they then stride over the tiles).
+// alone: nothing else runs beside the launch (the rule for the tiles, k_sample.hip).
 hipError_t launch_kle_f64(const double* zeta, const double* phi, int64_t phi_ld, int P, int K,
                           int64_t N, int64_t C, int64_t c0, double* w, hipStream_t st,
-                          int max_blocks = 0);
+                          bool alone = false);
 hipError_t launch_kle_f64_to_f32(const double* zeta, const double* phi, int64_t phi_ld, int P,
                                  int K, int64_t N, int64_t C, int64_t c0, float* w,
-                                 hipStream_t st, int max_blocks = 0);
+                                 hipStream_t st, bool alone = false);
+// max_blocks > 0 caps the workgroups (they then stride over the tiles).
 hipError_t launch_kle_bf16x3(const double* zeta, const double* phi, int64_t phi_ld, int P, int K,
                              int64_t N, int64_t C, int64_t c0, float* w, hipStream_t st,
                              int max_blocks = 0);

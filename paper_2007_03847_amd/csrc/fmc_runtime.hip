@@ -719,9 +719,9 @@ int fmc_kle_paths(fmc_context* ctx, int32_t precision, int32_t P, int32_t K, int
   (void)hipSetDevice(c->device);
   hipError_t e;
   if (precision == FMC_F64)
-    e = launch_kle_f64(zeta, phi, phi_ld, P, K, N, C, c0, (double*)w, c->stream);
+    e = launch_kle_f64(zeta, phi, phi_ld, P, K, N, C, c0, (double*)w, c->stream, true);
   else if (precision == FMC_F32)
-    e = launch_kle_f64_to_f32(zeta, phi, phi_ld, P, K, N, C, c0, (float*)w, c->stream);
+    e = launch_kle_f64_to_f32(zeta, phi, phi_ld, P, K, N, C, c0, (float*)w, c->stream, true);
   else if (precision == FMC_BF16X3) {
     // split the operands once (the columns c0..c0+C-1 of phi only), then contract
     const int Kp = kle_kp(K);

@@ -122,74 +122,81 @@ hipError_t launch_basis(int32_t kind, int32_t K, int64_t S, double T, double* ph
 //
 // FP64: v_mfma_f64_16x16x4_f64.  Operand lanes: A[i][k] at lane 16k + i,
 // B[k][j] at lane 16k + j; result register r of lane l is D[4r + l/16][l%16].
-// Each wave owns a 32 (c) x 64 (n) output tile: 2 x 4 blocks of 16 x 16 in
-// eight accumulators, so every k-step of four loads 2 + 4 operand fragments
-// for 8 matrix operations; the fragments of the next k-step are loaded while
-// the current one's operations run.  A workgroup's four waves lie along c (a
-// 128 x 64 tile): they read the same zeta fragments, which the first brings
-// into L1 for the others, so the design (tens to hundreds of MB, beyond the
-// L2) is streamed C/128 times per chunk; Phi (a few hundred KB shared by
+// Each wave owns a 32 (c) x 16 NB (n) output tile: 2 x NB blocks of 16 x 16 in
+// 2 NB accumulators, so every k-step of four loads 2 + NB operand fragments
+// for 2 NB matrix operations; the fragments of the next k-step are loaded while
+// the current one's operations run.  Phi (a few hundred KB shared by
 // every workgroup) stays in L2.
+//   NB = 4: a workgroup's four waves lie along c (a 128 x 64 tile): they read the
+// same zeta fragments, which the first brings into L1 for the others, so the design
+// (tens to hundreds of MB, beyond the L2) is streamed C/128 times per chunk.
+//   NB = 2: workgroups take four consecutive wave tiles of 32 x 32, c fastest.  No
+// wave idles past C, and a launch has up to four times the waves.
+// The rule (launch_kle_f64_t), us per call with NB = 4 / NB = 2: launches of fewer
+// than 512 128 x 64 tiles take NB = 2 (6 processes, 333 samples, C = 77: 8.8 / 7.2; 1000
+// samples, C = 2001: 9.5 / 8.8), as do those whose 128-rows would leave a fifth of
+// the waves idle (5e4 samples, C = 25: 124 / 113; 1e5, C = 83: 170 / 165) and launches
+// beside an integrator (10 machines, 1e4 samples, 4000 steps: 9.56 / 9.10 ms per run);
+// the others NB = 4 (1e4 samples, C = 419, inputs from memory: 66.9 / 68.4).
 // ---------------------------------------------------------------------------
 typedef double d4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 
-constexpr int kKleTC = 128, kKleTN = 64;  // workgroup tile (c, n): four waves along c
+constexpr int kKleTC = 32;  // c of a wave tile
 
-template <typename OutT, typename OffT>
+template <int NB, typename OutT, typename OffT>
 __device__ __forceinline__ void kle_f64_tile(const double* __restrict__ zeta,
                                              const double* __restrict__ phi, int64_t phi_ld,
                                              int P, int K, int64_t N, int64_t C, int64_t c0,
                                              OutT* __restrict__ w, int64_t bx, int64_t by, int p) {
   const int lane = threadIdx.x & 63;
-  const int64_t cb = by * kKleTC + (threadIdx.x >> 6) * 32;
-  const int64_t n0 = bx * kKleTN;
-  if (cb >= C) return;  // uniform per wave
+  const int64_t cb = by * kKleTC;
+  const int64_t n0 = bx * (16 * NB);
   const int li = lane & 15, lk = lane >> 4;
   // Per-lane byte offsets inside a k-step of four rows, from a base that
   // moves with the step (the loads take a scalar base and a 32-bit offset).
   // Columns past the edge (c >= C, n >= N) read the last valid one: they
   // feed only output rows and columns that are never stored, so every load
   // is unconditional and the loop carries no branch.
-  OffT ao[2], bo[4];
+  OffT ao[2], bo[NB];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int64_t c = cb + 16 * h + li;
     ao[h] = (OffT)(8 * (lk * phi_ld + (c < C ? c : C - 1)));
   }
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
+  for (int b = 0; b < NB; ++b) {
     const int64_t n = n0 + 16 * b + li;
     bo[b] = (OffT)(8 * (lk * N + (n < N ? n : N - 1)));
   }
   const char* __restrict__ A = (const char*)(phi + c0);                    // row j: + 8 j phi_ld
   const char* __restrict__ B = (const char*)(zeta + (int64_t)p * K * N);  // row j: + 8 j N
-  d4_t acc[2][4];
+  d4_t acc[2][NB];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[h][b] = d4_t{0.0, 0.0, 0.0, 0.0};
-  auto load = [&](int j0, double (&a)[2], double (&bv)[4]) {
+    for (int b = 0; b < NB; ++b) acc[h][b] = d4_t{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](int j0, double (&a)[2], double (&bv)[NB]) {
     const char* Aj = A + 8 * (int64_t)j0 * phi_ld;
     const char* Bj = B + 8 * (int64_t)j0 * N;
 #pragma unroll
     for (int h = 0; h < 2; ++h) a[h] = *(const double*)(Aj + ao[h]);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) bv[b] = *(const double*)(Bj + bo[b]);
+    for (int b = 0; b < NB; ++b) bv[b] = *(const double*)(Bj + bo[b]);
   };
-  auto step = [&](const double (&a)[2], const double (&bv)[4]) {
+  auto step = [&](const double (&a)[2], const double (&bv)[NB]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < NB; ++b)
         acc[h][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h], bv[b], acc[h][b], 0, 0, 0);
   };
   // k-steps of four rows in pairs, with two fragment sets in turn: the next
   // step's fragments load while this step's products run.  A prefetch past
   // the last full step re-reads that step's rows and stays unused.
   const int K4 = K & ~3;
-  double ax[2], bx4[4], ay[2], by4[4];
+  double ax[2], bx4[NB], ay[2], by4[NB];
   if (K4 > 0) load(0, ax, bx4);
   int j0 = 0;
   for (; j0 + 8 <= K4; j0 += 8) {
@@ -202,14 +209,14 @@ __device__ __forceinline__ void kle_f64_tile(const double* __restrict__ zeta,
   if (K4 < K) {  // the last K mod 4 rows; lanes of rows past K contribute zero
     const bool jv = K4 + lk < K;
     const int64_t dj = 8 * (int64_t)(jv ? K4 : K - 1 - lk);  // the lane's row, clamped to K - 1
-    double a[2], bv[4];
+    double a[2], bv[NB];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const double v = *(const double*)(A + dj * phi_ld + ao[h]);
       a[h] = jv ? v : 0.0;
     }
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < NB; ++b) {
       const double v = *(const double*)(B + dj * N + bo[b]);
       bv[b] = jv ? v : 0.0;
     }
@@ -223,7 +230,7 @@ __device__ __forceinline__ void kle_f64_tile(const double* __restrict__ zeta,
       if (c >= C) continue;
       OutT* row = w + (c * P + p) * N;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
+      for (int b = 0; b < NB; ++b) {
         const int64_t n = n0 + 16 * b + li;
         if (n < N) row[n] = (OutT)acc[h][b][r];
       }
@@ -241,52 +248,55 @@ __device__ __forceinline__ int64_t kle_xcd_tile(int64_t b, int64_t n_tiles) {
   return k < r ? k * (q + 1) + j : r * (q + 1) + (k - r) * q + j;
 }
 
-// The grid is a flat list of blocks striding over the (n, c, p) tiles, so a
-// launch can use fewer workgroups than tiles (to run beside another kernel).
+// One workgroup per group of four (c, n, p) wave tiles.
 // OffT is the type of the per-lane byte offsets: 32-bit while four rows of
 // either operand span less than 4 GiB (the loads then take a scalar base and
-// a 32-bit offset), else 64-bit.  Four waves per SIMD: eight accumulators
-// of 16 x 16 doubles (64 registers) and two k-steps of fragments.
-template <typename OutT, typename OffT>
+// a 32-bit offset), else 64-bit.  Four waves per SIMD at least.
+template <int NB, typename OutT, typename OffT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_kle_f64(const double* __restrict__ zeta, const double* __restrict__ phi, int64_t phi_ld, int P,
           int K, int64_t N, int64_t C, int64_t c0, OutT* __restrict__ w) {
-  const int64_t tx = (N + kKleTN - 1) / kKleTN, ty = (C + kKleTC - 1) / kKleTC;
-  const int64_t n_tiles = tx * ty * P;
-  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const int64_t L = gridDim.x == n_tiles ? kle_xcd_tile(tile, n_tiles) : tile;
-    kle_f64_tile<OutT, OffT>(zeta, phi, phi_ld, P, K, N, C, c0, w, (L / ty) % tx, L % ty,
-                             (int)(L / (tx * ty)));
-  }
+  const int64_t tx = (N + 16 * NB - 1) / (16 * NB);
+  const int64_t ty = NB == 4 ? (C + 4 * kKleTC - 1) / (4 * kKleTC) * 4 : (C + kKleTC - 1) / kKleTC;
+  const int64_t n_tiles = tx * ty * P, n_groups = (n_tiles + 3) / 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t L = 4 * kle_xcd_tile(blockIdx.x, n_groups) + wave;
+  const int64_t by = L % ty;
+  if (L < n_tiles && by * kKleTC < C)
+    kle_f64_tile<NB, OutT, OffT>(zeta, phi, phi_ld, P, K, N, C, c0, w, (L / ty) % tx, by,
+                                 (int)(L / (tx * ty)));
 }
 template <typename OutT>
 static hipError_t launch_kle_f64_t(const double* zeta, const double* phi, int64_t phi_ld, int P,
                                    int K, int64_t N, int64_t C, int64_t c0, OutT* w,
-                                   hipStream_t st, int max_blocks) {
+                                   hipStream_t st, bool alone) {
   if (C <= 0 || N <= 0 || P <= 0) return hipSuccess;
-  int64_t tiles = ((N + kKleTN - 1) / kKleTN) * ((C + kKleTC - 1) / kKleTC) * P;
-  if (max_blocks > 0) tiles = std::min<int64_t>(tiles, max_blocks);
+  const int64_t rows = (C + kKleTC - 1) / kKleTC, rows4 = (rows + 3) / 4;
+  const int64_t tiles4 = (N + 63) / 64 * rows4 * P;  // 128 x 64 tiles
+  const bool wide = alone && tiles4 >= 512 && 5 * rows >= 4 * 4 * rows4;
+  const int64_t grid = wide ? tiles4 : ((N + 31) / 32 * rows * P + 3) / 4;
   // largest byte offset of a lane inside a k-step: 8 (3 ld + ld - 1) < 32 ld
   const bool narrow = 32 * std::max<int64_t>(N, phi_ld) <= (int64_t)UINT32_MAX;
-  if (narrow)
-    hipLaunchKernelGGL((k_kle_f64<OutT, uint32_t>), dim3((unsigned)tiles), dim3(256), 0, st, zeta,
-                       phi, phi_ld, P, K, N, C, c0, w);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, zeta, phi, phi_ld, P, K, N, C, c0, w);
+  };
+  if (wide)
+    narrow ? go(k_kle_f64<4, OutT, uint32_t>) : go(k_kle_f64<4, OutT, int64_t>);
   else
-    hipLaunchKernelGGL((k_kle_f64<OutT, int64_t>), dim3((unsigned)tiles), dim3(256), 0, st, zeta,
-                       phi, phi_ld, P, K, N, C, c0, w);
+    narrow ? go(k_kle_f64<2, OutT, uint32_t>) : go(k_kle_f64<2, OutT, int64_t>);
   return hipGetLastError();
 }
 
 hipError_t launch_kle_f64(const double* zeta, const double* phi, int64_t phi_ld, int P, int K,
                           int64_t N, int64_t C, int64_t c0, double* w, hipStream_t st,
-                          int max_blocks) {
-  return launch_kle_f64_t<double>(zeta, phi, phi_ld, P, K, N, C, c0, w, st, max_blocks);
+                          bool alone) {
+  return launch_kle_f64_t<double>(zeta, phi, phi_ld, P, K, N, C, c0, w, st, alone);
 }
 
 hipError_t launch_kle_f64_to_f32(const double* zeta, const double* phi, int64_t phi_ld, int P,
                                  int K, int64_t N, int64_t C, int64_t c0, float* w,
-                                 hipStream_t st, int max_blocks) {
-  return launch_kle_f64_t<float>(zeta, phi, phi_ld, P, K, N, C, c0, w, st, max_blocks);
+                                 hipStream_t st, bool alone) {
+  return launch_kle_f64_t<float>(zeta, phi, phi_ld, P, K, N, C, c0, w, st, alone);
 }
 
 // ---------------------------------------------------------------------------
@@ -443,7 +453,9 @@ hipError_t launch_split_bf16(const double* X, int64_t ld, int K, int64_t items, 
 // v_mfma_f32_16x16x32_bf16.  Each wave owns a 32 (c) x 64 (n) output tile (2 x
 // 4 blocks, eight accumulators); a k-step of 32 loads 4 + 8 fragments of 16
 // bytes for 24 matrix operations, and the next k-step's fragments are loaded
-// while they run.  Four waves per workgroup along c, as for FP64.
+// while they run.  Four waves per workgroup along c.
+constexpr int kKle16TC = 128, kKle16TN = 64;  // workgroup tile (c, n): four waves along c
+
 __device__ __forceinline__ void kle_bf16s_tile(const __bf16* __restrict__ ph,
                                                const __bf16* __restrict__ pl, int Kp,
                                                const __bf16* __restrict__ zh,
@@ -451,8 +463,8 @@ __device__ __forceinline__ void kle_bf16s_tile(const __bf16* __restrict__ ph,
                                                int64_t C, int64_t c0, float* __restrict__ w,
                                                int64_t bx, int64_t by, int p) {
   const int lane = threadIdx.x & 63;
-  const int64_t cb = by * kKleTC + (threadIdx.x >> 6) * 32;
-  const int64_t n0 = bx * kKleTN;
+  const int64_t cb = by * kKle16TC + (threadIdx.x >> 6) * 32;
+  const int64_t n0 = bx * kKle16TN;
   if (cb >= C) return;  // uniform per wave
   const int li = lane & 15, ko = 8 * (lane >> 4);
   f4_t acc[2][4];
@@ -528,7 +540,7 @@ __global__ void __launch_bounds__(256) k_kle_bf16x3s(const __bf16* __restrict__ 
                                                      const __bf16* __restrict__ zl, int P,
                                                      int64_t N, int64_t C, int64_t c0,
                                                      float* __restrict__ w) {
-  const int64_t tx = (N + kKleTN - 1) / kKleTN, ty = (C + kKleTC - 1) / kKleTC;
+  const int64_t tx = (N + kKle16TN - 1) / kKle16TN, ty = (C + kKle16TC - 1) / kKle16TC;
   const int64_t n_tiles = tx * ty * P;
   for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const int64_t L = gridDim.x == n_tiles ? kle_xcd_tile(tile, n_tiles) : tile;
@@ -542,7 +554,7 @@ hipError_t launch_kle_bf16x3_split(const void* ph, const void* pl, int Kp, const
                                    float* w, hipStream_t st) {
   if (C <= 0 || N <= 0 || P <= 0) return hipSuccess;
   if (Kp <= 0 || Kp % 32 != 0) return hipErrorInvalidValue;
-  const int64_t tiles = ((N + kKleTN - 1) / kKleTN) * ((C + kKleTC - 1) / kKleTC) * P;
+  const int64_t tiles = ((N + kKle16TN - 1) / kKle16TN) * ((C + kKle16TC - 1) / kKle16TC) * P;
   hipLaunchKernelGGL(k_kle_bf16x3s, dim3((unsigned)tiles), dim3(256), 0, st, (const __bf16*)ph,
                      (const __bf16*)pl, Kp, (const __bf16*)zh, (const __bf16*)zl, P, N, C, c0, w);
   return hipGetLastError();
