@@ -1,6 +1,8 @@
 """The KLE path contraction at the edges of its wave tiles and of the workgroups of
-four of them (either tile shape), against the FP64 oracle: FP64 to 1e-13 of the largest
-path value, FP32 storage to half a unit in its last place (6e-8)."""
+four of them (either tile shape), and the design at the edges of a workgroup's
+samples and of the tabulated permutation, against the FP64 oracle: FP64 paths to 1e-13 of
+the largest path value, FP32 storage to half a unit in its last place (6e-8), strata
+bit for bit, values to 1e-15 (the other tests' bar)."""
 import numpy as np
 import pytest
 
@@ -28,3 +30,12 @@ def test_kle_wave_tiles(ctx, P, K, N, C, prec, bar):
         w = ctx.kle_paths(z, phi, P, K, C, c0=c0, precision=prec).cpu().numpy().astype(np.float64)
         ref = oracle.kle_paths(z.cpu().numpy(), phi.cpu().numpy(), P, K, c0, C)
         assert np.abs(w - ref).max() <= bar * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 255, 2047, 2048, 2049, 65536, 65537, 262144, 262145])
+@pytest.mark.parametrize("sampler", ["lhs", "srs"])
+def test_design_sizes(ctx, N, sampler):
+    st, z = ctx.lhs(seed=N, M=2, N=N, sampler=sampler)
+    ost, oz = oracle.lhs(N, 2, N, 0 if sampler == "lhs" else 1)
+    assert np.array_equal(st.cpu().numpy(), ost)
+    assert np.all(np.abs(z.cpu().numpy() - oz) <= 1e-15 * np.maximum(1.0, np.abs(oz)))
