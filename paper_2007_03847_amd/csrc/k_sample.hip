@@ -181,8 +181,9 @@ hipError_t launch_basis(int32_t kind, int32_t K, int64_t S, double T, double* ph
 // than 512 128 x 64 tiles take NB = 2 (6 processes, 333 samples, C = 77: 8.8 / 7.2; 1000
 // samples, C = 2001: 9.5 / 8.8), as do those whose 128-rows would leave a fifth of
 // the waves idle (5e4 samples, C = 25: 124 / 113; 1e5, C = 83: 170 / 165) and launches
-// beside an integrator (10 machines, 1e4 samples, 4000 steps: 9.56 / 9.10 ms per run);
-// the others NB = 4 (1e4 samples, C = 419, inputs from memory: 66.9 / 68.4).
+// beside an integrator (10 machines, 1e4 samples, 4000 steps: 9.46 / 9.01 ms per run);
+// the others NB = 4 (1e4 samples, C = 419, inputs from memory: 58.9 / 66.1, and 67.0
+// when a grid-stride loop's state made NB = 4 spill).
 // ---------------------------------------------------------------------------
 typedef double d4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
