@@ -488,7 +488,7 @@ def served_leg(ctx, fmc, workloads, oracle_mod, rates, n_max: int, seed: int = 1
     out = {"workload": "Poisson requests: 90% drawn uniformly from the 64 uneven classical "
                        "scenarios, 10% large flux-decay + IEEE type-1 requests (n=200, P=10, "
                        "T=30 s, N=5e4, K=100)",
-           "precision": "bf16x3", "time_chunk": {"classical": 200, "flux_decay": 12},
+           "precision": "bf16x3", "time_chunk": {"classical": 200, "classical_matrix_core": 100, "flux_decay": 12},
            "rates": []}
     # warm-up: one request of every size class and one short flux-decay request
     for i in (0, 17, 40):
