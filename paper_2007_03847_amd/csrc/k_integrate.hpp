@@ -682,6 +682,14 @@ __host__ __device__ constexpr bool rotated_form() {
   return sizeof(R) == 8;
 }
 
+// The path value v of a lane's process.  A lane without a process loads some other
+// path's, which may be an infinity or a NaN that its sigma = 0 would not remove: it
+// takes zero, in FP64 a number below 2^-1042 (the high word alone is selected).
+__device__ __forceinline__ float own_path(bool own, float v) { return own ? v : 0.0f; }
+__device__ __forceinline__ double own_path(bool own, double v) {
+  return __hiloint2double(own ? __double2hiint(v) : 0, __double2loint(v));
+}
+
 // (1 - cos d, sin d) turned by E0: dE = E0 (e^{j d} - 1) = -omc + j sd
 template <typename R>
 __device__ __forceinline__ void turn(R e0r, R e0i, R& omc, R& sd) {
@@ -1106,8 +1114,8 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
   // KLE path values of my processes: the two new stage columns of a step are
   // loaded two steps ahead (a step of a lone wave is shorter than the latency
   // of memory).
-  // A lane without a process reads the first process's path (its sigma is
-  // zero), the last steps read the last columns again: no lane branches.
+  // A lane without a process loads the first process's path of the first sample
+  // (see own_path), the last steps read the last columns again: no lane branches.
   R w0[PQ], w1[PQ], w2[PQ], n1[PQ], n2[PQ];
   auto column = [&](int64_t s) {  // first column of step s of this chunk
     return (2 * (s < a.s_end ? s : a.s_end - 1) - a.c_base) * colstride;
@@ -1116,9 +1124,9 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
     const int64_t c1 = column(a.s_begin + 1);
 #pragma unroll
     for (int r = 0; r < PQ; ++r) {
-      w0[r] = w[wofs[r]];
-      w1[r] = w[colstride + wofs[r]];
-      w2[r] = w[2 * colstride + wofs[r]];
+      w0[r] = own_path(own[r], w[wofs[r]]);
+      w1[r] = own_path(own[r], w[colstride + wofs[r]]);
+      w2[r] = own_path(own[r], w[2 * colstride + wofs[r]]);
       n1[r] = w[c1 + colstride + wofs[r]];
       n2[r] = w[c1 + 2 * colstride + wofs[r]];
     }
@@ -1145,8 +1153,8 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
       pub[3][r] = power(r, x4);
       yx[r] = x1 + dt6 * (((k1 + R(2) * k2) + R(2) * k3) + k4);
       w0[r] = w2[r];
-      w1[r] = n1[r];
-      w2[r] = n2[r];
+      w1[r] = own_path(own[r], n1[r]);
+      w2[r] = own_path(own[r], n2[r]);
       n1[r] = m1[r];
       n2[r] = m2[r];
     }

@@ -345,10 +345,14 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
   const R dt = a.dt, h2 = a.dt * R(0.5), dt6 = a.dt / R(6);
   const R hw2 = h2 * a.wb, hw = dt * a.wb, dw6 = dt6 * a.wb;
   const R inv_n = R(1) / (R)a.n_ref;
-  // the next step's path values load a step ahead; a lane without a process reads
-  // the first one's (its sigma is zero), the last step its own columns again
+  // the next step's path values load a step ahead; a lane without a process loads
+  // the first one's of the first sample (see own_path), the last step its own
+  // columns again
   R w0 = w[wofs], w1 = w[colstride + wofs], w2 = w[2 * colstride + wofs];
+  w0 = own_path(own, w0);
   for (int64_t s = a.s_begin; s < a.s_end; ++s) {
+    w1 = own_path(own, w1);
+    w2 = own_path(own, w2);
     const int64_t cn = 2 * (s + 1 < a.s_end ? s + 1 : s) - a.c_base;  // first column of the next step
     const R n1 = w[(cn + 1) * colstride + wofs], n2 = w[(cn + 2) * colstride + wofs];
     // the four stage values of my process (it does not see the machines)
