@@ -27,6 +27,7 @@
 
 #include <algorithm>
 
+#include "decor_plan.hpp"
 #include "fmc_internal.hpp"
 #include "fmc_runtime.hpp"
 
@@ -36,7 +37,6 @@ namespace {
 
 constexpr int kDcCovTile = 64;  // covariance tile edge (32x32 entries per wave)
 constexpr int kDcChunk = 32;    // samples per LDS stage of the covariance
-constexpr int kDcT = 16;        // matrix-core tile: block of the factor and of the substitution
 constexpr int kDcStride = 36;   // LDS row stride of the 32 samples (no bank conflicts)
 constexpr int kDcCholThreads = 512;
 // Longest rows ranked in LDS: two 32-bit words per entry, and with its value.
@@ -332,33 +332,29 @@ __global__ void __launch_bounds__(64) k_dc_whiten(int M, int64_t N, const double
       x[r] = ok && row < M ? X[(int64_t)row * N + n] - mean[row] : 0.0;
     }
   };
-  // L comes in batches of four blocks, the next one's loads (the next row of
-  // blocks' first batch at the end of a row) ahead of this one's products
-  constexpr int kB = 4;
-  auto load = [&](int b, int k0, double (&v)[kB][4]) {
-    const int row = kDcT * b + c;
+  // L comes in batches of four blocks (decor_plan.hpp), the next one's loads (the
+  // next row of blocks' first batch at the end of a row) ahead of this one's products;
+  // a single block row has nothing to load
+  constexpr int kB = kDcBatch;
+  auto load = [&](DcBatch t, double (&v)[kB][4]) {
+    const int row = kDcT * t.b + c;
     const double* lt = LT + (row < M ? row : 0) + (int64_t)g * M;
 #pragma unroll
     for (int q = 0; q < kB; ++q)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = k0 + q < b ? k0 + q : 0;  // (a block of the row; not used)
-        v[q][s] = lt[(int64_t)(kDcT * k + 4 * s) * M];
-      }
+      for (int s = 0; s < 4; ++s) v[q][s] = lt[(int64_t)dc_row(t.block(q), s, 0) * M];
   };
   d4v next;
   double cur[kB][4], nxt[kB][4];
   residual(0, next);
-  load(std::min(1, n_blk - 1), 0, cur);
+  if (dc_first_batch().b < n_blk) load(dc_first_batch(), cur);
   for (int b = 0; b < n_blk; ++b) {
     d4v acc = next, acc1 = {0.0, 0.0, 0.0, 0.0};
     if (b + 1 < n_blk) residual(b + 1, next);  // loads ahead of this block's products
     const bool in = kDcT * b + c < M;  // (a row past M read what LT does not hold)
     for (int k0 = 0; k0 < b; k0 += kB) {
-      if (k0 + kB < b)
-        load(b, k0 + kB, nxt);
-      else
-        load(b + 1 < n_blk ? b + 1 : b, 0, nxt);
+      const DcBatch nx = dc_next_batch({b, k0});
+      if (nx.b < n_blk) load(nx, nxt);  // uniform
 #pragma unroll
       for (int q = 0; q < kB; ++q) {
         if (k0 + q < b) {  // uniform
