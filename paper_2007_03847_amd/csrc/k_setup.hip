@@ -24,6 +24,39 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
   return make_double2((a.x * r + a.y) / d, (a.y * r - a.x) / d);
 }
 
+// Quotients by one b, as cdiv (Smith's algorithm): what depends on b alone is formed
+// once, and the three divisions are a reciprocal (the hardware's estimate and two
+// Newton steps) with the quotient corrected by its residual, which gives a / b = -1
+// exactly where a = -b, as a division does, at half its latency.  These divisions are
+// on the chain of every elimination step.
+struct Divisor {
+  double r, d, y;  // ratio of b's parts, Smith's denominator and its reciprocal
+  bool re;         // |Re b| >= |Im b|
+};
+__device__ __forceinline__ double recip(double b) {
+  double y = __builtin_amdgcn_rcp(b);
+  y = fma(fma(-b, y, 1.0), y, y);
+  return fma(fma(-b, y, 1.0), y, y);
+}
+__device__ __forceinline__ double quot(double a, double b, double y) {
+  const double q = a * y;
+  return fma(fma(-b, q, a), y, q);
+}
+__device__ __forceinline__ Divisor divisor(double2 b) {
+  Divisor v;
+  v.re = fabs(b.x) >= fabs(b.y);
+  const double hi = v.re ? b.x : b.y, lo = v.re ? b.y : b.x;
+  v.r = quot(lo, hi, recip(hi));
+  v.d = hi + lo * v.r;
+  v.y = recip(v.d);
+  return v;
+}
+__device__ __forceinline__ double2 quotient(double2 a, const Divisor& v) {
+  const double re = v.re ? a.x + a.y * v.r : a.x * v.r + a.y;
+  const double im = v.re ? a.y - a.x * v.r : a.y * v.r - a.x;
+  return make_double2(quot(re, v.d, v.y), quot(im, v.d, v.y));
+}
+
 // ---------------------------------------------------------------------------
 // Kron reduction (eq. 2 eliminated) of a small network: one workgroup of 512
 // threads, bound by the latency of its n_bus elimination steps.  The augmented
@@ -31,28 +64,21 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
 // it fits (n_bus W <= 4096).  Branches, loads and generators enter a row in
 // index order, so the sums are deterministic.  Gauss-Jordan elimination with
 // partial pivoting on rows that stay where they are: in step k every wave
-// finds the pivot (the largest max(|Re|, |Im|) of a_rk, to 18 bits, over the rows
+// finds the pivot (the largest max(|Re|, |Im|) of a_rk, to 14 bits, over the rows
 // not yet used, the lowest row on ties) by itself, and every element of the other rows and of the columns
 // beyond k is updated from the pivot row and column k, which the step leaves
 // alone, so one barrier per step suffices and no back substitution follows:
 // X = Y_BB^-1 Y_BA stands in the pivot rows and Y_red = Y_AA - Y_AB X.  39 buses
 // and 10 machines: 160 us with row exchanges, four barriers per step, a
-// complex division per element and a back substitution.
+// complex division per element and a back substitution; 49 us here.
+//
+// The pivot row is divided by the pivot, not multiplied by its reciprocal: of two
+// buses that only a line joins, the quotient is -1 and the second pivot cancels to
+// zero, so that such a network is refused; and the quotient of admittances of any
+// size stays in range.
 // ---------------------------------------------------------------------------
 constexpr int kKronLdsComplex = 4096;  // 64 KB of double2
 constexpr int kKronStage = 256;        // branches staged in LDS at a time
-
-// 1 / b = conj(b) / |b|^2, the reciprocal by the hardware's estimate and two Newton
-// steps (about 45 cycles on the chain of every elimination step, a division of
-// doubles takes 75 and Smith's algorithm two of them in a row).  |b|^2 stays far
-// inside the range of a double for admittances; a zero b gives NaN.
-__device__ __forceinline__ double2 cinv(double2 b) {
-  const double m = fma(b.x, b.x, b.y * b.y);
-  double r = __builtin_amdgcn_rcp(m);
-  r = fma(fma(-m, r, 1.0), r, r);
-  r = fma(fma(-m, r, 1.0), r, r);
-  return make_double2(b.x * r, -b.y * r);
-}
 
 // The largest key over the wave's lanes: rows of 16 by DPP, then the four rows.
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
@@ -115,14 +141,15 @@ __global__ void __launch_bounds__(512) k_kron(NetDev net, double2* __restrict__ 
   __syncthreads();
   // n_bus (n_bus + n_gen) <= 4096 means at most 63 buses: a lane per row
   bool used = lane >= nb;    // row `lane` has been a pivot row (each wave's own copy)
-  __shared__ int s_prow[64];  // pivot row and inverse pivot of column k
-  __shared__ double2 s_pinv[64];
+  __shared__ int s_prow[64];  // pivot row and pivot of column k
+  __shared__ double2 s_piv[64];
   for (int k = 0; k < nb; ++k) {
     unsigned key = 0;
     if (!used) {
+      // exponent and leading bits of the double; |a|^2 that underflows counts as zero
       const double2 v = A[lane * W + k];
-      const float m = (float)fmax(fabs(v.x), fabs(v.y));
-      if (m > 0.0f) key = (__float_as_uint(m) & ~63u) | (unsigned)(63 - lane);
+      const unsigned m = (unsigned)__double2hiint(fmax(fabs(v.x), fabs(v.y))) & ~63u;
+      if (fma(v.x, v.x, v.y * v.y) > 0.0) key = (m > 64u ? m : 64u) | (unsigned)(63 - lane);
     }
     key = wave_max_u32(key);
     if (key == 0) {  // uniform: every wave saw the same column
@@ -131,14 +158,15 @@ __global__ void __launch_bounds__(512) k_kron(NetDev net, double2* __restrict__ 
     }
     const int p = 63 - (int)(key & 63u);
     used |= p == lane;
-    const double2 inv = cinv(A[p * W + k]);
+    const double2 akk = A[p * W + k];
+    const Divisor by = divisor(akk);
     if (tid == 0) {
       s_prow[k] = p;
-      s_pinv[k] = inv;
+      s_piv[k] = akk;
     }
     // a thread takes a column and every 16th row (at most four)
     for (int c = k + 1 + tid % 32; c < W; c += 32) {
-      const double2 pc = cmul(A[p * W + c], inv);
+      const double2 pc = quotient(A[p * W + c], by);
       double fr[4], fi[4], vr[4], vi[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -159,7 +187,7 @@ __global__ void __launch_bounds__(512) k_kron(NetDev net, double2* __restrict__ 
     const int i = q / ng, g = q % ng, b = net.gen_bus[i];
     const double2 yg = make_double2(0.0, -1.0 / net.xdp[i]);
     double2 v = (i == g) ? yg : make_double2(0.0, 0.0);
-    const double2 x = cmul(A[s_prow[b] * W + nb + g], s_pinv[b]);
+    const double2 x = cdiv(A[s_prow[b] * W + nb + g], s_piv[b]);
     v = cadd(v, cmul(yg, x));  // -(Y_AB X), Y_AB = -yg
     Yred[q] = v;
   }
@@ -170,16 +198,19 @@ __global__ void __launch_bounds__(512) k_kron(NetDev net, double2* __restrict__ 
 // Large networks (the augmented system does not fit LDS): Kron's node
 // elimination on the full admittance matrix of the buses and the generator
 // internal nodes (W = n_bus + n_gen, buses first), kKronBlk buses at a time:
-// with D the block's diagonal part, Y_ij -= Y_ik D^-1 Y_kj for all remaining i, j.
+// with D the block's diagonal part, Y_ij -= Y_ik D^-1 Y_kj for all remaining i, j,
+// formed as (D^-1 S) (S^-1 Y_kj) with S the diagonal of D, so that both factors are
+// quotients of admittances (in range whatever their size, and exact for a bus that
+// one line joins to the rest: see the singular networks above).
 // After the last bus the generator block is Y_red.  The buses are eliminated in
 // index order without pivoting: the bus block of a network admittance matrix
 // whose series branches share one R/X ratio and whose shunts are loads and
 // transient reactances is diagonally dominant.  A zero pivot sets the status.
 //
 // Bound by the chain of blocks: one launch per block, in which every
-// workgroup forms D^-1 Y_kj of its 64 columns (again in each tile: cheaper than
+// workgroup forms (D^-1 S) (S^-1 Y_kj) of its 64 columns (again in each tile: cheaper than
 // another launch) and updates a tile of 32 x 64, and the workgroup of the next
-// block's diagonal part inverts it before it ends.  780 buses and 200
+// block's diagonal part forms its D^-1 S before it ends.  780 buses and 200
 // machines: 3.9 ms with a launch per bus (780 launches of 4.6 us).
 // ---------------------------------------------------------------------------
 constexpr int kKronBlk = 32;   // buses per elimination block = rows of a tile
@@ -234,12 +265,17 @@ __global__ void __launch_bounds__(64) k_kron_assemble(NetDev net, double2* __res
   if (lane == 0) row[r] = diag;
 }
 
-// Inverse of a kKronBlk x kKronBlk block by Gauss-Jordan without pivoting, 256
+// The scale S of a bus: its diagonal entry, or 1 where that is zero.
+__device__ __forceinline__ double2 kron_scale(double2 d) {
+  return d.x != 0.0 || d.y != 0.0 ? d : make_double2(1.0, 0.0);
+}
+
+// D^-1 S of a kKronBlk x kKronBlk block D by Gauss-Jordan without pivoting, 256
 // threads: thread t holds the entries (t / 8, t % 8 + 8 u), u = 0..3; the pivot row
 // and column of the next step pass through LDS (two buffers, one barrier per
 // step).  Entries past the block's kb rows are the identity's.
 struct KronInvLds {
-  double2 row[2][kKronBlk], col[2][kKronBlk];
+  double2 row[2][kKronBlk], col[2][kKronBlk], scale[kKronBlk];
 };
 __device__ __forceinline__ void kron_invert(double (&vr)[4], double (&vi)[4], int kb, KronInvLds& s,
                                             int* status) {
@@ -257,29 +293,32 @@ __device__ __forceinline__ void kron_invert(double (&vr)[4], double (&vi)[4], in
     }
   };
   publish(0);
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (jb + 8 * u == i) s.scale[i] = kron_scale(make_double2(vr[u], vi[u]));
   __syncthreads();
   for (int k = 0; k < kb; ++k) {
-    const double2 piv = s.row[k & 1][k], cik = s.col[k & 1][i];
+    const double2 piv = s.row[k & 1][k], cik = s.col[k & 1][i], sk = s.scale[k];
     if (!(piv.x != 0.0 || piv.y != 0.0) && threadIdx.x == 0) *status = -1;
-    const double2 inv = cinv(piv);
-    const double2 nc = cmul(make_double2(-cik.x, -cik.y), inv);  // -a_ik / a_kk
+    // 1 / a_kk in the pivot row, else -a_ik / a_kk; column k holds the inverse's, times s_k
+    const double2 f = quotient(i == k ? make_double2(1.0, 0.0) : make_double2(-cik.x, -cik.y), divisor(piv));
+    double2 fs = cmul(f, sk);
+    if (i == k && piv.x == sk.x && piv.y == sk.y) fs = make_double2(1.0, 0.0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = jb + 8 * u;
       const double2 akj = s.row[k & 1][j];
-      // a_ij - a_ik a_kj / a_kk; the pivot row is scaled, column k holds the inverse's
-      const double2 f = i == k ? inv : nc;
       const double2 p = cmul(f, akj);
       const double br = i == k ? 0.0 : vr[u], bi = i == k ? 0.0 : vi[u];
-      vr[u] = j == k ? f.x : br + p.x;
-      vi[u] = j == k ? f.y : bi + p.y;
+      vr[u] = j == k ? fs.x : br + p.x;
+      vi[u] = j == k ? fs.y : bi + p.y;
     }
     if (k + 1 < kb) publish(k + 1);
     __syncthreads();
   }
 }
 
-// The inverse of the first block's diagonal part (kb = its buses).
+// D^-1 S of the first block (kb = its buses).
 __global__ void __launch_bounds__(256) k_kron_first(const double2* __restrict__ A, int W, int kb,
                                                     double2* __restrict__ dinv, int* status) {
   __shared__ KronInvLds s;
@@ -299,12 +338,12 @@ __global__ void __launch_bounds__(256) k_kron_first(const double2* __restrict__ 
 
 // Elimination of the kb buses k0..k0 + kb - 1: tile (blockIdx.y, blockIdx.x) of
 // the trailing matrix (from row and column k1 = k0 + kb on).  dinv: the block's
-// inverse; dnext: receives the next block's (nbn buses, 0 after the last).
+// D^-1 S; dnext: receives the next block's (nbn buses, 0 after the last).
 __global__ void __launch_bounds__(256) k_kron_block(double2* __restrict__ A, int W, int k0, int kb,
                                                     int nbn, const double2* __restrict__ dinv,
                                                     double2* __restrict__ dnext, int* status) {
-  __shared__ double2 s_d[kKronBlk][kKronBlk];   // D^-1
-  __shared__ double2 s_t[kKronBlk][kKronCols];  // Y_kj of the tile's columns, then D^-1 Y_kj
+  __shared__ double2 s_d[kKronBlk][kKronBlk];   // D^-1 S
+  __shared__ double2 s_t[kKronBlk][kKronCols];  // S^-1 Y_kj of the tile's columns, then D^-1 Y_kj
   __shared__ double2 s_l[kKronBlk][kKronBlk];   // Y_ik of the tile's rows
   __shared__ KronInvLds s_inv;
   const int tid = threadIdx.x, k1 = k0 + kb;
@@ -317,7 +356,9 @@ __global__ void __launch_bounds__(256) k_kron_block(double2* __restrict__ A, int
   }
   for (int q = tid; q < kKronBlk * kKronCols; q += 256) {
     const int i = q / kKronCols, j = q % kKronCols;
-    s_t[i][j] = (i < kb && c0 + j < W) ? A[(int64_t)(k0 + i) * W + c0 + j] : zero;
+    s_t[i][j] = (i < kb && c0 + j < W) ? quotient(A[(int64_t)(k0 + i) * W + c0 + j],
+                                                  divisor(kron_scale(A[(int64_t)(k0 + i) * W + k0 + i])))
+                                       : zero;
   }
   __syncthreads();
   // thread: columns tx and tx + 32, rows 4 ty .. 4 ty + 3 of the tile
@@ -389,7 +430,7 @@ __global__ void __launch_bounds__(256) k_kron_extract(const double2* __restrict_
   Yred[q] = A[(int64_t)(nb + i) * W + nb + k];
 }
 
-// The work matrix, then two inverses of diagonal blocks (in turn).
+// The work matrix, then D^-1 S of two diagonal blocks (in turn).
 size_t kron_work_bytes(int n_bus, int n_gen) {
   const size_t W = (size_t)n_bus + n_gen;
   return (W * W + 2 * kKronBlk * kKronBlk) * sizeof(double2);
