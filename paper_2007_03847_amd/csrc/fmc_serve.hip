@@ -32,6 +32,7 @@
 
 #include "fmc_runtime.hpp"
 #include "serve_arena.hpp"
+#include "serve_lanes.hpp"
 
 namespace fmc {
 
@@ -250,6 +251,16 @@ void stage_inputs(Request& r, const fmc_system* s, const fmc_disturbance* d) {
 
 }  // namespace
 
+struct HipOps {  // of serve::Lanes
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  using Error = hipError_t;
+  static constexpr hipError_t kOk = hipSuccess;
+  static hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
+  static hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
+  static void sync(hipStream_t s) { (void)hipStreamSynchronize(s); }
+};
+
 struct ServeState {
   std::mutex mu;
   std::condition_variable cv_work, cv_done;
@@ -258,11 +269,9 @@ struct ServeState {
   serve::Arena arena;
   char* arena_base = nullptr;
   unsigned char* tick_dev = nullptr;  // upload region of a tick (outside the arena)
-  hipStream_t st = nullptr;
-  // lanes of a tick: st and lst (forked from st, joined back): the paths, then
-  // the size classes and the flux-decay integrators run side by side on them
-  hipStream_t lst[kLanes - 1] = {};
-  hipEvent_t lev[kLanes] = {};  // [0]: fork, [k]: lane k done
+  // lanes of a tick: the paths, then the size classes and the flux-decay
+  // integrators run side by side on them
+  serve::Lanes<HipOps, kLanes> ln;
   unsigned char* pin = nullptr;  // page-locked staging of a tick
   size_t pin_cap = 0;
   int n_cu = 0, bpc[kBatchClasses] = {};
@@ -336,7 +345,7 @@ int ensure_pin(ServeState* ss, size_t bytes) {
 // Upload a newly started request's inputs and enqueue its setup: network
 // reduction, operating point, packed coefficients, basis and design.
 int start_request(ServeState* ss, Request& r, size_t* pin_off) {
-  hipStream_t st = ss->st;
+  hipStream_t st = ss->ln.st;
   const size_t nb = r.sg.bytes.size();
   if (nb) {
     std::memcpy(ss->pin + *pin_off, r.sg.bytes.data(), nb);
@@ -375,7 +384,7 @@ int start_request(ServeState* ss, Request& r, size_t* pin_off) {
 // serving stream drained.
 int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<ReqP>& act,
              std::vector<ReqP>& finishing) {
-  hipStream_t st = ss->st;
+  hipStream_t st = ss->ln.st;
   const int na = (int)act.size();
   int64_t n_items = 0;  // items of the batched (classical) integrator
   for (auto& r : act)
@@ -398,28 +407,13 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
   std::vector<double> icost;
   icost.reserve(n_items);
   std::vector<std::pair<FdArgs, int64_t>> fd_launch;
-  auto lane = [&](int k) { return k == 0 ? st : ss->lst[k - 1]; };
-  auto fork = [&](int n) -> hipError_t {  // lanes 1 .. n - 1 after what st has
-    if (n < 2) return hipSuccess;
-    hipError_t e = hipEventRecord(ss->lev[0], st);
-    for (int k = 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(lane(k), ss->lev[0], 0);
-    return e;
-  };
-  auto join = [&](int n) -> hipError_t {  // st after lanes 1 .. n - 1
-    hipError_t e = hipSuccess;
-    for (int k = 1; k < n && e == hipSuccess; ++k) {
-      e = hipEventRecord(ss->lev[k], lane(k));
-      if (e == hipSuccess) e = hipStreamWaitEvent(st, ss->lev[k], 0);
-    }
-    return e;
-  };
   const int path_lanes = std::min(na, kLanes);
-  SCHK(fork(path_lanes));
+  SCHK(ss->ln.fork(path_lanes));
   for (int i = 0; i < na; ++i) {
     Request& r = *act[i];
     const int64_t s0 = r.s_next, s1 = std::min<int64_t>(r.S, s0 + r.Sc);
     const int64_t cols = 2 * (s1 - s0) + 1;
-    const hipStream_t ks = lane(i % path_lanes);
+    const hipStream_t ks = ss->ln.lane(i % path_lanes);
     if (r.par.precision == FMC_F32)
       SCHK(launch_kle_f64_to_f32(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, ks));
     else
@@ -498,7 +492,7 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
     r.s_next = s1;
     if (s1 == r.S) finishing.push_back(act[i]);
   }
-  SCHK(join(path_lanes));
+  SCHK(ss->ln.join(path_lanes));
   for (auto& o : order)
     std::stable_sort(o.begin(), o.end(), [&](int32_t x, int32_t y) { return icost[x] > icost[y]; });
   std::vector<int32_t> flat;
@@ -539,20 +533,20 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
   std::stable_sort(cls.begin(), cls.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
   const int class_lanes = std::min((int)cls.size(), kLanes);
   double load[kLanes] = {};
-  SCHK(fork(class_lanes));
+  SCHK(ss->ln.fork(class_lanes));
   for (const auto& [cost, k] : cls) {
     const int x = (int)(std::min_element(load, load + class_lanes) - load);
     load[x] += cost;
     if (k == kBatchClasses) {
-      for (auto& f : fd_launch) SCHK(launch_rk4_fd(f.first, f.second, lane(x)));
+      for (auto& f : fd_launch) SCHK(launch_rk4_fd(f.first, f.second, ss->ln.lane(x)));
       continue;
     }
     const int64_t nk = off[k + 1] - off[k];
     const int grid = (int)std::min<int64_t>(nk, (int64_t)ss->bpc[k] * ss->n_cu);
     BatchArgs b{args_d, items_d, order_d + off[k], (int32_t)nk, heads + k};
-    SCHK(launch_persistent(k, b, grid, lane(x)));
+    SCHK(launch_persistent(k, b, grid, ss->ln.lane(x)));
   }
-  SCHK(join(class_lanes));
+  SCHK(ss->ln.join(class_lanes));
   // rows completed by this tick: s0+1..s1 (and row 0 in a request's first chunk)
   for (int i = 0; i < na; ++i) {
     Request& r = *act[i];
@@ -650,8 +644,7 @@ void server_loop(Context* c, ServeState* ss) {
     }
     if (act.empty()) continue;
     std::vector<ReqP> finishing;
-    const int rc = run_tick(ss, fresh, act, finishing);
-    if (rc) (void)hipStreamSynchronize(ss->st);
+    const int rc = ss->ln.run([&] { return run_tick(ss, fresh, act, finishing); });
     std::lock_guard<std::mutex> lk(ss->mu);
     if (rc) {
       // a failed tick ends every active request with its status
@@ -689,12 +682,12 @@ int ensure_server(Context* c) {
     return fail(FMC_EDEVICE, "hipGetDeviceProperties failed");
   ss->n_cu = prop.multiProcessorCount;
   for (int k = 0; k < kBatchClasses; ++k) ss->bpc[k] = persistent_blocks_per_cu(k);
-  if (hipStreamCreateWithFlags(&ss->st, hipStreamNonBlocking) != hipSuccess)
+  if (hipStreamCreateWithFlags(&ss->ln.st, hipStreamNonBlocking) != hipSuccess)
     return fail(FMC_EDEVICE, "cannot create the serving stream");
-  for (auto& l : ss->lst)
+  for (auto& l : ss->ln.side)
     if (hipStreamCreateWithFlags(&l, hipStreamNonBlocking) != hipSuccess)
       return fail(FMC_EDEVICE, "cannot create the serving streams");
-  for (auto& e : ss->lev)
+  for (auto& e : ss->ln.ev)
     if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
       return fail(FMC_EDEVICE, "cannot create the serving events");
   c->serve = ss.release();
@@ -726,16 +719,11 @@ void serve_shutdown(Context* c) {
   }
   ss->cv_work.notify_all();
   if (ss->th.joinable()) ss->th.join();
-  if (ss->st) {
-    (void)hipStreamSynchronize(ss->st);
-    (void)hipStreamDestroy(ss->st);
-  }
-  for (auto& l : ss->lst)
-    if (l) {
-      (void)hipStreamSynchronize(l);
-      (void)hipStreamDestroy(l);
-    }
-  for (auto& e : ss->lev)
+  ss->ln.drain();
+  if (ss->ln.st) (void)hipStreamDestroy(ss->ln.st);
+  for (auto& l : ss->ln.side)
+    if (l) (void)hipStreamDestroy(l);
+  for (auto& e : ss->ln.ev)
     if (e) (void)hipEventDestroy(e);
   if (ss->pin) (void)hipHostFree(ss->pin);
   delete ss;
