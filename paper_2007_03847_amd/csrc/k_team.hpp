@@ -143,6 +143,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
   constexpr bool ROT = rotated_form<R>();
   R jr[2], ji[2], res[2], dmp[2], e0r[2], e0i[2], inv2h[2];
   bool live[2], on[2];
+  int live_mask[2];
   int pq[2];         // the first process at the machine, PM if none
   R bin[2];          // the machine's injection factor
   bool more = false;  // a machine of this wave has several processes
@@ -159,6 +160,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
     inv2h[q] = ROT ? R(1) : (in ? cf[Lp.inv2h() + m] : R(0));
     on[q] = m < n;
     live[q] = in && (cf[Lp.c0() + m] != R(0) || cf[Lp.s0() + m] != R(0));  // in service
+    live_mask[q] = lane_mask(live[q]);
     pq[q] = PM;
     bin[q] = R(0);
     for (int p = PM - 1; p >= 0; --p)
@@ -172,6 +174,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
   // my process: 4 wv + g of trajectory t
   const int pr = 4 * wv + g;
   const bool own = pr < P;
+  const int own_mask = lane_mask(own);
   const R theta = own ? cf[Lp.theta() + pr] : R(0), sigma = own ? cf[Lp.sigma() + pr] : R(0);
   const int64_t wofs = own ? (int64_t)pr * N + ns : 0, colstride = (int64_t)P * N;
   for (int q = tid; q < TW * XB * 2 * (PM + 1) * kTeamT; q += TPB) (&S.XI[0][0][0][0][0])[q] = R(0);
@@ -290,7 +293,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
       __syncthreads();  // every wave has read the previous pair
     else
       buf ^= 1;
-    rotation_stages<R, 2, 2>(d, live, sd, omc);
+    rotation_stages<R, 2, 2>(d, live, live_mask, sd, omc);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if constexpr (!ROT) {
@@ -299,7 +302,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
       }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        // a machine without EMF has a zero column of Z, whatever its angle has become
+        // a machine without EMF has a zero column of Z and turns by zero
         X[buf][h][16 * wv + 4 * g + 2 * q][t] = omc[h][q];
         X[buf][h][16 * wv + 4 * g + 2 * q + 1][t] = sd[h][q];
       }
@@ -346,13 +349,13 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
   const R hw2 = h2 * a.wb, hw = dt * a.wb, dw6 = dt6 * a.wb;
   const R inv_n = R(1) / (R)a.n_ref;
   // the next step's path values load a step ahead; a lane without a process loads
-  // the first one's of the first sample (see own_path), the last step its own
-  // columns again
+  // the first one's of the first sample and masks it (its sigma is zero, that path
+  // may not be finite), the last step its own columns again
   R w0 = w[wofs], w1 = w[colstride + wofs], w2 = w[2 * colstride + wofs];
-  w0 = own_path(own, w0);
+  w0 = masked(own_mask, w0);
   for (int64_t s = a.s_begin; s < a.s_end; ++s) {
-    w1 = own_path(own, w1);
-    w2 = own_path(own, w2);
+    w1 = masked(own_mask, w1);
+    w2 = masked(own_mask, w2);
     const int64_t cn = 2 * (s + 1 < a.s_end ? s + 1 : s) - a.c_base;  // first column of the next step
     const R n1 = w[(cn + 1) * colstride + wofs], n2 = w[(cn + 2) * colstride + wofs];
     // the four stage values of my process (it does not see the machines)
