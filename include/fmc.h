@@ -413,7 +413,8 @@ int fmc_run_batch(fmc_context *ctx, int32_t n, const fmc_scenario *scen, fmc_out
 /* Served form (continuous batching).  A server thread of the context runs
  * every admitted request together: each tick rebuilds the next time chunk of
  * KLE paths (par->time_chunk steps, 0: 200, or 100 on the FP32 matrix-core
- * variants) of every active request and runs
+ * variants, which take two such chunks in a tick with a flux-decay request) of
+ * every active request and runs
  * all of their work items in one persistent integrator launch per size class,
  * with the trajectory state resident on the device between ticks; requests
  * submitted meanwhile join at the next tick.  A request's result depends only

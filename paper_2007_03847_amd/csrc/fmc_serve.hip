@@ -59,7 +59,8 @@ struct Request {
   fmc_outputs out{};
   int n = 0, P = 0, K = 0, V = 0;
   int64_t N = 0, S = 0, C = 0, M = 0, Sc = 0;
-  int64_t s_prev = 0, s_next = 0;  // steps of the last tick: [s_prev, s_next)
+  bool half = false;               // Sc is half the default chunk (plan_request)
+  int64_t s_prev = 0, s_next = 0;  // steps of the last chunk: [s_prev, s_next)
   bool has_Y = false, inf_bus = false;
   int32_t n_bus = 0;
   double f0 = 60.0, V_inf = 0.0;
@@ -187,9 +188,9 @@ int plan_request(Request& r, const fmc_system* s, const fmc_disturbance* d, cons
   // A chunk the caller sets is kept, with items of 64.
   int64_t min_tiles = 1;
   if (r.bv.prod == 1) {
-    const bool half = p->time_chunk <= 0 && r.Sc >= 40;
-    if (half) r.Sc = (r.Sc + 1) / 2;
-    min_tiles = (half ? 32 : 64) / r.bv.TB;
+    r.half = p->time_chunk <= 0 && r.Sc >= 40;
+    if (r.half) r.Sc = (r.Sc + 1) / 2;
+    min_tiles = (r.half ? 32 : 64) / r.bv.TB;
   }
   r.tiles = (r.N + r.bv.TB - 1) / r.bv.TB;
   r.cost_tile = (double)r.S * r.bv.TB * (8.0 * r.bv.NG * r.bv.NG + 45.0 * r.bv.NG + 4.0 * r.P);
@@ -382,17 +383,29 @@ int start_request(ServeState* ss, Request& r, size_t* pin_off) {
 // One tick: start the fresh requests, then the next time chunk of every active
 // request; finished requests are merged and copied out.  Ends with the
 // serving stream drained.
+//
+// A tick lasts as long as its flux-decay requests' chunk (12 steps of 200
+// machines and 5e4 samples: 13 ms), so beside one a request with the halved default
+// chunk takes two of them in a tick, the second while the flux-decay integrators still
+// run.  1200 steps of 3000 samples beside that request, 12 / 30 / 48 machines: 104 /
+// 105 / 106 ms, with one chunk in a tick 182 / 182 / 183 (and 107 / 120 / 165 when
+// the chunk was 200 steps on slower integrators).  The chunk itself stays, and
+// with it the bits of the result.
 int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<ReqP>& act,
              std::vector<ReqP>& finishing) {
   hipStream_t st = ss->ln.st;
   const int na = (int)act.size();
-  int64_t n_items = 0;  // items of the batched (classical) integrator
-  for (auto& r : act)
+  std::vector<Request*> cl, fd;  // classical machines, flux decay
+  int64_t n_items = 0;           // items of the batched (classical) integrator
+  for (auto& r : act) {
+    (r->fd ? fd : cl).push_back(r.get());
     if (!r->fd) n_items += r->n_items;
-  const size_t up_bytes = al(sizeof(IntegArgs<float>) * na) + al(sizeof(BatchItem) * n_items) +
+  }
+  const bool beside = !cl.empty() && !fd.empty();
+  const size_t up_bytes = al(sizeof(IntegArgs<float>) * cl.size()) + al(sizeof(BatchItem) * n_items) +
                           al(sizeof(int32_t) * n_items);
   if (up_bytes + kAlign > kTickBytes) return fail(FMC_EINVAL, "too many work items in one tick");
-  size_t pin_need = up_bytes + al(64) * na;
+  size_t pin_need = (beside ? 2 : 1) * up_bytes + al(64) * na;
   for (auto& r : fresh) pin_need += al(r->sg.bytes.size());
   int rc = ensure_pin(ss, pin_need);
   if (rc) return rc;
@@ -400,156 +413,26 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
   for (auto& r : fresh)
     if ((rc = start_request(ss, *r, &pin_off))) return rc;
 
-  std::vector<IntegArgs<float>> args(na);
-  std::vector<BatchItem> items;
-  items.reserve(n_items);
-  std::vector<std::vector<int32_t>> order(kBatchClasses);
-  std::vector<double> icost;
-  icost.reserve(n_items);
-  std::vector<std::pair<FdArgs, int64_t>> fd_launch;
-  const int path_lanes = std::min(na, kLanes);
-  SCHK(ss->ln.fork(path_lanes));
-  for (int i = 0; i < na; ++i) {
-    Request& r = *act[i];
-    const int64_t s0 = r.s_next, s1 = std::min<int64_t>(r.S, s0 + r.Sc);
-    const int64_t cols = 2 * (s1 - s0) + 1;
-    const hipStream_t ks = ss->ln.lane(i % path_lanes);
-    if (r.par.precision == FMC_F32)
-      SCHK(launch_kle_f64_to_f32(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, ks));
-    else
-      SCHK(launch_kle_bf16x3(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * s0, r.w, ks));
-    if (r.fd) {
-      FdArgs f{};
-      f.coef = r.coef;
-      f.ap = r.fdap;
-      f.ap16 = fd_bf16_product(&r.par) ? (const void*)r.fdap : nullptr;
-      f.n_padk = 32 * ((r.n + 31) / 32);
-      f.w = r.w;
-      f.state = r.state;
-      f.xstate = r.xstate;
-      f.off = r.fdblk + FdLayout{r.n}.off();
-      f.nonfinite = r.cnt;
-      f.first_bad = (long long*)r.cnt + 1;
-      f.rows = r.part;
-      f.row_stride = (r.Sc + 1) * r.V;
-      f.row_base = s0;
-      f.n = r.n;
-      f.P = r.P;
-      f.V = r.V;
-      f.n_pad = r.n_pad;
-      f.N = r.N;
-      f.S = r.S;
-      f.s_begin = s0;
-      f.s_end = s1;
-      f.c_base = 2 * s0;
-      f.tiles = r.tiles;
-      f.tiles_per_item = r.tiles_per_item;
-      f.dt = (float)r.par.dt;
-      f.wb = (float)(2.0 * M_PI * r.f0);
-      f.recenter = r.inf_bus ? 0 : 1;
-      fd_launch.push_back({f, r.n_items});
-      r.s_prev = s0;
-      r.s_next = s1;
-      if (s1 == r.S) finishing.push_back(act[i]);
-      continue;
+  // the next chunk [s_prev, s_next] of the requests v: its paths, on `lanes` lanes
+  auto paths = [&](const std::vector<Request*>& v, int lanes) -> int {
+    lanes = std::min((int)v.size(), lanes);
+    SCHK(ss->ln.fork(lanes));
+    for (size_t i = 0; i < v.size(); ++i) {
+      Request& r = *v[i];
+      r.s_prev = r.s_next;
+      r.s_next = std::min<int64_t>(r.S, r.s_prev + r.Sc);
+      const int64_t cols = 2 * (r.s_next - r.s_prev) + 1;
+      const hipStream_t ks = ss->ln.lane((int)i % lanes);
+      if (r.par.precision == FMC_F32)
+        SCHK(launch_kle_f64_to_f32(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * r.s_prev, r.w, ks));
+      else
+        SCHK(launch_kle_bf16x3(r.zeta, r.phi, r.C, r.P, r.K, r.N, cols, 2 * r.s_prev, r.w, ks));
     }
-    IntegArgs<float>& a = args[i];
-    a.coef = r.coef;
-    a.w = r.w;
-    a.state = r.state;
-    a.partial = nullptr;
-    a.delta0 = r.canon + CanonLayout{r.n, r.P}.delta0();
-    a.traj_slot = nullptr;
-    a.traj = nullptr;
-    a.nonfinite = r.cnt;
-    a.first_bad = (long long*)r.cnt + 1;
-    a.n = r.n;
-    a.P = r.P;
-    a.V = r.V;
-    a.N = r.N;
-    a.S = r.S;
-    a.s_begin = s0;
-    a.s_end = s1;
-    a.c_base = 2 * s0;
-    a.lanes = r.tiles * 64 * 4;
-    a.dt = (float)r.par.dt;
-    a.wb = (float)(2.0 * M_PI * r.f0);
-    a.recenter = r.inf_bus ? 0 : 1;
-    a.n_ref = r.n;
-    const double frac = (double)(s1 - s0) / (double)r.S;
-    for (int64_t k = 0; k < r.n_items; ++k) {
-      BatchItem it;
-      it.rows = r.part + k * (r.Sc + 1) * r.V;  // this chunk's rows (steps s0..s1)
-      it.tile0 = k * r.tiles_per_item;
-      it.tile1 = std::min<int64_t>(r.tiles, it.tile0 + r.tiles_per_item);
-      it.scen = i;
-      it.variant = r.vid;
-      order[r.bv.cls].push_back((int32_t)items.size());
-      icost.push_back(r.cost_tile * frac * (double)(it.tile1 - it.tile0));
-      items.push_back(it);
-    }
-    r.s_prev = s0;
-    r.s_next = s1;
-    if (s1 == r.S) finishing.push_back(act[i]);
-  }
-  SCHK(ss->ln.join(path_lanes));
-  for (auto& o : order)
-    std::stable_sort(o.begin(), o.end(), [&](int32_t x, int32_t y) { return icost[x] > icost[y]; });
-  std::vector<int32_t> flat;
-  flat.reserve(n_items);
-  int64_t off[kBatchClasses + 1];
-  for (int k = 0; k < kBatchClasses; ++k) {
-    off[k] = (int64_t)flat.size();
-    flat.insert(flat.end(), order[k].begin(), order[k].end());
-  }
-  off[kBatchClasses] = (int64_t)flat.size();
-
-  // tick upload: [heads | args | items | order]
-  unsigned char* hp = ss->pin + pin_off;
-  unsigned char* dp = ss->tick_dev + kAlign;
-  size_t o = 0;
-  std::memcpy(hp + o, args.data(), sizeof(IntegArgs<float>) * na);
-  const IntegArgs<float>* args_d = (const IntegArgs<float>*)(dp + o);
-  o += al(sizeof(IntegArgs<float>) * na);
-  std::memcpy(hp + o, items.data(), sizeof(BatchItem) * n_items);
-  const BatchItem* items_d = (const BatchItem*)(dp + o);
-  o += al(sizeof(BatchItem) * n_items);
-  std::memcpy(hp + o, flat.data(), sizeof(int32_t) * n_items);
-  const int32_t* order_d = (const int32_t*)(dp + o);
-  o += al(sizeof(int32_t) * n_items);
-  SCHK(hipMemcpyAsync(dp, hp, o, hipMemcpyHostToDevice, st));
-  pin_off += o;
-  int32_t* heads = (int32_t*)ss->tick_dev;
-  SCHK(launch_fill_i64((int64_t*)heads, 0, kBatchClasses / 2, st));
-  // the size classes with items, the costliest first onto the lane with the least
-  // work; the flux-decay integrators, one after another, count as a class
-  std::vector<std::pair<double, int>> cls;
-  for (int k = 0; k < kBatchClasses; ++k) {
-    double cost = 0.0;
-    for (int32_t q : order[k]) cost += icost[q];
-    if (off[k + 1] > off[k]) cls.push_back({cost, k});
-  }
-  if (!fd_launch.empty()) cls.push_back({HUGE_VAL, kBatchClasses});
-  std::stable_sort(cls.begin(), cls.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-  const int class_lanes = std::min((int)cls.size(), kLanes);
-  double load[kLanes] = {};
-  SCHK(ss->ln.fork(class_lanes));
-  for (const auto& [cost, k] : cls) {
-    const int x = (int)(std::min_element(load, load + class_lanes) - load);
-    load[x] += cost;
-    if (k == kBatchClasses) {
-      for (auto& f : fd_launch) SCHK(launch_rk4_fd(f.first, f.second, ss->ln.lane(x)));
-      continue;
-    }
-    const int64_t nk = off[k + 1] - off[k];
-    const int grid = (int)std::min<int64_t>(nk, (int64_t)ss->bpc[k] * ss->n_cu);
-    BatchArgs b{args_d, items_d, order_d + off[k], (int32_t)nk, heads + k};
-    SCHK(launch_persistent(k, b, grid, ss->ln.lane(x)));
-  }
-  SCHK(ss->ln.join(class_lanes));
-  // rows completed by this tick: s0+1..s1 (and row 0 in a request's first chunk)
-  for (int i = 0; i < na; ++i) {
-    Request& r = *act[i];
+    SCHK(ss->ln.join(lanes));
+    return FMC_OK;
+  };
+  // the rows completed by the chunk of r: s_prev + 1 .. s_next (and row 0 in the first)
+  auto merge = [&](Request& r) -> int {
     const int64_t first = r.s_prev == 0 ? 0 : r.s_prev + 1, rows = r.s_next - first + 1;
     // FP64 offsets added back: delta0 (classical), or the 6n operating-point
     // values of the flux-decay states
@@ -560,9 +443,165 @@ int run_tick(ServeState* ss, const std::vector<ReqP>& fresh, const std::vector<R
     SCHK(launch_stats_merge_rows(r.part + (first - r.s_prev) * r.V, (r.Sc + 1) * r.V, groups, group,
                                  r.N, rows, r.V, n_off, r.par.ddof, offs, r.mean + first * r.V,
                                  r.var + first * r.V, st));
-  }
-  for (auto& rp : finishing) {
+    return FMC_OK;
+  };
+  // the chunk of the classical requests v on `lanes` lanes, and its merge
+  auto classical = [&](const std::vector<Request*>& v, int lanes) -> int {
+    std::vector<IntegArgs<float>> args(v.size());
+    std::vector<BatchItem> items;
+    std::vector<std::vector<int32_t>> order(kBatchClasses);
+    std::vector<double> icost;
+    for (size_t i = 0; i < v.size(); ++i) {
+      Request& r = *v[i];
+      IntegArgs<float>& a = args[i];
+      a.coef = r.coef;
+      a.w = r.w;
+      a.state = r.state;
+      a.partial = nullptr;
+      a.delta0 = r.canon + CanonLayout{r.n, r.P}.delta0();
+      a.traj_slot = nullptr;
+      a.traj = nullptr;
+      a.nonfinite = r.cnt;
+      a.first_bad = (long long*)r.cnt + 1;
+      a.n = r.n;
+      a.P = r.P;
+      a.V = r.V;
+      a.N = r.N;
+      a.S = r.S;
+      a.s_begin = r.s_prev;
+      a.s_end = r.s_next;
+      a.c_base = 2 * r.s_prev;
+      a.lanes = r.tiles * 64 * 4;
+      a.dt = (float)r.par.dt;
+      a.wb = (float)(2.0 * M_PI * r.f0);
+      a.recenter = r.inf_bus ? 0 : 1;
+      a.n_ref = r.n;
+      const double frac = (double)(r.s_next - r.s_prev) / (double)r.S;
+      for (int64_t k = 0; k < r.n_items; ++k) {
+        BatchItem it;
+        it.rows = r.part + k * (r.Sc + 1) * r.V;  // this chunk's rows
+        it.tile0 = k * r.tiles_per_item;
+        it.tile1 = std::min<int64_t>(r.tiles, it.tile0 + r.tiles_per_item);
+        it.scen = (int32_t)i;
+        it.variant = r.vid;
+        order[r.bv.cls].push_back((int32_t)items.size());
+        icost.push_back(r.cost_tile * frac * (double)(it.tile1 - it.tile0));
+        items.push_back(it);
+      }
+    }
+    for (auto& o : order)
+      std::stable_sort(o.begin(), o.end(), [&](int32_t x, int32_t y) { return icost[x] > icost[y]; });
+    std::vector<int32_t> flat;
+    flat.reserve(items.size());
+    int64_t off[kBatchClasses + 1];
+    for (int k = 0; k < kBatchClasses; ++k) {
+      off[k] = (int64_t)flat.size();
+      flat.insert(flat.end(), order[k].begin(), order[k].end());
+    }
+    off[kBatchClasses] = (int64_t)flat.size();
+
+    // upload: [heads | args | items | order]; lane 0 has waited for the last
+    // upload's readers
+    unsigned char* hp = ss->pin + pin_off;
+    unsigned char* dp = ss->tick_dev + kAlign;
+    size_t o = 0;
+    std::memcpy(hp + o, args.data(), sizeof(IntegArgs<float>) * args.size());
+    const IntegArgs<float>* args_d = (const IntegArgs<float>*)(dp + o);
+    o += al(sizeof(IntegArgs<float>) * args.size());
+    std::memcpy(hp + o, items.data(), sizeof(BatchItem) * items.size());
+    const BatchItem* items_d = (const BatchItem*)(dp + o);
+    o += al(sizeof(BatchItem) * items.size());
+    std::memcpy(hp + o, flat.data(), sizeof(int32_t) * flat.size());
+    const int32_t* order_d = (const int32_t*)(dp + o);
+    o += al(sizeof(int32_t) * flat.size());
+    SCHK(hipMemcpyAsync(dp, hp, o, hipMemcpyHostToDevice, st));
+    pin_off += o;
+    int32_t* heads = (int32_t*)ss->tick_dev;
+    SCHK(launch_fill_i64((int64_t*)heads, 0, kBatchClasses / 2, st));
+    // the size classes with items, the costliest first onto the lane with the
+    // least work
+    std::vector<std::pair<double, int>> cls;
+    for (int k = 0; k < kBatchClasses; ++k) {
+      double cost = 0.0;
+      for (int32_t q : order[k]) cost += icost[q];
+      if (off[k + 1] > off[k]) cls.push_back({cost, k});
+    }
+    std::stable_sort(cls.begin(), cls.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+    lanes = std::min((int)cls.size(), lanes);
+    double load[kLanes] = {};
+    SCHK(ss->ln.fork(lanes));
+    for (const auto& [cost, k] : cls) {
+      const int x = (int)(std::min_element(load, load + lanes) - load);
+      load[x] += cost;
+      const int64_t nk = off[k + 1] - off[k];
+      const int grid = (int)std::min<int64_t>(nk, (int64_t)ss->bpc[k] * ss->n_cu);
+      BatchArgs b{args_d, items_d, order_d + off[k], (int32_t)nk, heads + k};
+      SCHK(launch_persistent(k, b, grid, ss->ln.lane(x)));
+    }
+    SCHK(ss->ln.join(lanes));
+    for (Request* r : v) {
+      const int e = merge(*r);
+      if (e) return e;
+    }
+    return FMC_OK;
+  };
+
+  std::vector<Request*> all;
+  for (auto& r : act) all.push_back(r.get());
+  if ((rc = paths(all, kLanes))) return rc;
+  // the flux-decay integrators, one after another: beside classical requests on the
+  // last lane, which these then leave alone
+  const hipStream_t fs = ss->ln.lane(beside ? kLanes - 1 : 0);
+  if (beside) SCHK(ss->ln.fork(kLanes));
+  for (Request* rp : fd) {
     Request& r = *rp;
+    FdArgs f{};
+    f.coef = r.coef;
+    f.ap = r.fdap;
+    f.ap16 = fd_bf16_product(&r.par) ? (const void*)r.fdap : nullptr;
+    f.n_padk = 32 * ((r.n + 31) / 32);
+    f.w = r.w;
+    f.state = r.state;
+    f.xstate = r.xstate;
+    f.off = r.fdblk + FdLayout{r.n}.off();
+    f.nonfinite = r.cnt;
+    f.first_bad = (long long*)r.cnt + 1;
+    f.rows = r.part;
+    f.row_stride = (r.Sc + 1) * r.V;
+    f.row_base = r.s_prev;
+    f.n = r.n;
+    f.P = r.P;
+    f.V = r.V;
+    f.n_pad = r.n_pad;
+    f.N = r.N;
+    f.S = r.S;
+    f.s_begin = r.s_prev;
+    f.s_end = r.s_next;
+    f.c_base = 2 * r.s_prev;
+    f.tiles = r.tiles;
+    f.tiles_per_item = r.tiles_per_item;
+    f.dt = (float)r.par.dt;
+    f.wb = (float)(2.0 * M_PI * r.f0);
+    f.recenter = r.inf_bus ? 0 : 1;
+    SCHK(launch_rk4_fd(f, r.n_items, fs));
+  }
+  if (!cl.empty() && (rc = classical(cl, beside ? kLanes - 1 : kLanes))) return rc;
+  if (beside) {
+    std::vector<Request*> again;
+    for (Request* r : cl)
+      if (r->half && r->s_next < r->S) again.push_back(r);
+    if (!again.empty()) {
+      if ((rc = paths(again, kLanes - 1))) return rc;
+      if ((rc = classical(again, kLanes - 1))) return rc;
+    }
+    SCHK(ss->ln.join(kLanes));
+  }
+  for (Request* r : fd)
+    if ((rc = merge(*r))) return rc;
+  for (auto& rp : act) {
+    Request& r = *rp;
+    if (r.s_next < r.S) continue;
+    finishing.push_back(rp);
     const size_t sv = (size_t)(r.S + 1) * r.V * 8;
     const hipMemcpyKind kind =
         r.out.mem_kind == FMC_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
