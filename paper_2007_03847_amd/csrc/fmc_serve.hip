@@ -40,7 +40,7 @@ namespace {
 
 using Clock = std::chrono::steady_clock;
 
-constexpr size_t kTickBytes = size_t(32) << 20;  // per-tick upload region (args, items, orders)
+constexpr size_t kTickBytes = size_t(16) << 20;  // upload region of a chunk (args, items, orders)
 constexpr int64_t kMaxItems = 1024;             // work items per request
 constexpr int kMaxActive = 256;                 // requests admitted at once
 // A process has four hardware queues; launches on more streams than that wait for
@@ -50,6 +50,9 @@ constexpr int kLanes = 4;
 constexpr int64_t kDefaultChunk = 200;          // steps per tick
 constexpr int64_t kDefaultChunkFd = 12;         // steps per tick of a flux-decay request
 constexpr size_t kAlign = serve::kAlign;
+static_assert(kMaxActive * (kMaxItems * (sizeof(BatchItem) + sizeof(int32_t)) + sizeof(IntegArgs<float>)) +
+                      4 * kAlign <= kTickBytes,
+              "a chunk of every admitted request fits the upload region");
 
 size_t al(size_t x) { return serve::align_up(x); }
 
