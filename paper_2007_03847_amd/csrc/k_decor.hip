@@ -680,6 +680,9 @@ struct CovPlan {
   }
 };
 
+// Rows that a workgroup ranks in LDS; longer ones take the buffers below.
+constexpr bool ranked_in_lds(int64_t N) { return N <= kDcRowMax; }
+
 struct RankBufs {
   double2* lohi;
   int32_t *bkt, *off, *fill, *perm;
@@ -694,7 +697,7 @@ void launch_rank(int32_t M, int64_t N, const double* V, const RankBufs& b, int32
                        words + (size_t)N * sizeof(double), st, (int)N, V, R, inv);
     return;
   }
-  if (N <= kDcRowMax) {
+  if (ranked_in_lds(N)) {
     hipLaunchKernelGGL(k_dc_rank_row<false>, dim3((unsigned)M), dim3(kDcRankThreads), words, st,
                        (int)N, V, R, inv);
     return;
@@ -717,7 +720,7 @@ void launch_rank(int32_t M, int64_t N, const double* V, const RankBufs& b, int32
 
 size_t decorrelate_workspace(int32_t M, int64_t N) {
   const CovPlan cp(M, N);
-  return (size_t)M * N * (sizeof(double) + 7 * sizeof(int32_t)) +
+  return (size_t)M * N * (sizeof(double) + (ranked_in_lds(N) ? 3 : 7) * sizeof(int32_t)) +
          ((size_t)cp.n_slices + 2) * M * M * sizeof(double) + 3 * (size_t)M * sizeof(double2) +
          (size_t)(M + kDcT - 1) / kDcT * 256 * sizeof(double) + 8 * 256;
 }
@@ -728,21 +731,24 @@ int decorrelate_design(Context* c, int32_t M, int64_t N, double* zeta, int32_t* 
     return fail(FMC_EINVAL, "correlation reduction needs M <= 1024 and M < N < 2^31");
   const size_t MN = (size_t)M * N;
   const CovPlan cp(M, N);
-  void *z, *rz, *inv, *bkt, *off, *fill, *perm, *part, *cv, *lt, *di, *mean, *lohi, *sts;
+  void *z, *rz, *inv, *part, *cv, *lt, *di, *mean, *sts;
+  void *bkt = nullptr, *off = nullptr, *fill = nullptr, *perm = nullptr, *lohi = nullptr;
   int rc;
   if ((rc = c->ensure("dc_z", MN * sizeof(double), &z))) return rc;
   if ((rc = c->ensure("dc_rz", MN * sizeof(int32_t), &rz))) return rc;
   if ((rc = c->ensure("dc_inv", MN * sizeof(int32_t), &inv))) return rc;
-  if ((rc = c->ensure("dc_bkt", MN * sizeof(int32_t), &bkt))) return rc;
-  if ((rc = c->ensure("dc_off", MN * sizeof(int32_t), &off))) return rc;
-  if ((rc = c->ensure("dc_fill", MN * sizeof(int32_t), &fill))) return rc;
-  if ((rc = c->ensure("dc_perm", MN * sizeof(int32_t), &perm))) return rc;
+  if (!ranked_in_lds(N)) {
+    if ((rc = c->ensure("dc_bkt", MN * sizeof(int32_t), &bkt))) return rc;
+    if ((rc = c->ensure("dc_off", MN * sizeof(int32_t), &off))) return rc;
+    if ((rc = c->ensure("dc_fill", MN * sizeof(int32_t), &fill))) return rc;
+    if ((rc = c->ensure("dc_perm", MN * sizeof(int32_t), &perm))) return rc;
+    if ((rc = c->ensure("dc_lohi", (size_t)M * sizeof(double2), &lohi))) return rc;
+  }
   if ((rc = c->ensure("dc_part", (size_t)cp.n_slices * M * M * sizeof(double), &part))) return rc;
   if ((rc = c->ensure("dc_c", (size_t)M * M * sizeof(double), &cv))) return rc;
   if ((rc = c->ensure("dc_lt", (size_t)M * M * sizeof(double), &lt))) return rc;
   if ((rc = c->ensure("dc_di", (size_t)(M + kDcT - 1) / kDcT * 256 * sizeof(double), &di))) return rc;
   if ((rc = c->ensure("dc_mean", (size_t)M * sizeof(double), &mean))) return rc;
-  if ((rc = c->ensure("dc_lohi", (size_t)M * sizeof(double2), &lohi))) return rc;
   if ((rc = c->ensure("dc_status", 256, &sts))) return rc;
   double* Z = (double*)z;
   double* mu = (double*)mean;
