@@ -42,6 +42,15 @@ constexpr int kDcCholThreads = 512;
 // Longest rows ranked in LDS: two 32-bit words per entry, and with its value.
 constexpr int64_t kDcRowMax = 20000, kDcRowValues = 10200;
 constexpr int kDcRankThreads = 1024;
+// Comparisons inside buckets, per entry of the row and workgroup, from which a row is
+// sorted instead; workgroups of a row at most (k_dc_rank_row).
+constexpr int kDcCrowd = 192, kDcRankSplit = 16;
+
+// Static LDS of k_dc_rank_row; it and the arrays of the longest rows fit a CU's 160 KB.
+constexpr size_t kDcRankStatic = kDcRankThreads / 64 * (2 * sizeof(double) + 2 * sizeof(int32_t));
+static_assert(kDcRankStatic + kDcRowValues * sizeof(double) + (2 * kDcRowValues + 1) * sizeof(int32_t) <= 160 * 1024 &&
+                  kDcRankStatic + (2 * kDcRowMax + 1) * sizeof(int32_t) <= 160 * 1024,
+              "LDS of the rows ranked in LDS");
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
@@ -526,6 +535,18 @@ __global__ void __launch_bounds__(256) k_dc_rank(int64_t N, const double* __rest
 // from memory again).  A thread keeps its entries in registers.  The global form's
 // counters and orders make six passes with an atomic per entry and pass to L2: 350
 // us for 300 rows of 1e4, 42 us here.
+//
+// Counting inside a bucket is quadratic in its entries.  Where a design has fewer
+// rows than the chip has CUs, gridDim.y workgroups form a row's buckets, each for
+// itself, and count in a share of them (the share of a bucket follows from its offset,
+// which is the same in all).  A row whose counting would still cost more than sorting
+// it (an outlier that stretches the range, few distinct values, heavy tails) is
+// sorted by the first workgroup: runs of 1, 2, 4, ... entries of the order merge, each
+// entry finding its place in the other run by bisection, and the arrays of offsets and
+// order take turns.  Whole reduction of 16 rows of 2e4, ms, by one workgroup that counts /
+// here / by the global form: normal values 0.22 / 0.15 / 0.36, rounded to 0.05 1.5 / 0.30
+// / 0.77, with an outlier 87 / 1.3 / 10; kDcCrowd is where sorting takes over, within a
+// tenth of the best from 128 to 300.
 template <bool VALUES>
 __global__ void __launch_bounds__(kDcRankThreads) k_dc_rank_row(int N, const double* __restrict__ V,
                                                                 int32_t* __restrict__ R,
@@ -536,7 +557,7 @@ __global__ void __launch_bounds__(kDcRankThreads) k_dc_rank_row(int N, const dou
   int32_t* s_off = reinterpret_cast<int32_t*>(VALUES ? s_val + N : s_val);
   int32_t* s_perm = s_off + N + 1;
   __shared__ double s_lo[kDcRankThreads / 64], s_hi[kDcRankThreads / 64];
-  __shared__ int32_t s_sum[kDcRankThreads / 64];
+  __shared__ int32_t s_sum[kDcRankThreads / 64], s_work[kDcRankThreads / 64];
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const int64_t row = (int64_t)blockIdx.x * N;
   const double* v = V + row;
@@ -571,13 +592,65 @@ __global__ void __launch_bounds__(kDcRankThreads) k_dc_rank_row(int N, const dou
   const double span = hi - lo;
   const double scale = (lo <= hi && span > 0.0 && span < INFINITY) ? (double)N / span : 0.0;
   if (!(lo <= hi)) lo = 0.0;
+  // The row by merging: R and inv as below.
+  auto sort_row = [&]() {
+    int32_t *src = s_off, *dst = s_perm;
+    auto key = [&](int n) { return order_key(VALUES ? s_val[n] : v[n]); };
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int n = tid + j * kDcRankThreads;
+      if (n < N) {
+        src[n] = n;
+        if constexpr (VALUES) s_val[n] = x[j];
+      }
+    }
+    __syncthreads();
+    for (int len = 1; len < N; len *= 2) {
+#pragma unroll 4
+      for (int j = 0; j < kPer; ++j) {
+        const int p = tid + j * kDcRankThreads;
+        if (p < N) {
+          const int n = src[p];
+          const uint64_t k = key(n);
+          const int base = p & ~(2 * len - 1);         // of the two runs
+          const int other = base + ((p & len) ? 0 : len);  // the one without p
+          int lo = min(other, N), hi = min(other + len, N);
+          const int o0 = lo;
+          while (lo < hi) {  // entries of the other run before mine: by value, then by index
+            const int mid = (lo + hi) / 2, m = src[mid];
+            const uint64_t km = key(m);
+            if (km < k || (km == k && m < n))
+              lo = mid + 1;
+            else
+              hi = mid;
+          }
+          dst[base + (p & (len - 1)) + (lo - o0)] = n;
+        }
+      }
+      __syncthreads();
+      int32_t* t = src;
+      src = dst;
+      dst = t;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int p = tid + j * kDcRankThreads;
+      if (p < N) {
+        if (R) R[row + src[p]] = p;
+        if (inv) inv[row + p] = src[p];
+      }
+    }
+  };
+  auto bucket = [&](double y) {
+    const double f = (y - lo) * scale;
+    return !(f >= 0.0) ? 0 : !(f < (double)N) ? N - 1 : (int32_t)f;  // NaN, -inf; +inf, top
+  };
   int32_t bkt[kPer], slot[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const int n = tid + j * kDcRankThreads;
     if (n < N) {
-      const double f = (x[j] - lo) * scale;
-      bkt[j] = !(f >= 0.0) ? 0 : !(f < (double)N) ? N - 1 : (int32_t)f;  // NaN, -inf; +inf, top
+      bkt[j] = bucket(x[j]);
       slot[j] = atomicAdd(&s_off[bkt[j]], 1);
     }
   }
@@ -586,7 +659,28 @@ __global__ void __launch_bounds__(kDcRankThreads) k_dc_rank_row(int N, const dou
     const int per = (N + kDcRankThreads - 1) / kDcRankThreads;
     const int q0 = tid * per, q1 = min(N, q0 + per);
     int32_t mine = 0;
-    for (int q = q0; q < q1; ++q) mine += s_off[q];
+    int32_t work = 0;    // comparisons: the sum of the counts' squares (N <= 20000: below 2^31)
+    bool crowd = false;  // one bucket costs more than the sort by itself
+    for (int q = q0; q < q1; ++q) {
+      const int32_t c = s_off[q];
+      mine += c;
+      work += c * c;
+      crowd = crowd || c * c > kDcCrowd * N;
+    }
+    for (int w = 32; w > 0; w >>= 1) work += __shfl_xor(work, w, 64);
+    if (__builtin_amdgcn_ballot_w64(crowd) != 0) work = -1;
+    if (lane == 0) s_work[wave] = work;
+    __syncthreads();
+    work = 0;
+    crowd = false;
+    for (int w = 0; w < kDcRankThreads / 64; ++w) {
+      crowd = crowd || s_work[w] < 0;
+      work += s_work[w];
+    }
+    if (crowd || work / kDcCrowd > N * (int)gridDim.y) {  // uniform
+      if (blockIdx.y == 0) sort_row();
+      return;
+    }
     int32_t up = mine;  // inclusive over the wave
     for (int w = 1; w < 64; w <<= 1) {
       const int32_t o = __shfl_up(up, w, 64);
@@ -614,21 +708,26 @@ __global__ void __launch_bounds__(kDcRankThreads) k_dc_rank_row(int N, const dou
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int n = tid + j * kDcRankThreads;
-    if (n < N) {
-      const int32_t o0 = s_off[bkt[j]], o1 = s_off[bkt[j] + 1];
-      const uint64_t key = order_key(x[j]);
-      int32_t r = o0;
-      for (int32_t p = o0; p < o1; ++p) {
-        const int32_t m = s_perm[p];
-        const uint64_t km = order_key(VALUES ? s_val[p] : v[m]);
-        r += (km < key) || (km == key && m < n);
-      }
-      if (R) R[row + n] = r;
-      if (inv) inv[row + r] = n;
+  // in the order of the buckets: the lanes of a wave walk the same few of them.  My
+  // share: the buckets that start in [lo_p, hi_p)
+  const int lo_p = (int)((int64_t)blockIdx.y * N / gridDim.y), hi_p = (int)((int64_t)(blockIdx.y + 1) * N / gridDim.y);
+#pragma unroll 1
+  for (int p = lo_p + tid; p < N; p += kDcRankThreads) {
+    const int32_t n = s_perm[p];
+    const double y = VALUES ? s_val[p] : v[n];
+    const int32_t b = bucket(y), o0 = s_off[b], o1 = s_off[b + 1];
+    if (o0 < lo_p) continue;  // the share before has it
+    if (o0 >= hi_p) break;
+    const uint64_t key = order_key(y);
+    int32_t r = o0;
+#pragma unroll 4
+    for (int32_t q = o0; q < o1; ++q) {
+      const int32_t m = s_perm[q];
+      const uint64_t km = order_key(VALUES ? s_val[q] : v[m]);
+      r += (km < key) || (km == key && m < n);
     }
+    if (R) R[row + n] = r;
+    if (inv) inv[row + r] = n;
   }
 }
 
@@ -692,13 +791,16 @@ struct RankBufs {
 void launch_rank(int32_t M, int64_t N, const double* V, const RankBufs& b, int32_t* R,
                  int32_t* inv, hipStream_t st) {
   const size_t words = (size_t)(2 * N + 1) * sizeof(int32_t);
+  // workgroups per row: as many as leave each a CU of its own, for rows long enough that
+  // counting may weigh
+  const unsigned split = N < 4096 ? 1u : (unsigned)std::max(1, std::min(kDcRankSplit, 256 / M));
   if (N <= kDcRowValues) {
-    hipLaunchKernelGGL(k_dc_rank_row<true>, dim3((unsigned)M), dim3(kDcRankThreads),
+    hipLaunchKernelGGL(k_dc_rank_row<true>, dim3((unsigned)M, split), dim3(kDcRankThreads),
                        words + (size_t)N * sizeof(double), st, (int)N, V, R, inv);
     return;
   }
   if (ranked_in_lds(N)) {
-    hipLaunchKernelGGL(k_dc_rank_row<false>, dim3((unsigned)M), dim3(kDcRankThreads), words, st,
+    hipLaunchKernelGGL(k_dc_rank_row<false>, dim3((unsigned)M, split), dim3(kDcRankThreads), words, st,
                        (int)N, V, R, inv);
     return;
   }
