@@ -10,89 +10,104 @@
 namespace fmc {
 
 // ---------------------------------------------------------------------------
-// LHS (Sec. IV-B).  Row i = p*K + j follows the reindexing of Sec. IV-A; a
-// workgroup takes `per` samples of a row per thread, sample-fastest so the stores
-// coalesce.
+// LHS (Sec. IV-B).  Row i = p*K + j follows the reindexing of Sec. IV-A; samples
+// run along the threads so that the stores coalesce.
 //
 // Bound by integer multiplications.  The stratum permutation's round function
 // depends on the right half (h bits) and the round's key only, so for h <= kLhsTabBits
-// (N <= 2^18) the workgroup tabulates it for its row: eight tables of 2^h values, and a
-// round is one LDS read instead of two 64-bit multiplications, four to six times per
-// element (a wave walks as long as its last lane).  300 rows of 1e4 samples: 139 ->
-// 68 us; 1000 rows of 5e4: 1.53 -> 0.79 ms.  Designs below kLhsTabMin values, which
-// a launch does not fill the chip with, take a sample per thread and no table (300
-// rows of 200: 9.6 us, with the table 10.4).
+// (N <= 2^18) a workgroup can tabulate it for its row: eight tables of 2^h values, and a
+// round is one LDS read instead of two 64-bit multiplications, 4^h / N times per
+// element (a wave walks as long as its last lane).  300 rows of 1e4 samples: 132 ->
+// 65 us; 1000 rows of 5e4: 1.53 -> 0.79 ms.
+//
+// The rule (launch_lhs): the table form takes eight samples per thread and the
+// tables' time first, 20 to 30 us in all however few the rows; the other's time goes with
+// the M 4^h candidates walked.  us with / without tables: 60 rows of 8000 (0.98e6
+// candidates) 33 / 37, 250 of 1500 (1.02e6) 34 / 40, 120 of 2000 (0.49e6) 34 / 23, 20 of
+// 8000 (0.33e6) 32 / 18; short tables (N <= 1024): 500 of 1000 (0.51e6) 15 / 18, 250 of
+// 1000 (0.26e6) 12 / 12.
 // ---------------------------------------------------------------------------
 constexpr int kLhsPer = 8, kLhsTabBits = 9;
-constexpr int64_t kLhsTabMin = 1 << 17;
 
-template <bool TAB>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
-k_lhs(uint64_t seed, int32_t M, int64_t N, int32_t sampler, int h, int per,
-      int32_t* __restrict__ strata, double* __restrict__ zeta) {
+// the values of (row i, sample n) in stratum s, and of simple random sampling
+__device__ __forceinline__ double lhs_value(uint64_t seed, int64_t i, int64_t n, int64_t s, int64_t N) {
+  return ppnd16(stratum_prob(s, u01(draw64(seed, (uint64_t)i, (uint64_t)n, 0, kTagJitter)), N));
+}
+
+// A sample per thread, either sampler.
+__global__ void __launch_bounds__(256) k_lhs(uint64_t seed, int32_t M, int64_t N, int32_t sampler,
+                                             int h, int32_t* __restrict__ strata,
+                                             double* __restrict__ zeta) {
+  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t i = blockIdx.y;
   __shared__ uint64_t s_key[8];
-  __shared__ uint16_t s_tab[TAB ? 8 << kLhsTabBits : 1];  // [round][right half]
   if (sampler == 0) {
     if (threadIdx.x < 8) s_key[threadIdx.x] = draw64(seed, (uint64_t)i, threadIdx.x, 0, kTagPerm);
     __syncthreads();
-    if constexpr (TAB) {
-      const uint64_t mask = (1ULL << h) - 1ULL;
-      for (int q = threadIdx.x; q < (8 << h); q += 256)
-        s_tab[q] = (uint16_t)(mix64(((uint64_t)q & mask) ^ s_key[q >> h]) & mask);
-      __syncthreads();
-    }
   }
-  const int64_t n0 = (int64_t)blockIdx.x * 256 * per + threadIdx.x;
+  if (n >= N || i >= M) return;
+  double z;
+  int32_t s_out;
+  if (sampler == 0) {
+    uint64_t key[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) key[r] = s_key[r];
+    const int64_t s = lhs_stratum(key, N, h, n);
+    z = lhs_value(seed, i, n, s, N);
+    s_out = (int32_t)s;
+  } else {
+    z = ppnd16(u01(draw64(seed, (uint64_t)i, (uint64_t)n, 0, kTagSrs)));
+    s_out = -1;
+  }
+  const int64_t o = i * N + n;
+  if (strata) strata[o] = s_out;
+  zeta[o] = z;
+}
+
+// LHS with the tables: kLhsPer samples per thread.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
+k_lhs_tab(uint64_t seed, int64_t N, int h, int32_t* __restrict__ strata, double* __restrict__ zeta) {
+  const int64_t i = blockIdx.y;
+  __shared__ uint64_t s_key[8];
+  __shared__ uint16_t s_tab[8 << kLhsTabBits];  // [round][right half]
+  if (threadIdx.x < 8) s_key[threadIdx.x] = draw64(seed, (uint64_t)i, threadIdx.x, 0, kTagPerm);
+  __syncthreads();
+  const uint32_t mask = (1u << h) - 1u;
+  for (int q = threadIdx.x; q < (8 << h); q += 256)
+    s_tab[q] = (uint16_t)(mix64(((uint64_t)q & mask) ^ s_key[q >> h]) & mask);
+  __syncthreads();
+  const int64_t n0 = (int64_t)blockIdx.x * 256 * kLhsPer + threadIdx.x;
 #pragma unroll 1
-  for (int e = 0; e < per; ++e) {
+  for (int e = 0; e < kLhsPer; ++e) {
     const int64_t n = n0 + 256 * e;
     if (n >= N) return;
-    double z;
-    int32_t s_out;
-    if (sampler == 0) {
-      int64_t s;
-      if constexpr (TAB) {
-        const uint32_t mask = (1u << h) - 1u;
-        uint32_t x = (uint32_t)n;
-        do {
-          uint32_t L = x >> h, R = x & mask;
+    uint32_t x = (uint32_t)n;
+    do {
+      uint32_t L = x >> h, R = x & mask;
 #pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            const uint32_t t = L ^ s_tab[(r << h) + R];
-            L = R;
-            R = t;
-          }
-          x = (L << h) | R;
-        } while (x >= (uint32_t)N);
-        s = x;
-      } else {
-        uint64_t key[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) key[r] = s_key[r];
-        s = lhs_stratum(key, N, h, n);
+      for (int r = 0; r < 8; ++r) {
+        const uint32_t t = L ^ s_tab[(r << h) + R];
+        L = R;
+        R = t;
       }
-      const double U = u01(draw64(seed, (uint64_t)i, (uint64_t)n, 0, kTagJitter));
-      z = ppnd16(stratum_prob(s, U, N));
-      s_out = (int32_t)s;
-    } else {
-      z = ppnd16(u01(draw64(seed, (uint64_t)i, (uint64_t)n, 0, kTagSrs)));
-      s_out = -1;
-    }
+      x = (L << h) | R;
+    } while (x >= (uint32_t)N);
     const int64_t o = i * N + n;
-    if (strata) strata[o] = s_out;
-    zeta[o] = z;
+    if (strata) strata[o] = (int32_t)x;
+    zeta[o] = lhs_value(seed, i, n, x, N);
   }
 }
 
 hipError_t launch_lhs(uint64_t seed, int32_t M, int64_t N, int32_t sampler, int32_t* strata,
                       double* zeta, hipStream_t st) {
   const int h = feistel_half_bits(N);
-  const bool tab = h <= kLhsTabBits && M * N >= kLhsTabMin;
-  const int per = tab ? kLhsPer : 1;
-  const dim3 grid((unsigned)((N + 256 * per - 1) / (256 * per)), (unsigned)M);
-  hipLaunchKernelGGL(tab ? k_lhs<true> : k_lhs<false>, grid, dim3(256), 0, st, seed, M, N, sampler, h,
-                     per, strata, zeta);
+  const int64_t groups = (N + 256 * kLhsPer - 1) / (256 * kLhsPer);
+  if (sampler == 0 && h <= kLhsTabBits && ((int64_t)M << (2 * h)) >= (h <= 5 ? 1 << 18 : 3 << 18))
+    hipLaunchKernelGGL(k_lhs_tab, dim3((unsigned)groups, (unsigned)M), dim3(256), 0, st, seed, N, h, strata,
+                       zeta);
+  else
+    hipLaunchKernelGGL(k_lhs, dim3((unsigned)((N + 255) / 256), (unsigned)M), dim3(256), 0, st, seed, M, N,
+                       sampler, h, strata, zeta);
   return hipGetLastError();
 }
 
