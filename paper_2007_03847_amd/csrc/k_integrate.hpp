@@ -704,6 +704,17 @@ __host__ __device__ constexpr bool rotated_form() {
   return sizeof(R) == 8;
 }
 
+// The group integrator in its lean form: four exchanges per step, a stage each,
+// instead of two, and the processes always through the exchange row.  About forty
+// registers less, for the systems whose rows of Y leave no room for them (a spilled
+// row comes back in every stage).  us per step, 4000 samples, with two exchanges / lean:
+// FP64 14 machines 4.4 / 2.1, 20 machines 26 / 16, 45 machines 247 / 145; FP32 20 machines
+// 2.6 / 2.9, 30 machines 3.8 / 3.5, general processes 17.6 / 3.6, 45 machines 102 / 25.
+template <typename R, int NG>
+__host__ __device__ constexpr bool lean_form() {
+  return sizeof(R) == 8 ? NG >= 16 : NG >= 32;
+}
+
 // (1 - cos d, sin d) turned by E0: dE = E0 (e^{j d} - 1) = -omc + j sd
 template <typename R>
 __device__ __forceinline__ void turn(R e0r, R e0i, R& omc, R& sd) {
@@ -777,14 +788,15 @@ struct GroupStats {
 // the state for a following chunk.  GEN: the processes are the general Ito
 // processes of a.sde.
 //
-// Processes: with one machine per lane and at most one process at a machine, the
+// Processes: with one machine per lane and at most one process at a machine (and not in
+// the lean form), the
 // lane of the machine owns its process and adds the injection itself (no exchange:
 // the wave reads ten pairs per stage instead of fourteen values for ten machines
 // and four process slots, and drops the product with the 0/1 injection matrix);
 // else lane g owns processes g, g + L, ... and publishes the injected powers in
 // the exchange row.  Which of the two holds is the same for all waves and chunks:
 // it comes from the packed owner machines, which an event leaves alone.
-template <typename R, int NG, int PM, int L, int WPB, int D, bool GEN = false>
+template <typename R, int NG, int PM, int L, int WPB, int D, bool GEN = false, bool LEAN = lean_form<R, NG>()>
 __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
                                           unsigned char* lds, GroupStats st, bool keep_state) {
   using Sh = GroupShape<R, NG, PM, L, WPB, D>;
@@ -845,9 +857,10 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
   // my processes: pid[r], or none (PM)
   int pid[PQ];
   bool local = false;
+  constexpr bool kLocal = G == 1 && !LEAN;
 #pragma unroll
   for (int r = 0; r < PQ; ++r) pid[r] = lane_on && g + L * r < P ? g + L * r : PM;
-  if constexpr (G == 1 && PQ == 1) {
+  if constexpr (kLocal) {
     int mine = PM, n_mine = 0;
 #pragma unroll
     for (int p = PM - 1; p >= 0; --p)
@@ -856,7 +869,11 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
         ++n_mine;
       }
     local = __builtin_amdgcn_ballot_w64(n_mine > 1) == 0;
-    if (local) pid[0] = mine;
+    if (local) {
+      pid[0] = mine;
+#pragma unroll
+      for (int r = 1; r < PQ; ++r) pid[r] = PM;
+    }
   }
   R theta[PQ], sigma[PQ];
   bool own[PQ];
@@ -891,7 +908,7 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
     for (int p = 0; p < PM; ++p) {
       const int i = g * G + q;
       binc[q][p] = i < NG ? cf[Lp.binc() + i * PM + p] : R(0);
-      if (G == 1 && PQ == 1 && local && p == pid[0]) binl = binc[q][p];
+      if (kLocal && local && p == pid[0]) binl = binc[q][p];
     }
 
   // the process slots p >= P of my trajectory's exchange rows stay zero
@@ -910,20 +927,23 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
   // stages 1 and 2, then 3 and 4, share one rotation, one exchange and one pass
   // over the rows of Y.
   //
-  // Network part of a pair of stages at angles d[h], h = 0, 1: rotation, exchange
+  // (The lean form takes a stage at a time: H = 1.)
+  //
+  // Network part of H stages at angles d[h]: rotation, exchange
   // and, per machine, sum_k Z_ik eps_k (cr, ci); in the plain form sum_k Y_ik dE_k
   // of the rotated EMFs' deviations dE = -omc + j sd, omc and sd then turned by E0.
-  R sd[2][G], omc[2][G], cr[2][G], ci[2][G];
-  auto network = [&](const R (&d)[2][G], const R (&pub)[2][PQ]) {
-    rotation_stages<R, 2, G>(d, live, live_mask, sd, omc);
+  constexpr int H = LEAN ? 1 : 2;
+  R sd[H][G], omc[H][G], cr[H][G], ci[H][G];
+  auto network = [&](const R (&d)[H][G], const R (&pub)[H][PQ]) {
+    rotation_stages<R, H, G>(d, live, live_mask, sd, omc);
     if constexpr (!ROT) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < H; ++h)
 #pragma unroll
         for (int q = 0; q < G; ++q) turn(e0r[q], e0i[q], omc[h][q], sd[h][q]);
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < H; ++h) {
 #pragma unroll
       for (int q = 0; q < G; ++q) {
         // a machine without EMF has a zero column of Z and turns by zero
@@ -943,7 +963,7 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
       // scheduler would otherwise spend hoisting all of them
       if ((k & 3) == 0 && k > 0) asm volatile("" ::: "memory");
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < H; ++h) {
         const R2 e = xch[h][tl][k];  // eps = -e.x + j e.y
 #pragma unroll
         for (int q = 0; q < G; ++q) {
@@ -960,7 +980,7 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
   };
   // injected powers of my machines in stage h
   auto injection = [&](int h, const R (&pub)[PQ], R (&inj)[G]) {
-    if (G == 1 && PQ == 1 && local) {  // wave-uniform
+    if (kLocal && local) {  // wave-uniform
       inj[0] = binl * pub[0];
       return;
     }
@@ -1179,42 +1199,47 @@ __device__ __forceinline__ void group_run(const IntegArgs<R>& a, int64_t tile,
     }
     // the angles' derivatives are w_b times the stage speeds: their sum runs
     // over the speeds, and w_b sits in the step constants
-    R d[2][G], u[2][G], kw[G], inj[G], su[G], sa[G];
+    R d[H][G], u[2][G], kw[G], inj[G], su[G], sa[G];
+    using Pub = const R (*)[H][PQ];
 #pragma unroll
     for (int q = 0; q < G; ++q) {
       d[0][q] = yd[q];
-      d[1][q] = yd[q] + hw2 * yw[q];
+      if constexpr (H == 2) d[1][q] = yd[q] + hw2 * yw[q];
     }
-    network(d, *reinterpret_cast<const R (*)[2][PQ]>(&pub[0]));
+    network(d, *reinterpret_cast<Pub>(&pub[0]));
     injection(0, pub[0], inj);
     accel(0, yw, inj, kw);
 #pragma unroll
     for (int q = 0; q < G; ++q) {
+      if constexpr (H == 1) d[0][q] = yd[q] + hw2 * yw[q];
       u[0][q] = yw[q] + h2 * kw[q];
       su[q] = yw[q] + R(2) * u[0][q];
       sa[q] = kw[q];
-      d[0][q] = yd[q] + hw2 * u[0][q];
     }
-    injection(1, pub[1], inj);
-    accel(1, u[0], inj, kw);
+    if constexpr (H == 1) network(d, *reinterpret_cast<Pub>(&pub[1]));
+    injection(H - 1, pub[1], inj);
+    accel(H - 1, u[0], inj, kw);
 #pragma unroll
     for (int q = 0; q < G; ++q) {
+      d[0][q] = yd[q] + hw2 * u[0][q];
       u[1][q] = yw[q] + h2 * kw[q];
       su[q] += R(2) * u[1][q];
       sa[q] += R(2) * kw[q];
-      d[1][q] = yd[q] + hw * u[1][q];
+      if constexpr (H == 2) d[1][q] = yd[q] + hw * u[1][q];
     }
-    network(d, *reinterpret_cast<const R (*)[2][PQ]>(&pub[2]));
+    network(d, *reinterpret_cast<Pub>(&pub[2]));
     injection(0, pub[2], inj);
     accel(0, u[1], inj, kw);
 #pragma unroll
     for (int q = 0; q < G; ++q) {
+      if constexpr (H == 1) d[0][q] = yd[q] + hw * u[1][q];
       u[0][q] = yw[q] + dt * kw[q];
       su[q] += u[0][q];
       sa[q] += R(2) * kw[q];
     }
-    injection(1, pub[3], inj);
-    accel(1, u[0], inj, kw);
+    if constexpr (H == 1) network(d, *reinterpret_cast<Pub>(&pub[3]));
+    injection(H - 1, pub[3], inj);
+    accel(H - 1, u[0], inj, kw);
 #pragma unroll
     for (int q = 0; q < G; ++q) {
       yd[q] += dw6 * su[q];
@@ -1297,6 +1322,35 @@ k_rk4_group(IntegArgs<R> a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[Sh::lds_bytes];
   GroupStats st{reinterpret_cast<double2*>(a.partial) + (int64_t)blockIdx.x * (a.S + 1) * a.V, 0};
   group_run<R, NG, PM, L, WPB, D>(a, blockIdx.x, lds, st, true);
+}
+
+template <typename R, int NG, int PM, int L, int WPB, bool GEN>
+__global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(3)))
+k_rk4_group_lean(IntegArgs<R> a) {
+  constexpr int D = WPB == 1 ? 4 : 8;
+  using Sh = GroupShape<R, NG, PM, L, WPB, D>;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[Sh::lds_bytes];
+  GroupStats st{reinterpret_cast<double2*>(a.partial) + (int64_t)blockIdx.x * (a.S + 1) * a.V, 0};
+  group_run<R, NG, PM, L, WPB, D, GEN, true>(a, blockIdx.x, lds, st, true);
+}
+
+// 16 machines in FP32 fit three waves per SIMD in the lean form, two in the other: a
+// launch of more than two and at most three waves per SIMD takes the lean one (returns
+// whether it did).  us per step, 14 machines, general processes, lean / other: 8000
+// samples (2.0 waves) 2.4 / 2.3, 8300 3.1 / 3.7, 12000 (2.9) 3.1 / 3.8, 16000 4.9 / 4.6,
+// 24000 6.9 / 6.9.
+template <typename R, int NG, int PM, int L, int WPB, bool GEN>
+bool launch_third_wave(const IntegArgs<R>& a, int64_t n_groups, hipStream_t st) {
+  if constexpr (sizeof(R) == 4 && NG == 16 && L > 1) {
+    constexpr int64_t kSimds = 1024;
+    const int64_t waves = n_groups * WPB;
+    if (waves > 2 * kSimds && waves <= 3 * kSimds) {
+      hipLaunchKernelGGL((k_rk4_group_lean<R, NG, PM, L, WPB, GEN>), dim3((unsigned)n_groups), dim3(64 * WPB),
+                         0, st, a);
+      return true;
+    }
+  }
+  return false;
 }
 
 // The same for general Ito processes (IntegArgs::sde), instantiated in their

@@ -15,7 +15,7 @@ hipError_t launch_integrate_gen_f32(int variant_id, const IntegArgs<float>& a, i
     if constexpr (L == 1)                                                                   \
       hipLaunchKernelGGL((k_rk4_lane<float, NG, PM, true>), dim3((unsigned)n_groups), dim3(64), 0, \
                          st, a);                                                             \
-    else                                                                                     \
+    else if (!launch_third_wave<float, NG, PM, L, WPB, true>(a, n_groups, st))               \
       hipLaunchKernelGGL((k_rk4_group_gen<float, NG, PM, L, WPB>), dim3((unsigned)n_groups),   \
                          dim3(64 * WPB), 0, st, a);                                          \
     return hipGetLastError();                                                                \
