@@ -346,7 +346,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
   };
 
   const R dt = a.dt, h2 = a.dt * R(0.5), dt6 = a.dt / R(6);
-  const R hw2 = h2 * a.wb, hw = dt * a.wb, dw6 = dt6 * a.wb;
+  const R hw2 = h2 * a.wb, hw = dt * a.wb;
   const R inv_n = R(1) / (R)a.n_ref;
   // the next step's path values load a step ahead; a lane without a process loads
   // the first one's of the first sample and masks it (its sigma is zero, that path
@@ -398,7 +398,7 @@ __device__ __forceinline__ void team_run(const IntegArgs<R>& a, int NG, int64_t 
     accel(1, u, k);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      yd[q] += dw6 * su[q];
+      yd[q] += angle_step(dt6, a.wb, su[q]);
       yw[q] += dt6 * (sa[q] + k[q]);
     }
     yx += dt6 * (((k1 + R(2) * k2) + R(2) * k3) + k4);
