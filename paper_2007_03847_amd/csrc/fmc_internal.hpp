@@ -39,7 +39,8 @@ struct CanonLayout {
 // Packed coefficients of one integrator variant (NG machines, PM processes,
 // padded with inert entries), in the variant's arithmetic type.
 // Plain form (one trajectory per lane): Y, I0, res, D, 1/(2H) as they are.
-// Rotated form (lanes per trajectory, teams): every machine's quantities in the
+// Rotated form (lanes per trajectory and teams in FP64; their FP32 kernels take the
+// plain one, see rotated_form): every machine's quantities in the
 // frame of its own EMF at the operating point and scaled by its 1/(2H), so that
 // with eps_k = e^{j d_k} - 1 the acceleration is
 //   res - D u + inj - Re(eps_i conj J_i) - Re(conj(1 + eps_i) sum_k Z_ik eps_k),

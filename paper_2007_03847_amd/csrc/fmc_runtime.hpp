@@ -37,8 +37,9 @@ struct Context {
   hipStream_t bstream = nullptr;     // capture stream of the batched form
   hipStream_t gstream = nullptr;     // KLE contractions overlapped with the integrator
   hipEvent_t gev[4] = {};            // [b]: paths of buffer b ready, [2+b]: buffer b consumed
-  // batched form: one stream per size class so that a tick's class launches
-  // share the chip (forked from and joined back into bstream inside the graph)
+  // batched form: the streams that a batch's per-scenario launches and, four of them,
+  // a tick's size classes are spread over so that they share the chip (forked from
+  // and joined back into bstream inside the graph)
   hipStream_t cstream[kSideStreams] = {};
   hipEvent_t cev[kSideStreams + 1] = {};  // [x]: stream x joins, [kSideStreams]: fork
   std::map<std::string, std::pair<uint64_t, hipGraphExec_t>> graphs;  // shape -> (gen, graph)

@@ -659,14 +659,13 @@ __global__ void __launch_bounds__(64) k_rk4_lane(IntegArgs<R> a) {
 // Group variant: L lanes share one trajectory (any L <= 64; a wave holds
 // floor(64/L) trajectories and leaves the remaining lanes idle), lane g owns
 // the G = ceil(NG/L) machines g*G .. g*G+G-1 and the rows of Y for them (held
-// in registers, read once).  Per stage each lane rotates its own machines, the
-// (dRe E~, dIm E~) pairs of a trajectory are exchanged through LDS (the lanes
-// of a trajectory are in one wave, whose LDS operations complete in order, so
-// only a compiler-level wavefront fence is needed), and each lane forms the
-// network currents of its rows.  Every lane integrates the P disturbance
-// processes of its trajectory (cheap) so that each can add the injections of
-// its own machines.  A workgroup of WPB waves merges the statistics of its
-// trajectories once per step.
+// in registers, read once).  Twice per step (four times in the lean form) each lane
+// rotates its own machines for the coming stages, the pairs of a trajectory are
+// exchanged through LDS (the lanes of a trajectory are in one wave, whose LDS
+// operations complete in order, so only a compiler-level wavefront fence is needed),
+// and each lane forms the network sums of its rows.  A disturbance process is
+// integrated by one lane (group_run says which).  A workgroup of WPB waves reduces the
+// statistics of its trajectories over several collected steps at once.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
