@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(256) k_dc_rank(int64_t N, const double* __rest
 // values (rows up to kDcRowValues; else the values of a bucket's entries are read
 // from memory again).  A thread keeps its entries in registers.  The global form's
 // counters and orders make six passes with an atomic per entry and pass to L2: 350
-// us for 300 rows of 1e4, 42 us here.
+// us for 300 rows of 1e4, 48 us here.
 //
 // Counting inside a bucket is quadratic in its entries.  Where a design has fewer
 // rows than the chip has CUs, gridDim.y workgroups form a row's buckets, each for
